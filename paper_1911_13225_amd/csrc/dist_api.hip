@@ -752,6 +752,13 @@ static int mlp_grid(dist_ctx* ctx, long long rows, int prec) {
   return (int)std::max(1LL, std::min<long long>(tiles, ctx->n_cu));
 }
 
+// Workgroups of a decoder query over `rows` rows: one per run of the smallest
+// tile, at most one per CU (the rows are dealt out evenly).
+static int eval_grid(dist_ctx* ctx, long long rows, int prec) {
+  const long long runs = (rows + mlp_granule(prec) - 1) / mlp_granule(prec);
+  return (int)std::max(1LL, std::min<long long>(runs, ctx->n_cu));
+}
+
 // March all images of a workspace from their coarsest level to completion.
 int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_params* prm, hipStream_t st,
               float* t_hist) {
@@ -855,7 +862,7 @@ int run_finalize(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trac
     }
     {
       TimedLaunch tl(ctx, 1, st, fo.hit_count, 6);
-      launch_eval(np, ea, mlp_grid(ctx, 6LL * n_img * hw, np), st);
+      launch_eval(np, ea, eval_grid(ctx, 6LL * n_img * hw, np), st);
     }
     launch_normals(w->pool, w->imgs, w->hits, fo.hit_count, n_img * hw, w->fv, prm->normal_delta, normal, w->nraw,
                    st);
@@ -1638,7 +1645,7 @@ extern "C" int dist_sdf_eval(dist_ctx* ctx, const float* points, const int32_t* 
     ea.f_out = f;
     {
       TimedLaunch tl(ctx, 1, st);
-      launch_eval(precision, ea, mlp_grid(ctx, n, precision), st);
+      launch_eval(precision, ea, eval_grid(ctx, n, precision), st);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) rc = dist_set_error(DIST_EHIP, "eval launch failed: %s", hipGetErrorString(e));
@@ -1685,7 +1692,7 @@ extern "C" int dist_sdf_eval_noalloc(dist_ctx* ctx, const float* points, const i
   ea.n = n;
   ea.n_lat = n_latents;
   ea.f_out = f;
-  launch_eval(precision, ea, mlp_grid(ctx, n, precision), st);
+  launch_eval(precision, ea, eval_grid(ctx, n, precision), st);
   HIPCHK(hipGetLastError());
   return DIST_OK;
 }

@@ -211,6 +211,7 @@ constexpr size_t kDwLds = (size_t)2 * 2 * 128 * kDwLd * 2;  // two buffers of bo
 void launch_dw(int precision, const DwArgs& a, hipStream_t s);
 
 int mlp_tile_rows(int precision);                 // rays per MLP tile
+int mlp_granule(int precision);                   // smallest forward tile: rows are dealt out in runs of it
 int adj_tile_rows(int precision);                 // samples per adjoint tile
 size_t mlp_smem_bytes(int precision, const NetDev& net);
 size_t adj_mask_words(int precision, const NetDev& net);   // per workgroup

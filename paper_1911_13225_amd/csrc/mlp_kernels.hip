@@ -519,7 +519,9 @@ __device__ __forceinline__ void gemm_f32(f32x16 (&acc)[MTW][NTW], const Sm<0>& s
         for (int i = 0; i < MTW; ++i)
 #pragma unroll
           for (int j = 0; j < NTW; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(p.a[sl][j][sidx], p.b[cb][i][sidx], acc[i][j], 0, 0, 0);
+            // the packed fragment holds its four columns in the order 0, 2, 1, 3
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(p.a[sl][j][((sidx & 1) << 1) | (sidx >> 1)],
+                                                             p.b[cb][i][sidx], acc[i][j], 0, 0, 0);
       {
         const int kn = min(ks + D, ksteps - 1);
 #pragma unroll
@@ -930,7 +932,9 @@ __device__ __forceinline__ void ep_vjp(const NetDev& net, const EpCtx& ec, f32x1
 // Run one layer (accumulator init + GEMM + barrier + epilogue + barrier) for an
 // output width N (128, 256 or 512 after padding): WN waves split N into groups
 // of NTW 32-wide tiles; the NW / WN wave groups split the rows into MTW tiles.
-template <int P, int MR, int MTW, int NTW, int WN, int MODE, bool CAP, bool SKIP, int NOUT = 1>
+// A 32-row tile of a 128-wide layer has work for 4 of 8 waves; the others only
+// keep the barriers.
+template <int P, int NW, int MR, int MTW, int NTW, int WN, int MODE, bool CAP, bool SKIP, int NOUT = 1>
 __device__ __forceinline__ void layer_run(const NetDev& net, const EpCtx& ec, const Sm<P>& s, const void* wp,
                                           const void* wlo, int ksteps, int nbytes) {
   // lane-dependent addressing is recomputed per layer (see opaque()); the wave
@@ -939,6 +943,8 @@ __device__ __forceinline__ void layer_run(const NetDev& net, const EpCtx& ec, co
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   const int nw = wave % WN, mg = wave / WN;
   const int nt0 = nw * NTW, mt0 = mg * MTW;
+  constexpr bool IDLE = WN * (MR / 32 / MTW) < NW;
+  const bool on = !IDLE || mg == 0;
   f32x16 acc[MTW][NTW];
   // the VJP's ReLU mask words are requested before the GEMM, so their latency
   // (HBM for saved masks) hides behind it (the bf16 layout has no registers to
@@ -954,27 +960,31 @@ __device__ __forceinline__ void layer_run(const NetDev& net, const EpCtx& ec, co
       for (int j = 0; j < NTW; ++j)
         mb[i][j] = ec.mk.p[mask_at(ec.mk, max(mask_row(ec.mk, s, (mt0 + i) * 32 + r), 0), ec.layer, nt0 + j)];
   };
-  if constexpr (VJP && EARLY) load_masks();
-  if constexpr (VJP) acc_mfma_start<P, MTW, NTW>(acc, nullptr, nt0, lane);
-  else if constexpr (SKIP) acc_bias<P, MTW, NTW, true>(acc, ec, s, nt0, mt0, lane);
-  else acc_mfma_start<P, MTW, NTW>(acc, net.bfrag[ec.layer], nt0, lane);
-  if constexpr (P == 1) {
-    gemm_bf16<MTW, NTW, 4>(acc, s, (const bf16x8*)wp, ksteps, nt0, mt0, lane, nbytes);
-  } else if constexpr (P == 2) {
-    gemm_split<MTW, NTW, !VJP, VJP ? 4 : 2>(acc, s, (const bf16x8*)wp, (const bf16x8*)wlo, ksteps, nt0, mt0, lane,
-                                         nbytes);
-  } else {
-    gemm_f32<MTW, NTW>(acc, s, (const f32x4*)wp, ksteps, nt0, mt0, lane, nbytes);
+  if (on) {
+    if constexpr (VJP && EARLY) load_masks();
+    if constexpr (VJP) acc_mfma_start<P, MTW, NTW>(acc, nullptr, nt0, lane);
+    else if constexpr (SKIP) acc_bias<P, MTW, NTW, true>(acc, ec, s, nt0, mt0, lane);
+    else acc_mfma_start<P, MTW, NTW>(acc, net.bfrag[ec.layer], nt0, lane);
+    if constexpr (P == 1) {
+      gemm_bf16<MTW, NTW, 4>(acc, s, (const bf16x8*)wp, ksteps, nt0, mt0, lane, nbytes);
+    } else if constexpr (P == 2) {
+      gemm_split<MTW, NTW, !VJP, VJP ? 4 : 2>(acc, s, (const bf16x8*)wp, (const bf16x8*)wlo, ksteps, nt0, mt0, lane,
+                                           nbytes);
+    } else {
+      gemm_f32<MTW, NTW>(acc, s, (const f32x4*)wp, ksteps, nt0, mt0, lane, nbytes);
+    }
   }
   __syncthreads();
-  if constexpr (MODE == EP_ACT) ep_act<P, MTW, NTW, false, CAP>(ec, acc, s, nt0, mt0, lane);
-  if constexpr (MODE == EP_ACT_MASK) ep_act<P, MTW, NTW, true, CAP>(ec, acc, s, nt0, mt0, lane);
-  if constexpr (MODE == EP_LAST) ep_last<P, MR, MTW, NTW, false, CAP, NOUT>(net, ec, acc, s, nt0, mt0, nw, lane);
-  if constexpr (MODE == EP_LAST_ADJ) ep_last<P, MR, MTW, NTW, true, CAP, NOUT>(net, ec, acc, s, nt0, mt0, nw, lane);
-  if constexpr (VJP) {
-    constexpr bool GP = MODE == EP_VJP;
-    if constexpr (!EARLY) load_masks();
-    ep_vjp<P, MTW, NTW, WN, CAP, GP>(net, ec, acc, s, nt0, mt0, mg, nw, lane, mb);
+  if (on) {
+    if constexpr (MODE == EP_ACT) ep_act<P, MTW, NTW, false, CAP>(ec, acc, s, nt0, mt0, lane);
+    if constexpr (MODE == EP_ACT_MASK) ep_act<P, MTW, NTW, true, CAP>(ec, acc, s, nt0, mt0, lane);
+    if constexpr (MODE == EP_LAST) ep_last<P, MR, MTW, NTW, false, CAP, NOUT>(net, ec, acc, s, nt0, mt0, nw, lane);
+    if constexpr (MODE == EP_LAST_ADJ) ep_last<P, MR, MTW, NTW, true, CAP, NOUT>(net, ec, acc, s, nt0, mt0, nw, lane);
+    if constexpr (VJP) {
+      constexpr bool GP = MODE == EP_VJP;
+      if constexpr (!EARLY) load_masks();
+      ep_vjp<P, MTW, NTW, WN, CAP, GP>(net, ec, acc, s, nt0, mt0, mg, nw, lane, mb);
+    }
   }
   __syncthreads();
   if constexpr (CAP) {
@@ -987,29 +997,155 @@ __device__ __forceinline__ void layer_run(const NetDev& net, const EpCtx& ec, co
   }
 }
 
+// ---------------------------------------------------------------------------
+// 16-row float32 tiles (forward only, 4 waves).  A float32 tile is bound by
+// the matrix cores whatever its rows hold, so a tile with few rows (the tail
+// of a march, a small query batch) runs on 16x16x4 MFMAs: half the work of 32
+// rows.  Both instructions accumulate one product after the other with one
+// rounding each, so with the contraction taken in the order of gemm_f32
+// (0, 4, 1, 5, 2, 6, 3, 7 of every 8) a row's values are the same bit for bit
+// as in a taller tile.  A lane reads its operands of two MFMAs as 8 of the 16
+// bytes that a lane of the 32-row tile reads (see k_pack's column order).
+// Lane (r, g4) holds in acc[j][e] the feature 16 (nt0 + j) + 4 g4 + e of row r.
+// ---------------------------------------------------------------------------
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <int NTW>
+__device__ __forceinline__ void gemm_f32_m16(f32x4 (&acc)[NTW], const Sm<0>& s, const void* wp, int ksteps, int nt0,
+                                             int lane, int nbytes) {
+  static_assert(NTW % 2 == 0, "16-output tiles come in pairs (one packed 32-row fragment)");
+  const int r = lane & 15, g4 = lane >> 4;
+  const __amdgpu_buffer_rsrc_t rs = frag_rsrc(wp, nbytes);
+  const int voff = (r + 32 * (g4 & 1)) * 16 + 8 * (g4 >> 1);
+  auto ld_w = [&](int j, int ks) {
+    return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(
+        rs, voff, (((nt0 + j) >> 1) * ksteps + ks) * 1024 + (j & 1) * 256, 0));
+  };
+  // the lane's k of the first MFMA of an 8-step: 4 (g4 & 1) + (g4 >> 1), of the second two further
+  const char* arow = s.act + (size_t)r * s.rowb + 16 * (g4 & 1) + 4 * (g4 >> 1);
+  constexpr int D = 4;
+  f32x2 w[D][NTW];
+  float b[2][2];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) w[d][j] = ld_w(j, d);
+    __builtin_amdgcn_sched_barrier(0);     // prologue loads stay in stage order
+  }
+  b[0][0] = *(const float*)arow;
+  b[0][1] = *(const float*)(arow + 8);
+  for (int k0 = 0; k0 < ksteps; k0 += D) {
+    const char* ab = arow + 32 * k0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      // the next step's activations (after the layer's last step one chunk
+      // past K, inside the row's padding, not used)
+      b[(d & 1) ^ 1][0] = *(const float*)(ab + 32 * (d + 1));
+      b[(d & 1) ^ 1][1] = *(const float*)(ab + 32 * (d + 1) + 8);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NTW; ++j)
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[d][j][i], b[d & 1][i], acc[j], 0, 0, 0);
+      const int kn = min(k0 + d + D, ksteps - 1);
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) w[d][j] = ld_w(j, kn);
+      __builtin_amdgcn_sched_barrier(0);   // keep the prefetch distance
+    }
+  }
+  mfma_drain();
+}
+
+template <int NTW, bool LAST, bool SKIP, int NOUT>
+__device__ __forceinline__ void layer_run_m16(const NetDev& net, const EpCtx& ec, const Sm<0>& s, const void* wp,
+                                              int ksteps, int nbytes) {
+  const int t = opaque((int)threadIdx.x);
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  const int nt0 = wave * NTW;
+  const int r = lane & 15, g4 = lane >> 4;
+  f32x4 acc[NTW];
+#pragma unroll
+  for (int j = 0; j < NTW; ++j) {
+    const int n = 16 * (nt0 + j) + 4 * g4;
+    if constexpr (!SKIP) {
+      const float4 b = ld4(ec.bias + n);
+      acc[j] = f32x4{b.x, b.y, b.z, b.w};
+    } else {
+      const float4 p = s.pts[r];
+      const float4 b = ld4(ec.biasS_lat + (size_t)s.lat[r] * ec.wpad + n);
+      const float4 wx = ld4(ec.wsp + n), wy = ld4(ec.wsp + ec.wpad + n), wz = ld4(ec.wsp + 2 * ec.wpad + n);
+      acc[j][0] = fmaf(wx.x, p.x, fmaf(wy.x, p.y, fmaf(wz.x, p.z, b.x)));
+      acc[j][1] = fmaf(wx.y, p.x, fmaf(wy.y, p.y, fmaf(wz.y, p.z, b.y)));
+      acc[j][2] = fmaf(wx.z, p.x, fmaf(wy.z, p.y, fmaf(wz.z, p.z, b.z)));
+      acc[j][3] = fmaf(wx.w, p.x, fmaf(wy.w, p.y, fmaf(wz.w, p.z, b.w)));
+    }
+  }
+  gemm_f32_m16<NTW>(acc, s, wp, ksteps, nt0, lane, nbytes);
+  __syncthreads();
+  if constexpr (!LAST) {
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) {
+      const float v[4] = {fmaxf(acc[j][0], 0.f), fmaxf(acc[j][1], 0.f), fmaxf(acc[j][2], 0.f), fmaxf(acc[j][3], 0.f)};
+      store4<0>(s, r, 16 * (nt0 + j) + 4 * g4, 0, v);
+    }
+  } else {
+    // output layer: the sums of ep_last in its order.  Its lane g of a row
+    // walks features 8 q + 4 g + e of the wave's 32-feature tiles; here those
+    // lie alternately with lanes g and g + 2 of the row, which hand the sum on
+    const int wstride = net.wpad[net.nl - 2];
+#pragma unroll
+    for (int c = 0; c < NOUT; ++c) {
+      float sum = 0.f;
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) {
+        const float4 w4 = ld4(net.wlast + c * wstride + 16 * (nt0 + j) + 4 * g4);
+        const float wl[4] = {w4.x, w4.y, w4.z, w4.w};
+        auto chain = [&](float a) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a = fmaf(wl[e], fmaxf(acc[j][e], 0.f), a);
+          return a;
+        };
+        sum = __shfl_xor(chain(sum), 32);       // valid in lanes g4 >= 2
+        sum = __shfl_xor(chain(sum), 32);       // valid in lanes g4 < 2
+      }
+      const float tot = sum + __shfl_xor(sum, 16);
+      if (g4 == 0) s.part[(c * 8 + wave) * 16 + r] = tot;
+    }
+  }
+  __syncthreads();
+}
+
 // One layer of output width N and contracted width K; returns the number of
 // wave groups that wrote output-layer partial sums.
 // SKIP: the layer reads [h, z, p] (its bias is per latent plus W_p p).
 template <int P, int NW, int MR, int MODE, bool CAP, bool SKIP = false, int NOUT = 1>
 __device__ __forceinline__ int layer(const NetDev& net, const EpCtx& ec, const Sm<P>& s, const void* wp,
                                      const void* wlo, int N, int K) {
-  constexpr int MT = MR / 32;
   const int ksteps = K / (P ? 16 : 8);
   const int nbytes = N * K * (P ? 2 : 4);       // the layer's packed fragment array
-  static_assert(NW == 4 || NW == 8, "4 or 8 waves");
-  if constexpr (NW == 8) {
-    if (N == 512) layer_run<P, MR, MT, 2, 8, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
-    else if (N == 256) layer_run<P, MR, MT, 1, 8, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
-    else {
-      layer_run<P, MR, MT / 2, 1, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
+  if constexpr (MR == 16) {
+    static_assert(P == kPrecF32 && NW == 4 && (MODE == EP_ACT || MODE == EP_LAST) && !CAP, "float32 forward only");
+    constexpr bool LAST = MODE == EP_LAST;
+    if (N == 512) layer_run_m16<8, LAST, SKIP, NOUT>(net, ec, s, wp, ksteps, nbytes);
+    else if (N == 256) layer_run_m16<4, LAST, SKIP, NOUT>(net, ec, s, wp, ksteps, nbytes);
+    else layer_run_m16<2, LAST, SKIP, NOUT>(net, ec, s, wp, ksteps, nbytes);
+    return 4;
+  } else {
+    constexpr int MT = MR / 32;
+    static_assert(NW == 4 || NW == 8, "4 or 8 waves");
+    if constexpr (NW == 8) {
+      if (N == 512) layer_run<P, NW, MR, MT, 2, 8, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
+      else if (N == 256) layer_run<P, NW, MR, MT, 1, 8, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
+      else {
+        layer_run<P, NW, MR, (MT > 1 ? MT / 2 : 1), 1, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
+        return 4;
+      }
+      return 8;
+    } else {
+      if (N == 512) layer_run<P, NW, MR, MT, 4, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
+      else if (N == 256) layer_run<P, NW, MR, MT, 2, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
+      else layer_run<P, NW, MR, MT, 1, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
       return 4;
     }
-    return 8;
-  } else {
-    if (N == 512) layer_run<P, MR, MT, 4, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
-    else if (N == 256) layer_run<P, MR, MT, 2, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
-    else layer_run<P, MR, MT, 1, 4, MODE, CAP, SKIP, NOUT>(net, ec, s, wp, wlo, ksteps, nbytes);
-    return 4;
   }
 }
 
@@ -1310,61 +1446,107 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
 // ---------------------------------------------------------------------------
 // Plain decoder queries (explicit points, or the 6-point normal stencil)
 // ---------------------------------------------------------------------------
+// A workgroup takes its rows in the tallest tiles first and the rest in the
+// tile that holds it at the least cost.  Measured per tile with every CU busy
+// (DeepSDF decoder): bf16 128 / 64 / 32 rows 86 / 52 / 41 us (below 64 rows the
+// weights' way into the CU is the bound), split 64 / 32 rows 128 / 88 us,
+// float32 64 / 32 / 16 rows 372 / 200 / 107 us (bound by the matrix cores
+// throughout).
+template <int P> constexpr int kGranule = P == kPrecF32 ? 16 : 32;
+
 template <int P>
-__global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_eval(EvalArgs a) {
+__device__ __forceinline__ int next_tile(int left) {
+  if constexpr (P == kPrecBF16) return left > 64 ? 128 : (left > 32 ? 64 : 32);
+  else if constexpr (P == kPrecF32) return left > 48 ? 64 : (left > 16 ? 32 : 16);
+  else return left > 32 ? 64 : 32;
+}
+
+// Rows [first, last) of `count` that this workgroup owns.  The rows are dealt
+// out in runs of the smallest tile, so that every workgroup has the same
+// number to one run; where the share leaves a rest that takes a full tile
+// anyway, in full tiles, so that some workgroups have none of the last round
+// and leave the others their bandwidth (bf16, 20,011 points: 79 us against
+// 83 us with 79 rows to every CU).
+template <int P>
+__device__ __forceinline__ void row_share(long long count, long long& first, long long& last) {
   constexpr int M = Cfg<P>::M;
-  Sm<P> s(dyn_smem, a.net.kmax);
+  const long long G = gridDim.x, runs = (count + kGranule<P> - 1) / kGranule<P>;
+  const int rest = (int)((runs + G - 1) / G * kGranule<P> % M);
+  const int g = rest && next_tile<P>(rest) == M ? M : kGranule<P>;
+  const long long t = (count + g - 1) / g;
+  first = t * blockIdx.x / G * g;
+  last = min(count, t * (blockIdx.x + 1) / G * g);
+}
+
+template <int P, int M>
+__device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, long long base, int k) {
   const int tid = threadIdx.x;
-  const long long count = a.mode == 0 ? a.n : 6ll * (long long)(*a.hit_count);
   // stencil queries may keep their ReLU masks for the backward (the host
   // only asks for it when every stencil index fits an int)
-  const bool keep = P != kPrecBF16 && a.mode == 1 && a.mask_out != nullptr;
+  const bool keep = P != kPrecBF16 && M > 16 && a.mode == 1 && a.mask_out != nullptr;
   const int ntmax = a.net.kmax / 32;
   const MaskRef mk{a.mask_out, (a.net.nl - 1) * ntmax, ntmax, true};
-  for (long long tile = blockIdx.x; tile * M < count; tile += gridDim.x) {
-    if (tid < M) {
-      const long long idx = tile * M + tid;
-      float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-      int lt = 0, row = -1;
-      if (idx < count) {
-        row = (int)min(idx, (long long)INT_MAX);
-        if (a.mode == 0) {
-          p = make_float4(a.pts[3 * idx], a.pts[3 * idx + 1], a.pts[3 * idx + 2], 0.f);
-          lt = min(max(a.lat[idx], 0), a.n_lat - 1);
-        } else {
-          const int h = (int)(idx / 6), j = (int)(idx - 6ll * h);
-          const int r = a.hits[h];
-          const ImgDesc& im = a.imgs[a.pool.img[r]];
-          const float4 d = a.pool.d[r];
-          const float dd = d.w + a.pool.flast[r];          // Eq. 1 ray distance
-          float q[3] = {fmaf(dd, d.x, im.c[0]), fmaf(dd, d.y, im.c[1]), fmaf(dd, d.z, im.c[2])};
-          const int ax = j >> 1;
-          q[ax] = (j & 1) ? q[ax] - a.delta : q[ax] + a.delta;
-          p = make_float4(q[0], q[1], q[2], 0.f);
-          lt = im.latent;
-        }
-      }
-      s.pts[tid] = p;
-      s.lat[tid] = lt;
-      s.rid[tid] = row;
-    }
-    __syncthreads();
-    int wn;
-    if constexpr (P != kPrecBF16)
-      wn = keep ? mlp_forward<P, kFwdWaves<P>, Cfg<P>::M, true, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, mk)
-                : mlp_forward<P, kFwdWaves<P>, Cfg<P>::M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
-    else
-      wn = mlp_forward<P, kFwdWaves<P>, Cfg<P>::M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
-    if (tid < M && s.rid[tid] >= 0) {
-      float m = a.net.blast;
-      for (int w = 0; w < wn; ++w) m += s.part[w * M + tid];
-      a.f_out[tile * M + tid] = sdf_from_m(s.pts[tid], m);
-      if (keep) {
-        const float th = tanhf(m);
-        a.dtanh_out[tile * M + tid] = 1.f - th * th;
+  if (tid < M) {
+    const long long idx = base + tid;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    int lt = 0, row = -1;
+    if (tid < k) {
+      row = (int)min(idx, (long long)INT_MAX);
+      if (a.mode == 0) {
+        p = make_float4(a.pts[3 * idx], a.pts[3 * idx + 1], a.pts[3 * idx + 2], 0.f);
+        lt = min(max(a.lat[idx], 0), a.n_lat - 1);
+      } else {
+        const int h = (int)(idx / 6), j = (int)(idx - 6ll * h);
+        const int r = a.hits[h];
+        const ImgDesc& im = a.imgs[a.pool.img[r]];
+        const float4 d = a.pool.d[r];
+        const float dd = d.w + a.pool.flast[r];          // Eq. 1 ray distance
+        float q[3] = {fmaf(dd, d.x, im.c[0]), fmaf(dd, d.y, im.c[1]), fmaf(dd, d.z, im.c[2])};
+        const int ax = j >> 1;
+        q[ax] = (j & 1) ? q[ax] - a.delta : q[ax] + a.delta;
+        p = make_float4(q[0], q[1], q[2], 0.f);
+        lt = im.latent;
       }
     }
-    __syncthreads();
+    s.pts[tid] = p;
+    s.lat[tid] = lt;
+    s.rid[tid] = row;
+  }
+  __syncthreads();
+  int wn;
+  if constexpr (P != kPrecBF16 && M > 16)
+    wn = keep ? mlp_forward<P, kFwdWaves<P>, M, true, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, mk)
+              : mlp_forward<P, kFwdWaves<P>, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+  else
+    wn = mlp_forward<P, kFwdWaves<P>, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+  if (tid < M && s.rid[tid] >= 0) {
+    float m = a.net.blast;
+    for (int w = 0; w < wn; ++w) m += s.part[w * M + tid];
+    a.f_out[base + tid] = sdf_from_m(s.pts[tid], m);
+    if (keep) {
+      const float th = tanhf(m);
+      a.dtanh_out[base + tid] = 1.f - th * th;
+    }
+  }
+  __syncthreads();
+}
+
+template <int P>
+__global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_eval(EvalArgs a) {
+  Sm<P> s(dyn_smem, a.net.kmax);
+  const long long count = a.mode == 0 ? a.n : 6ll * (long long)(*a.hit_count);
+  long long base, last;
+  row_share<P>(count, base, last);
+  while (base < last) {
+    const int left = (int)min(last - base, (long long)Cfg<P>::M);
+    int m = next_tile<P>(left);
+    if (m == 16 && a.mode == 1) m = 32;               // the masks of a stencil query need whole words
+    const int k = min(left, m);
+    if (P == kPrecF32 && m == 16) eval_tile<P, P == kPrecF32 ? 16 : 32>(a, s, base, k);
+    else if (m == 32) eval_tile<P, 32>(a, s, base, k);
+    else if (P == kPrecBF16 && m == 64) eval_tile<P, 64>(a, s, base, k);
+    else eval_tile<P, Cfg<P>::M>(a, s, base, k);
+    base += k;
   }
 }
 
@@ -1608,6 +1790,7 @@ __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // Host-side helpers
 // ---------------------------------------------------------------------------
 int mlp_tile_rows(int precision) { return rows_for(precision); }
+int mlp_granule(int precision) { return precision == kPrecF32 ? kGranule<kPrecF32> : kGranule<kPrecBF16>; }
 
 int adj_tile_rows(int precision) { return mlp_tile_rows(precision); }
 size_t mlp_smem_bytes(int precision, const NetDev& net) { return smem_bytes_for(precision, net.kmax, net.nout); }
@@ -1987,7 +2170,8 @@ void launch_vjp_saved(int precision, const AdjArgs& a, int grid, hipStream_t st)
 //   bf16: fragment (rt, ks) = 64 lanes x 8 values, lane l holds row rt*32 + l%32,
 //         columns ks*16 + (l/32)*8 + 0..7
 //   f32 : fragment (rt, ks) = 64 lanes x 4 values, lane l holds row rt*32 + l%32,
-//         columns ks*8 + (l/32)*4 + 0..3
+//         columns ks*8 + (l/32)*4 + {0, 2, 1, 3}: a lane of the 16-row tile
+//         (gemm_f32_m16) takes one half of the 16 bytes
 // Rows are output features (or input features when transposed), columns the
 // contracted dimension; entries outside the matrix are zero.
 // ---------------------------------------------------------------------------
@@ -1998,7 +2182,8 @@ __global__ void k_pack(int precision, int transpose, const float* __restrict__ W
   const int per = precision ? 8 : 4;
   const int ksteps = cols_pad / kfrag;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-    const int e = (int)(i % per);
+    int e = (int)(i % per);
+    if (!precision) e = ((e & 1) << 1) | (e >> 1);
     const long long fl = i / per;
     const int lane = (int)(fl % 64);
     const long long frag = fl / 64;

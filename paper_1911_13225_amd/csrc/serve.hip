@@ -358,7 +358,8 @@ void Server::complete(sched::Job* j) {
     ea.delta = q.prm.normal_delta;
     ea.f_out = r->d_fv;
     const long long rows = 6LL * r->n_views * r->hw;
-    launch_eval(kPrecSplit, ea, (int)std::max(1LL, std::min<long long>((rows + 63) / 64, ctx->n_cu)), s->st);
+    const int run = mlp_granule(kPrecSplit);
+    launch_eval(kPrecSplit, ea, (int)std::max(1LL, std::min<long long>((rows + run - 1) / run, ctx->n_cu)), s->st);
     launch_normals(s->pool, s->imgs, r->d_hits, r->d_hit_count, r->n_views * r->hw, r->d_fv, q.prm.normal_delta,
                    q.normal, r->d_nraw, s->st);
   }

@@ -1,0 +1,54 @@
+"""Tile heights of the decoder kernels on the GPU.
+
+A launch takes its rows in tiles of 128, 64, 32 or 16 rows, chosen by their
+number.  A row's value does not depend on the tile that holds it, so every
+count around a tile's edge is checked against the same rows of one large
+launch, bit for bit, and against the FP64 oracle.
+"""
+import numpy as np
+import pytest
+import torch
+
+import dist_inputs as di
+from _common import gpu_ctx, oracle_decoder
+
+pytestmark = pytest.mark.gpu
+
+# widths of all three padded sizes, two of them between layers and at the skip
+MIXED_SPEC = di.DecoderSpec(latent_dim=33, out_dims=(256, 200, 512, 100, 256, 1), skip_layer=2)
+SPECS = {"c1": di.C1_SPEC, "deepsdf": di.DEEPSDF_SPEC, "mixed": MIXED_SPEC}
+_CTX = {}
+
+
+def ctx_for(name):
+    """The seeded decoder with nonzero biases, and its oracle."""
+    if name not in _CTX:
+        spec = SPECS[name]
+        Ws, bs = di.make_decoder(spec, seed=5)
+        rng = np.random.Generator(np.random.PCG64(6))
+        bs = [(0.02 * rng.standard_normal(b.shape)).astype(np.float32) for b in bs]
+        from oracle import dist_oracle as O
+        _CTX[name] = (gpu_ctx(spec, Ws=Ws, bs=bs), O.Decoder(spec, Ws, bs))
+    return _CTX[name]
+
+
+# bounds of test_sdf_eval_*: FP32 2e-6, bf16 1e-3, split 1e-6 (x2 for the random biases' larger activations)
+@pytest.mark.parametrize("prec,tol", [(0, 4e-6), (1, 2e-3), (2, 2e-6)], ids=["fp32", "bf16", "split"])
+@pytest.mark.parametrize("name", list(SPECS))
+def test_query_rows_do_not_depend_on_the_tile(name, prec, tol):
+    from paper_1911_13225_amd import api
+    ctx, dec = ctx_for(name)
+    spec = SPECS[name]
+    n = 256 * 128 + 1                        # full tiles and a rest on every CU
+    rng = np.random.Generator(np.random.PCG64(7))
+    P = rng.uniform(-0.7, 0.7, (n, 3)).astype(np.float32)
+    Z = di.make_latents(3, spec.latent_dim, sigma=0.1)
+    lat = (np.arange(n) % 3).astype(np.int32)
+    Pt, lt, Zt = (torch.tensor(x, device="cuda") for x in (P, lat, Z))
+    full = api.dist_sdf_eval(ctx, Pt, lt, Zt, prec)
+    fo = dec.sdf(Z[lat[:300]].astype(np.float64), P[:300].astype(np.float64))
+    assert np.abs(full[:300].cpu().numpy() - fo).max() <= tol
+    for k in (1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65, 255 * 16 + 1, 256 * 16 + 1, 256 * 32 + 1, 256 * 48 + 1,
+              256 * 64 + 1, 256 * 79):
+        part = api.dist_sdf_eval(ctx, Pt[:k].contiguous(), lt[:k].contiguous(), Zt, prec)
+        assert torch.equal(part, full[:k]), k
