@@ -211,6 +211,8 @@ int dist_set_error(int code, const char* fmt, ...);
 int ctx_alloc(dist_ctx* ctx, void** p, size_t bytes);
 void ctx_free(dist_ctx* ctx, void* p, size_t bytes);
 int slots_per_image(int hw, int levels);
+// the folded biases of the codes z: bias0 [n_lat][wpad 0] and, with a skip layer, biasS [n_lat][wpad skip]
+void fold_into(const dist_ctx* ctx, const float* z, int n_lat, float* bias0, float* biasS, hipStream_t st);
 int fold_biases(dist_ctx* ctx, Workspace* w, const float* z, int n_lat, hipStream_t st);
 int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_params* prm, hipStream_t st,
               float* t_hist = nullptr);

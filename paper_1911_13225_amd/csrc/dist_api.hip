@@ -738,11 +738,16 @@ static int stage_images(Workspace* w, const std::vector<ImgDesc>& d, const std::
   return DIST_OK;
 }
 
-int fold_biases(dist_ctx* ctx, Workspace* w, const float* z, int n_lat, hipStream_t st) {
-  launch_fold_bias(ctx->bf[0], ctx->w0z, z, n_lat, ctx->L, ctx->out_dims[0], ctx->wpad[0], w->bias0_lat, st);
+void fold_into(const dist_ctx* ctx, const float* z, int n_lat, float* bias0, float* biasS, hipStream_t st) {
+  FoldArgs f{};
+  f.layer[0] = FoldLayer{ctx->bf[0], ctx->w0z, ctx->out_dims[0], ctx->wpad[0], bias0};
   if (ctx->skip >= 0)
-    launch_fold_bias(ctx->bf[ctx->skip], ctx->wsz, z, n_lat, ctx->L, ctx->out_dims[ctx->skip],
-                     ctx->wpad[ctx->skip], w->biasS_lat, st);
+    f.layer[1] = FoldLayer{ctx->bf[ctx->skip], ctx->wsz, ctx->out_dims[ctx->skip], ctx->wpad[ctx->skip], biasS};
+  launch_fold_bias(f, z, n_lat, ctx->L, st);
+}
+
+int fold_biases(dist_ctx* ctx, Workspace* w, const float* z, int n_lat, hipStream_t st) {
+  fold_into(ctx, z, n_lat, w->bias0_lat, w->biasS_lat, st);
   HIPCHK(hipGetLastError());
   return DIST_OK;
 }
@@ -1526,14 +1531,6 @@ static int color_check(dist_ctx* cctx, const dist_saved* geom, const float* zc, 
   return DIST_OK;
 }
 
-static void color_fold(dist_ctx* cctx, const float* zc, int n_lat, hipStream_t st) {
-  ColorSpace* c = cctx->col;
-  launch_fold_bias(cctx->bf[0], cctx->w0z, zc, n_lat, cctx->L, cctx->out_dims[0], cctx->wpad[0], c->bias0, st);
-  if (cctx->skip >= 0)
-    launch_fold_bias(cctx->bf[cctx->skip], cctx->wsz, zc, n_lat, cctx->L, cctx->out_dims[cctx->skip],
-                     cctx->wpad[cctx->skip], c->biasS, st);
-}
-
 extern "C" int dist_render_color(dist_ctx* cctx, const dist_saved* geom, const float* zc, int32_t n_latents,
                                  int32_t precision, float* rgb, void* stream) {
   int rc = color_check(cctx, geom, zc, n_latents, precision);
@@ -1548,7 +1545,7 @@ extern "C" int dist_render_color(dist_ctx* cctx, const dist_saved* geom, const f
   if (rc) return rc;
   ColorSpace* c = cctx->col;
   const int prec = precision == DIST_FP32 ? kPrecF32 : kPrecBF16;
-  color_fold(cctx, zc, n_latents, st);
+  fold_into(cctx, zc, n_latents, c->bias0, c->biasS, st);
   hipLaunchKernelGGL(k_fill_f32, dim3(512), dim3(256), 0, st, rgb, 3 * npix);
   launch_fill_i32(c->count, 0, 1, st);
   launch_color_hits(w->pool, w->imgs, n_img, hw, c->list, c->count, st);
@@ -1590,7 +1587,7 @@ extern "C" int dist_render_color_bwd(dist_ctx* cctx, const dist_saved* geom, con
                    adj_mask_words(prec, cctx->net[prec]) * grid);
   if (rc) return rc;
   BwdSpace* b = c->bw;
-  color_fold(cctx, zc, n_latents, st);
+  fold_into(cctx, zc, n_latents, c->bias0, c->biasS, st);
   launch_color_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, hw, n_latents, tile, g_rgb, b->bsum,
                        b->boff, b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, c->cseed,
                        b->sample_lat, std::min<long long>(cap, c->cap_seed), st);
@@ -1678,10 +1675,7 @@ extern "C" int dist_sdf_eval_noalloc(dist_ctx* ctx, const float* points, const i
   // the folded biases overwrite their whole range, so nothing needs clearing
   float* b0 = sp;
   float* bS = sp + (size_t)n_latents * ctx->wpad[0];
-  launch_fold_bias(ctx->bf[0], ctx->w0z, z, n_latents, ctx->L, ctx->out_dims[0], ctx->wpad[0], b0, st);
-  if (ctx->skip >= 0)
-    launch_fold_bias(ctx->bf[ctx->skip], ctx->wsz, z, n_latents, ctx->L, ctx->out_dims[ctx->skip],
-                     ctx->wpad[ctx->skip], bS, st);
+  fold_into(ctx, z, n_latents, b0, bS, st);
   EvalArgs ea{};
   ea.net = ctx->net[precision];
   ea.bias0_lat = b0;

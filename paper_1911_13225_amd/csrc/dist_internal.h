@@ -240,8 +240,18 @@ void launch_color_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t
 void launch_pack_bias(int precision, const float* bias, int wpad, void* dst, hipStream_t st);
 void launch_pack_w(int precision, bool transpose, const float* W, int out, int in_stride, int ncols,
                    int npad, int kpad, void* dst, hipStream_t s);
-void launch_fold_bias(const float* b, const float* Wz, const float* z, int n_lat, int L, int nout,
-                      int npad, float* dst, hipStream_t s);
+// Folded biases of the layers that read the code: layer 0 and, if npad > 0,
+// the skip layer.  dst[l][npad] = b + Wz z_l for the codes z [n_lat][L].
+struct FoldLayer {
+  const float* b;
+  const float* Wz;                 // [nout][L]
+  int nout, npad;
+  float* dst;
+};
+struct FoldArgs {
+  FoldLayer layer[2];
+};
+void launch_fold_bias(const FoldArgs& a, const float* z, int n_lat, int L, hipStream_t st);
 
 // Grouping of n explicit samples (points [n][3], seeds [n], latent ids [n],
 // clamped to [0, n_lat)) into per-latent segments padded to whole tiles of

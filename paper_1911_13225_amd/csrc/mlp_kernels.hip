@@ -2237,35 +2237,82 @@ void launch_pack_bias(int precision, const float* bias, int wpad, void* dst, hip
   hipLaunchKernelGGL(k_pack_bias, dim3((n_tiles * 64 + 255) / 256), dim3(256), 0, st, precision, bias, n_tiles, dst);
 }
 
-// dst[l][n] = b[n] + sum_j Wz[n][j] z[l][j]  (rows n >= nout are zero)
-__global__ void k_fold_bias(const float* __restrict__ b, const float* __restrict__ Wz, const float* __restrict__ z,
-                            int n_lat, int L, int nout, int npad, float* __restrict__ dst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_lat * npad) return;
-  const int l = i / npad, n = i - l * npad;
-  float acc = 0.f;
-  if (n < nout) {
-    acc = b[n];
-    const float* w = Wz + (size_t)n * L;
-    const float* zz = z + (size_t)l * L;
+// Per-latent folded biases of layer 0 and of the skip layer (blockIdx.y):
+// dst[l][n] = b[n] + sum_j Wz[n][j] z[l][j], summed in order of j (rows n >=
+// nout are zero).  Every render and query starts with it, so its latency
+// counts, not its 1 MB of weights: a workgroup requests all of its 16 rows of
+// Wz and 8 codes at once, staged in LDS (rows 4 banks apart), and the ordered
+// sums run from there, 16 rows x 8 codes side by side.  Both layers in one
+// launch: 7 us, where one thread per output reading its own row of Wz from
+// memory took 11 us for each layer (DeepSDF, one code).
+constexpr int kFoldRows = 16, kFoldLat = 8;
+__global__ __launch_bounds__(kFoldRows * kFoldLat) void k_fold_bias(FoldArgs a, const float* __restrict__ z,
+                                                                    int n_lat, int L) {
+  constexpr int NT = kFoldRows * kFoldLat;
+  extern __shared__ __attribute__((aligned(16))) float fold_smem[];
+  const FoldLayer& f = a.layer[blockIdx.y];
+  const int n0 = blockIdx.x * kFoldRows;
+  if (n0 >= f.npad) return;
+  const int ld = (L + 3) / 4 * 4 + 4;
+  float* sw = fold_smem;
+  float* sz = fold_smem + kFoldRows * ld;
+  const int t = threadIdx.x, nr = min(kFoldRows, f.nout - n0);
+  const int l0 = blockIdx.z * kFoldLat, nz = min(kFoldLat, n_lat - l0);
+  // `rows` consecutive rows of L values to LDS, 16 loads in flight per thread
+  auto stage = [&](const float* src, int rows, float* dst) {
+    const int total = rows * L;
+    for (int i0 = t; i0 < total; i0 += 16 * NT) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = src[min(i0 + u * NT, total - 1)];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int i = i0 + u * NT;
+        if (i < total) dst[i / L * ld + i % L] = v[u];
+      }
+    }
+  };
+  if (nr > 0) stage(f.Wz + (size_t)n0 * L, nr, sw);
+  stage(z + (size_t)l0 * L, nz, sz);
+  const int r = t % kFoldRows, l = t / kFoldRows, n = n0 + r;
+  float acc = n < f.nout ? f.b[n] : 0.f;
+  __syncthreads();
+  if (l >= nz || n >= f.npad) return;
+  if (n < f.nout) {
+    const float *w = sw + r * ld, *zz = sz + l * ld;
     int j = 0;
-    // 32 weights requested before the 32 products are summed in order
-    for (; j + 32 <= L; j += 32) {
-      float wv[32];
+    for (; j + 16 <= L; j += 16) {
+      float4 wv[4], zv[4];
 #pragma unroll
-      for (int u = 0; u < 32; ++u) wv[u] = w[j + u];
+      for (int u = 0; u < 4; ++u) {
+        wv[u] = ld4(w + j + 4 * u);
+        zv[u] = ld4(zz + j + 4 * u);
+      }
 #pragma unroll
-      for (int u = 0; u < 32; ++u) acc = fmaf(wv[u], zz[j + u], acc);
+      for (int u = 0; u < 4; ++u) {
+        acc = fmaf(wv[u].x, zv[u].x, acc);
+        acc = fmaf(wv[u].y, zv[u].y, acc);
+        acc = fmaf(wv[u].z, zv[u].z, acc);
+        acc = fmaf(wv[u].w, zv[u].w, acc);
+      }
     }
     for (; j < L; ++j) acc = fmaf(w[j], zz[j], acc);
   }
-  dst[i] = acc;
+  f.dst[(size_t)(l0 + l) * f.npad + n] = acc;
 }
 
-void launch_fold_bias(const float* b, const float* Wz, const float* z, int n_lat, int L, int nout, int npad,
-                      float* dst, hipStream_t st) {
-  const int total = n_lat * npad;
-  hipLaunchKernelGGL(k_fold_bias, dim3((total + 255) / 256), dim3(256), 0, st, b, Wz, z, n_lat, L, nout, npad, dst);
+void launch_fold_bias(const FoldArgs& a, const float* z, int n_lat, int L, hipStream_t st) {
+  const int npad = std::max(a.layer[0].npad, a.layer[1].npad);
+  const size_t smem = (size_t)(kFoldRows + kFoldLat) * ((L + 3) / 4 * 4 + 4) * sizeof(float);
+  // grid.z is limited to 65535 blocks: more codes than 8 x 65535 go in further launches
+  for (int l0 = 0; l0 < n_lat; l0 += kFoldLat * 65535) {
+    const int nl = std::min(n_lat - l0, kFoldLat * 65535);
+    FoldArgs f = a;
+    for (FoldLayer& y : f.layer) y.dst += (size_t)l0 * y.npad;
+    hipLaunchKernelGGL(k_fold_bias, dim3((npad + kFoldRows - 1) / kFoldRows, a.layer[1].npad ? 2 : 1,
+                                         (nl + kFoldLat - 1) / kFoldLat),
+                       dim3(kFoldRows * kFoldLat), smem, st, f, z + (size_t)l0 * L, nl, L);
+  }
 }
 
 }  // namespace dist

@@ -294,13 +294,9 @@ void Server::release(sched::Job* j) {
 // Fold the request's latent into the pooled per-latent biases: the start of
 // every render (the first, and each z-opt iteration's).
 static void fold_latent(Server* s, Request* r) {
-  const int L = s->ctx->L;
-  const float* z = s->z_pool + (size_t)r->lat * L;
-  launch_fold_bias(s->ctx->bf[0], s->ctx->w0z, z, 1, L, s->ctx->out_dims[0], s->ctx->wpad[0],
-                   s->bias0 + (size_t)r->lat * s->ctx->wpad[0], s->st);
-  if (s->ctx->skip >= 0)
-    launch_fold_bias(s->ctx->bf[s->ctx->skip], s->ctx->wsz, z, 1, L, s->ctx->out_dims[s->ctx->skip],
-                     s->ctx->wpad[s->ctx->skip], s->biasS + (size_t)r->lat * s->ctx->wpad[s->ctx->skip], s->st);
+  const dist_ctx* ctx = s->ctx;
+  fold_into(ctx, s->z_pool + (size_t)r->lat * ctx->L, 1, s->bias0 + (size_t)r->lat * ctx->wpad[0],
+            ctx->skip >= 0 ? s->biasS + (size_t)r->lat * ctx->wpad[ctx->skip] : nullptr, s->st);
 }
 
 // The request holds its ray slots, image slots and latent slot: descriptors,

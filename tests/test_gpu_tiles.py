@@ -52,3 +52,20 @@ def test_query_rows_do_not_depend_on_the_tile(name, prec, tol):
               256 * 64 + 1, 256 * 79):
         part = api.dist_sdf_eval(ctx, Pt[:k].contiguous(), lt[:k].contiguous(), Zt, prec)
         assert torch.equal(part, full[:k]), k
+
+
+@pytest.mark.parametrize("n_lat", [1, 7, 8, 9, 33])
+@pytest.mark.parametrize("name", list(SPECS))
+def test_codes_fold_one_by_one(name, n_lat):
+    """A code's folded biases do not depend on the codes beside it."""
+    from paper_1911_13225_amd import api
+    ctx, dec = ctx_for(name)
+    Z = di.make_latents(n_lat, SPECS[name].latent_dim, sigma=0.1)
+    P = np.random.Generator(np.random.PCG64(8)).uniform(-0.7, 0.7, (n_lat, 3)).astype(np.float32)
+    Pt, Zt = torch.tensor(P, device="cuda"), torch.tensor(Z, device="cuda")
+    f = api.dist_sdf_eval(ctx, Pt, torch.arange(n_lat, device="cuda", dtype=torch.int32), Zt, 0)
+    assert np.abs(f.cpu().numpy() - dec.sdf(Z.astype(np.float64), P.astype(np.float64))).max() <= 4e-6
+    for i in range(n_lat):
+        one = api.dist_sdf_eval(ctx, Pt[i:i + 1].contiguous(), torch.zeros(1, device="cuda", dtype=torch.int32),
+                                Zt[i:i + 1].contiguous(), 0)
+        assert torch.equal(one, f[i:i + 1]), i
