@@ -779,51 +779,34 @@ int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_p
   ma.biasS_lat = w->biasS_lat;
   ma.qcount = w->qcount;
   ma.t_hist = t_hist;
-  // steps before the last coarse-to-fine split: one launch per step, every
-  // image splitting after the same steps
+  ma.max_steps = prm->max_steps;
+  ma.K = prm->k_samples;
+  ma.alpha = prm->alpha;
+  ma.eps = prm->eps;
+  ma.tail_end = w->pool.cap;
+  ma.rows_done = (ctx->timing && ctx->d_rows) ? ctx->d_rows + 0 : nullptr;
+  // one launch per level: three steps of every ray, then the split that makes
+  // the next level's list; at full resolution every remaining step.  The
+  // counters hold each level's list length and its claims.
   int* tail_cnt = w->counters + prm->max_steps + 5;
-  for (int n = 0; n < 3 * L; ++n) {
-    const int lv = L - n / 3;
-    const long long rays = (long long)n_img * (hw >> (2 * lv));
-    ma.list = w->list[n & 1];
-    ma.count = w->counters + n;
-    // at a split the children replace the rays, otherwise the march step
-    // appends its survivors to the next list
-    const bool split = n % 3 == 2;
-    int* nxt = w->list[(n + 1) & 1];
-    int* ncnt = w->counters + n + 1;
-    ma.next_list = split ? nullptr : nxt;
-    ma.next_count = split ? nullptr : ncnt;
+  for (int lv = L; lv >= 0; --lv) {
+    const int i = L - lv;
+    ma.list = w->list[i & 1];
+    ma.count = w->counters + i;
+    ma.claim = w->counters + 3 + i;
+    ma.n_begin = 3 * i;
+    ma.n_end = lv > 0 ? 3 * (i + 1) : prm->max_steps;
+    ma.mark_long = lv == 1;
+    // the last split orders the full-resolution list: children of rays that
+    // graze the surface first, the others from the list's end
+    ma.count_tail = L > 0 && lv == 0 ? tail_cnt : nullptr;
     {
-      TimedLaunch tl(ctx, 0, st, ma.count, 1);
-      // the bf16 march may choose 64-row tiles, so size its grid by those
-      launch_march(prec, ma, mlp_grid(ctx, rays, prec == kPrecBF16 ? kPrecSplit : prec), st);
+      TimedLaunch tl(ctx, 0, st);
+      launch_march_run(prec, ma, eval_grid(ctx, (long long)n_img * (hw >> (2 * lv)), prec), st);
     }
-    // the last split orders the full-resolution list for the one-launch
-    // march: children of rays still marching first, the others from the
-    // list's end
-    if (split)
-      launch_split(w->pool, w->imgs, w->imgs_list, n_img, hw >> (2 * (lv - 1)), lv - 1, n + 1, nxt, ncnt, st,
-                   lv == 1 ? tail_cnt : nullptr, w->pool.cap);
-  }
-  // full resolution: every remaining step in one launch; the rays of the
-  // step's list are claimed into per-workgroup rings carved from the other
-  // list (grid and ring size bounded by its capacity)
-  {
-    const int n = 3 * L;
-    const long long cap = w->pool.cap;
-    const int grid = (int)std::max(1LL, std::min<long long>(ctx->n_cu, cap / 256));
-    ma.list = w->list[n & 1];
-    ma.count = w->counters + n;
-    ma.count_tail = L > 0 ? tail_cnt : nullptr;
-    ma.tail_end = w->pool.cap;
-    ma.next_list = w->list[(n + 1) & 1];
-    ma.next_count = nullptr;
-    ma.claim = w->counters + n + 1;
-    ma.ring_cap = (int)std::min<long long>(4096, cap / grid);
-    ma.rows_done = (ctx->timing && ctx->d_rows) ? ctx->d_rows + 0 : nullptr;
-    TimedLaunch tl(ctx, 0, st);
-    launch_march_ring(prec, ma, grid, st);
+    if (lv > 0)
+      launch_split(w->pool, w->imgs, w->imgs_list, n_img, hw >> (2 * (lv - 1)), lv - 1, 3 * (i + 1),
+                   w->list[(i + 1) & 1], w->counters + i + 1, st, lv == 1 ? tail_cnt : nullptr, w->pool.cap);
   }
   HIPCHK(hipGetLastError());
   return DIST_OK;

@@ -41,7 +41,7 @@ struct RayPool {
   int* img;
   uint8_t* st;
   uint8_t* n;
-  float* flast;
+  float* flast;        // last f (a ray that marched up to the last split: see MarchArgs::mark_long)
   float* rec_f;
   float* rec_t;
   uint8_t* rec_n;
@@ -91,20 +91,22 @@ struct MarchArgs {
   const float* biasS_lat;          // [n_lat][wpad_skip]
   const int* list;                 // active ray slots
   const int* count;                // number of entries in list
-  // k_march_ring: a second run of *count_tail entries stored backwards from
+  unsigned long long* qcount;      // per-image decoder queries
+  int* ecount;                     // k_march: per-image count of non-finite queries (or null)
+  // k_march_run: steps [n_begin, n_end) of every ray of the list (ACTIVE, its
+  // records empty), with the call's tracing parameters
+  int n_begin, n_end, max_steps, K;
+  float alpha, eps;
+  // a second run of *count_tail entries stored backwards from
   // list[tail_end - 1], taken after the first (or null)
   const int* count_tail;
   int tail_end;
-  unsigned long long* qcount;      // per-image decoder queries (or null)
-  int* ecount;                     // per-image count of non-finite queries (or null)
-  // rays still ACTIVE after the step are appended here (null: the caller
-  // builds the next list itself, e.g. at a coarse-to-fine split)
-  int* next_list;
-  int* next_count;
+  int* claim;                      // list entries claimed so far (starts at 0)
+  // the level before the last split (three steps): flast of a ray still
+  // marching receives how near it passes to the surface (see k_split)
+  int mark_long;
   float* t_hist;                   // [max_steps][pool.cap]: t of each ray at each of its steps (or null)
-  unsigned long long* rows_done;   // k_march_ring: queries made, added at the end (or null)
-  int* claim;                      // k_march_ring: rays of `list` claimed so far (starts at 0)
-  int ring_cap;                    // k_march_ring: ring slots per workgroup in next_list
+  unsigned long long* rows_done;   // queries made, added at the end (or null)
 };
 
 struct EvalArgs {
@@ -217,9 +219,10 @@ size_t mlp_smem_bytes(int precision, const NetDev& net);
 size_t adj_mask_words(int precision, const NetDev& net);   // per workgroup
 hipError_t mlp_setup(int precision, const NetDev& net);    // raise LDS limits
 
-void launch_march(int precision, const MarchArgs& a, int grid, hipStream_t s);
-// every remaining step in one launch (rays claimed from list into per-workgroup rings in next_list)
-void launch_march_ring(int precision, const MarchArgs& a, int grid, hipStream_t s);
+// one step of every ray of the list (bf16, the serving pool)
+void launch_march(const MarchArgs& a, int grid, hipStream_t s);
+// all steps of one coarse-to-fine level
+void launch_march_run(int precision, const MarchArgs& a, int grid, hipStream_t s);
 void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t s);
 // recompute-and-VJP: precision kPrecSplit or kPrecF32 (no bf16 variant; other
 // values launch nothing); VJP from saved masks: any precision

@@ -1200,34 +1200,47 @@ __device__ __forceinline__ float sdf_from_m(float4 p, float m) {
   return 0.5f * (r - 0.5f) + 0.05f * tanhf(m);
 }
 
-// Append `value` for every thread with flag set; one atomic per workgroup.
-// Called by all threads of the workgroup.
-template <int NT>
-__device__ __forceinline__ void wg_append(bool flag, int value, int* list, int* counter) {
-  __shared__ int wcnt[NT / 64];
-  __shared__ int base;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const unsigned long long bal = __ballot(flag);
-  const int within = __popcll(bal & ((1ull << lane) - 1ull));
-  if (lane == 0) wcnt[w] = __popcll(bal);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int tot = 0;
-    for (int i = 0; i < NT / 64; ++i) tot += wcnt[i];
-    base = tot ? atomicAdd(counter, tot) : 0;
-  }
-  __syncthreads();
-  int off = base;
-  for (int i = 0; i < w; ++i) off += wcnt[i];
-  if (flag) list[off + within] = value;
+// ---------------------------------------------------------------------------
+// Tile heights
+// ---------------------------------------------------------------------------
+// A workgroup takes its rows in the tallest tiles first and the rest in the
+// tile that holds it at the least cost.  Measured per tile with every CU busy
+// (DeepSDF decoder): bf16 128 / 64 / 32 rows 86 / 52 / 41 us (below 64 rows the
+// weights' way into the CU is the bound), split 64 / 32 rows 128 / 88 us,
+// float32 64 / 32 / 16 rows 372 / 200 / 107 us (bound by the matrix cores
+// throughout).
+template <int P> constexpr int kGranule = P == kPrecF32 ? 16 : 32;
+
+template <int P>
+__device__ __forceinline__ int next_tile(int left) {
+  if constexpr (P == kPrecBF16) return left > 64 ? 128 : (left > 32 ? 64 : 32);
+  else if constexpr (P == kPrecF32) return left > 48 ? 64 : (left > 16 ? 32 : 16);
+  else return left > 32 ? 64 : 32;
+}
+
+// Rows [first, last) of `count` that this workgroup owns.  The rows are dealt
+// out in runs of the smallest tile, so that every workgroup has the same
+// number to one run; where the share leaves a rest that takes a full tile
+// anyway, in full tiles, so that some workgroups have none of the last round
+// and leave the others their bandwidth (bf16, 20,011 points: 79 us against
+// 83 us with 79 rows to every CU).
+template <int P>
+__device__ __forceinline__ void row_share(long long count, long long& first, long long& last) {
+  constexpr int M = Cfg<P>::M;
+  const long long G = gridDim.x, runs = (count + kGranule<P> - 1) / kGranule<P>;
+  const int rest = (int)((runs + G - 1) / G * kGranule<P> % M);
+  const int g = rest && next_tile<P>(rest) == M ? M : kGranule<P>;
+  const long long t = (count + g - 1) / g;
+  first = t * blockIdx.x / G * g;
+  last = min(count, t * (blockIdx.x + 1) / G * g);
 }
 
 // ---------------------------------------------------------------------------
-// March step (Alg. 1 with aggressive steps, convergence and escape; Sec. 3.2)
+// March step of the serving pool (Alg. 1 with aggressive steps, convergence
+// and escape; Sec. 3.2): one query of every ray of the active list.
 // ---------------------------------------------------------------------------
 // Load the rays of one tile: row i < k takes ray slot rid_of(i), the other
-// rows of the M-row tile stay idle (rid -1).  With a history buffer the
-// ray's t is recorded at its own step (t_hist[n][slot], stride pool.cap).
+// rows of the M-row tile stay idle (rid -1).
 template <int P, int M, class RidOf>
 __device__ __forceinline__ void march_load(const MarchArgs& a, const Sm<P>& s, int k, RidOf rid_of) {
   const int tid = threadIdx.x;
@@ -1240,7 +1253,6 @@ __device__ __forceinline__ void march_load(const MarchArgs& a, const Sm<P>& s, i
       const float4 d = a.pool.d[r];
       p = make_float4(fmaf(d.w, d.x, im.c[0]), fmaf(d.w, d.y, im.c[1]), fmaf(d.w, d.z, im.c[2]), 0.f);
       lt = im.latent;
-      if (a.t_hist) a.t_hist[(size_t)a.pool.n[r] * a.pool.cap + r] = d.w;
     }
     s.pts[tid] = p;
     s.lat[tid] = lt;
@@ -1251,13 +1263,12 @@ __device__ __forceinline__ void march_load(const MarchArgs& a, const Sm<P>& s, i
 
 // One decoder query per loaded row and the march epilogue: running top-K of
 // |f|, convergence (|f| < eps, Eq. 1), the step limit, the aggressive step
-// t += alpha f and the unit-sphere escape test.  Returns whether this
-// thread's ray is still ACTIVE; the queries are counted per image.
+// t += alpha f and the unit-sphere escape test.  The queries are counted per
+// image.
 template <int P, int M>
-__device__ __forceinline__ bool march_eval(const MarchArgs& a, const Sm<P>& s) {
+__device__ __forceinline__ void march_eval(const MarchArgs& a, const Sm<P>& s) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wn = mlp_forward<P, kFwdWaves<P>, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
-  bool still = false;
   if (tid < M && s.rid[tid] >= 0) {
     float m = a.net.blast;
     for (int w = 0; w < wn; ++w) m += s.part[w * M + tid];
@@ -1302,7 +1313,6 @@ __device__ __forceinline__ bool march_eval(const MarchArgs& a, const Sm<P>& s) {
     }
     pl.st[r] = st;
     pl.n[r] = (uint8_t)(n + 1);
-    still = st == ST_ACTIVE;
   }
   if (a.qcount && tid < M) {
     // queries of this tile per image, one atomic per distinct image in a wave
@@ -1318,39 +1328,31 @@ __device__ __forceinline__ bool march_eval(const MarchArgs& a, const Sm<P>& s) {
       todo &= ~same;
     }
   }
-  return still;
 }
 
-// One march step over the active list: M-row tiles, the survivors appended to
-// the next list (compaction fused into the step).
-template <int P, int M>
-__device__ __forceinline__ void march_tiles(const MarchArgs& a, const Sm<P>& s, int count) {
-  const int tid = threadIdx.x;
-  for (int tile = blockIdx.x; tile * M < count; tile += gridDim.x) {
-    const int k = min(M, count - tile * M);
-    march_load<P, M>(a, s, k, [&](int i) { return a.list[tile * M + i]; });
-    const bool still = march_eval<P, M>(a, s);
-    if (a.next_list) wg_append<kFwdWaves<P> * 64>(still, still ? s.rid[tid] : 0, a.next_list, a.next_count);
+// One march step over the active list, its rays dealt out as the rows of a
+// query (row_share).
+__global__ __launch_bounds__(kFwdWaves<1> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<1> / 4, kFwdWaves<1> / 4))) void k_march(MarchArgs a) {
+  Sm<1> s(dyn_smem, a.net.kmax);
+  long long first, last;
+  row_share<1>(*a.count, first, last);
+  int base = (int)first;
+  while (base < (int)last) {
+    const int left = min((int)last - base, Cfg<1>::M), m = next_tile<1>(left);
+    auto rid_of = [&](int i) { return a.list[base + i]; };
+    const int k = min(left, m);
+    if (m == 32) {
+      march_load<1, 32>(a, s, k, rid_of);
+      march_eval<1, 32>(a, s);
+    } else if (m == 64) {
+      march_load<1, 64>(a, s, k, rid_of);
+      march_eval<1, 64>(a, s);
+    } else {
+      march_load<1, 128>(a, s, k, rid_of);
+      march_eval<1, 128>(a, s);
+    }
+    base += k;
     __syncthreads();
-  }
-}
-
-
-// The bf16 step takes 64-row tiles when they finish sooner.  A 64-row tile
-// streams the same weights for half the rows, so it is bound by the vector
-// memory path and costs about 0.77x a 128-row tile: it wins only when every
-// workgroup has at most one tile (the converging tail of the march).
-template <int P>
-__global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_march(MarchArgs a) {
-  Sm<P> s(dyn_smem, a.net.kmax);
-  const int count = *a.count;
-  if constexpr (P == kPrecBF16) {
-    const int g = gridDim.x;
-    const int r128 = (count + 128 * g - 1) / (128 * g), r64 = (count + 64 * g - 1) / (64 * g);
-    if (r64 * 77 < r128 * 100) march_tiles<P, 64>(a, s, count);
-    else march_tiles<P, 128>(a, s, count);
-  } else {
-    march_tiles<P, Cfg<P>::M>(a, s, count);
   }
 }
 
@@ -1374,70 +1376,280 @@ __device__ __forceinline__ int wg_prefix(bool flag, int* total) {
   return off + __popcll(bal & ((1ull << lane) - 1ull));
 }
 
-// Every remaining step of the march in one launch (after the last
-// coarse-to-fine split).  Each ray's trajectory depends on that ray alone, so
-// the rays need not advance in lockstep: every workgroup keeps a ring of rays
-// in its own region of a spare list (ring_cap slots), marches tiles of up to
-// M of them and puts the survivors back at the ring's end.  While it holds
-// fewer than 2M live rays it claims more from the input list (one atomic per
-// claim of up to 256), so workgroups that draw short rays take more of them
-// and the grid stays busy until the input is spent.  Small claims keep the
-// last fresh rays spread over many workgroups: with claims of 1024 the
-// workgroups that claimed last still marched hundreds of rays after the
-// others had run dry (3% of the march).  No step waits for the
-// slowest tile of the grid, and tiles stay full until a workgroup has fewer
-// than M live rays.  A ring never overflows: claims are capped by its free
-// slots and a ray returns only after leaving it.  Every ray stops within
-// max_steps queries and a workgroup leaves once a claim returns nothing and
-// its ring is empty, so every workgroup leaves the loop.
+// ---------------------------------------------------------------------------
+// The march of a batch render: every step of one coarse-to-fine level in one
+// launch (Alg. 1, Sec. 3.2; the steps after the last split run to max_steps).
+// A ray's trajectory depends on that ray alone, so the rays need not advance
+// in lockstep: a workgroup holds up to `top` rays in the rows of its tile and
+// keeps their whole state (direction, t, interval, camera centre, top-K
+// records) in LDS from the first step to the last.  After each step the rays
+// that stopped are written to the pool, the others move up and new ones are
+// claimed from the level's list into the free rows, so tiles stay full until
+// the list is spent and then shrink through the tile heights.  Global memory
+// is read once per ray instead of four dependent loads per step, which is
+// what a step of few rays waits for.
+//   Height: a single 256^2 image has some 240 rays per CU and its longest
+// rays take all 44 steps, so the launch is bound by the steps times the time
+// of one tile, and a tall tile only makes the first of them slower; a large
+// batch wants the tall tile, whose rows cost least.  march_top weighs both.
+// Measured (DeepSDF decoder, the march of a forward) against one launch per
+// coarse step and rings of rays in global memory marched in 128-row and 64-row
+// (float32: 64-row) tiles, children of all rays still marching first: bf16 one
+// image of 256^2 2.45 -> 1.80 ms, four 5.25 -> 3.60 ms, 32 24.0 -> 22.6 ms;
+// float32 one image 29.0 -> 9.3 ms; the small decoder at 32^2 0.96 -> 0.17 ms.
+// ---------------------------------------------------------------------------
+struct MarchRows {
+  float4* dt;              // direction, t
+  float4* c;               // camera centre, latent (bits)
+  float2* b;               // t_lo, t_hi
+  int* img;
+  int* n;                  // next global step
+  unsigned* rn;            // records' steps, one byte each
+  float2* fp;              // the two queries before the last one (f of steps n - 2 and n - 1)
+  float* rf;               // records [kMaxK][M]
+  float* rt;
+  __device__ MarchRows(char* base, int M) {
+    dt = (float4*)base;
+    c = dt + M;
+    b = (float2*)(c + M);
+    fp = b + M;
+    img = (int*)(fp + M);
+    n = img + M;
+    rn = (unsigned*)(n + M);
+    rf = (float*)(rn + M);
+    rt = rf + kMaxK * M;
+  }
+};
+__host__ __device__ constexpr size_t march_row_bytes() { return 16 + 16 + 8 + 8 + 4 + 4 + 4 + 2 * 4 * kMaxK; }
+
+// Smallest tile height that holds `live` rays.
 template <int P>
-__global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_march_ring(MarchArgs a) {
-  constexpr int M = Cfg<P>::M, NT = kFwdWaves<P> * 64;
-  __shared__ int claim_lds[2];
+__device__ __forceinline__ int march_height(int live) {
+  if constexpr (P == kPrecBF16) return live > 64 ? 128 : (live > 32 ? 64 : 32);
+  else if constexpr (P == kPrecF32) return live > 32 ? 64 : (live > 16 ? 32 : 16);
+  else return live > 32 ? 64 : 32;
+}
+
+// Rows to fill per tile, for n0 rays on G workgroups, nh of them expected to
+// take many steps (and first in the list), and up to S steps: the height with
+// the least estimated time, (full tiles) x (time of a tile) + (steps left to
+// the longest ray after them) x (time of the smallest tile).  Long rays that
+// find no row at the start wait for some twelve steps of others; after two
+// coarse levels they are known (the list's first nh), before any ray may be
+// one.  The tile times are those above next_tile; the queries per ray those of
+// the synthetic shapes (the choice is flat around its turning points: the next
+// height costs about 10%).  bf16, us by height 32 / 64 / 128: one image of
+// 256^2 1739 / 1941 / 2677, two 2802 / 2178 / 2938, four 5184 / 3751 / 3543;
+// float32, height 16 / 32 / 64: one image 9274 / 9414 / 15840, two 17419 /
+// 16176 / 17098.
+template <int P>
+__device__ __forceinline__ int march_top(const MarchArgs& a, int n0, int nh, int G) {
+  constexpr int H[3] = {P == kPrecF32 ? 16 : 32, P == kPrecF32 ? 32 : 64, P == kPrecBF16 ? 128 : 64};
+  constexpr float T[3] = {P == kPrecBF16 ? 41.f : (P == kPrecF32 ? 107.f : 88.f),
+                          P == kPrecBF16 ? 52.f : (P == kPrecF32 ? 200.f : 128.f),
+                          P == kPrecBF16 ? 86.f : (P == kPrecF32 ? 372.f : 128.f)};
+  const float S = (float)(a.n_end - a.n_begin), x = 1.5f / a.alpha;
+  const float q = (a.n_begin == 0 ? 8.7f : (a.n_begin == 3 ? 5.9f : 4.f)) * x * sqrtf(x);
+  const float work = (float)n0 / (float)G * fminf(q, S);
+  int best = H[0];
+  float cost = 3e38f;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const float tiles = work / (float)H[i];
+    const float lng = (float)(a.n_begin >= 6 ? nh : n0);
+    const float wait = S > 3.f ? 12.f * fmaxf(0.f, lng / ((float)H[i] * (float)G) - 1.f) : 0.f;
+    const float c = tiles * T[i] + fmaxf(0.f, S + wait - tiles) * T[0];
+    if (c < cost) {
+      cost = c;
+      best = H[i];
+    }
+  }
+  return best;
+}
+
+// How near a ray passes to the surface, from three queries f0, f1, f2 in a
+// row: with f approximated by the parabola through them (steps alpha f), its
+// least value along the ray times its curvature, f'' f - f'^2 / 2 at the last
+// query, which has no unit.  Near zero the ray grazes the surface and takes
+// many steps: on the benchmark's shapes |value| < 0.02 holds for a tenth of
+// the rays and for 98-99% of those with more than 12 steps left.
+__device__ __forceinline__ float graze(float f0, float f1, float f2, float alpha) {
+  const float s1 = (f1 - f0) / (alpha * f0), s2 = (f2 - f1) / (alpha * f1);
+  const float c = 2.f * (s2 - s1) / (alpha * (f0 + f1));
+  const float sl = s2 + 0.5f * c * alpha * f1;
+  return f2 * c - 0.5f * sl * sl;
+}
+
+template <int P>
+__global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_march_run(MarchArgs a) {
+  constexpr int M = Cfg<P>::M, NW = kFwdWaves<P>, NT = NW * 64;
+  __shared__ int claim_lds;
   Sm<P> s(dyn_smem, a.net.kmax);
-  const int tid = threadIdx.x;
-  const int nh = *a.count, n0 = nh + (a.count_tail ? *a.count_tail : 0), RC = a.ring_cap;
-  int* ring = a.next_list + (size_t)blockIdx.x * RC;
-  int head = 0, tail = 0, live = 0;
+  MarchRows rw((char*)(s.part + 8 * M), M);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const RayPool& pl = a.pool;
+  const int nh = *a.count, n0 = nh + (a.count_tail ? *a.count_tail : 0), K = a.K;
+  const int top = march_top<P>(a, n0, nh, gridDim.x), chunk = top / 2;
+  int live = 0, rb = 0, re = 0;          // rows in use; claimed list entries not loaded yet
   bool more = true;
   long long rows = 0;
   while (true) {
-    if (more && live < 2 * M) {
-      if (tid == 0) {
-        const int want = min(256, RC - live);
-        const int st = atomicAdd(a.claim, want);
-        claim_lds[0] = st;
-        claim_lds[1] = max(0, min(want, n0 - st));
-      }
+    const int need = top - live, have = min(need, re - rb);
+    int st0 = 0, got = 0;
+    if (more && have < need) {
+      const int want = max(chunk, need - have);
+      if (tid == 0) claim_lds = atomicAdd(a.claim, want);
       __syncthreads();
-      const int st = claim_lds[0], got = claim_lds[1];
-      for (int i = tid; i < got; i += NT) {
-        const int j = st + i;
-        ring[(tail + i) % RC] = j < nh ? a.list[j] : a.list[a.tail_end - 1 - (j - nh)];
-      }
-      tail += got;
-      live += got;
-      more = got > 0;
-      __syncthreads();
+      st0 = claim_lds;
+      got = max(0, min(want, n0 - st0));
+      more = got == want;
     }
-    if (live == 0) break;
-    const int k = min(M, live);
-    auto rid_of = [&](int i) { return ring[(head + i) % RC]; };
-    bool still;
-    if (P == kPrecBF16 && k <= 64) {
-      march_load<P, 64>(a, s, k, rid_of);
-      still = march_eval<P, 64>(a, s);
+    const int fresh = have + min(need - have, got);
+    if (tid >= live && tid < live + fresh) {
+      // the ray's whole state: its records start empty at every level
+      const int i = tid - live, j = i < have ? rb + i : st0 + i - have;
+      const int r = j < nh ? a.list[j] : a.list[a.tail_end - 1 - (j - nh)];
+      const int img = pl.img[r];
+      const float4 d = pl.d[r];
+      const float2 b = pl.b[r];
+      const ImgDesc& im = a.imgs[img];
+      rw.dt[tid] = d;
+      rw.c[tid] = make_float4(im.c[0], im.c[1], im.c[2], __int_as_float(im.latent));
+      rw.b[tid] = b;
+      rw.img[tid] = img;
+      rw.n[tid] = a.n_begin;
+      rw.rn[tid] = 0u;
+      for (int k = 0; k < K; ++k) {
+        rw.rf[k * M + tid] = INFINITY;
+        rw.rt[k * M + tid] = 0.f;
+      }
+      s.rid[tid] = r;
+    }
+    if (have < need) {                   // the reserve is spent; what is left of the claim replaces it
+      rb = st0 + fresh - have;
+      re = st0 + got;
     } else {
-      march_load<P, M>(a, s, k, rid_of);
-      still = march_eval<P, M>(a, s);
+      rb += have;
     }
+    live += fresh;
+    if (live == 0) break;
+    const int h = march_height<P>(live);
+    if (tid < h) {
+      float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+      int lt = 0;
+      if (tid < live) {
+        const float4 d = rw.dt[tid], c = rw.c[tid];
+        p = make_float4(fmaf(d.w, d.x, c.x), fmaf(d.w, d.y, c.y), fmaf(d.w, d.z, c.z), 0.f);
+        lt = __float_as_int(c.w);
+        if (a.t_hist) a.t_hist[(size_t)rw.n[tid] * pl.cap + s.rid[tid]] = d.w;
+      }
+      s.pts[tid] = p;
+      s.lat[tid] = lt;
+    }
+    __syncthreads();
+    int wn;
+    if (P == kPrecF32 && h == 16)
+      wn = mlp_forward<P, NW, P == kPrecF32 ? 16 : 32, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+    else if (h == 32) wn = mlp_forward<P, NW, 32, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+    else if (P == kPrecBF16 && h == 64)
+      wn = mlp_forward<P, NW, 64, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+    else wn = mlp_forward<P, NW, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+    // epilogue: top-K of |f|, convergence (Eq. 1), step limit, the aggressive
+    // step and the escape test
+    bool still = false, stop = false;
+    float f = 0.f;
+    float4 d{}, c{};
+    float2 b{}, fp{};
+    int r = 0, img = 0, n = 0;
+    unsigned rn = 0;
+    float rf[kMaxK] = {}, rt[kMaxK] = {};
+    if (tid < live) {
+      float m = a.net.blast;
+      for (int w = 0; w < wn; ++w) m += s.part[w * h + tid];
+      f = sdf_from_m(s.pts[tid], m);
+      d = rw.dt[tid];
+      c = rw.c[tid];
+      b = rw.b[tid];
+      r = s.rid[tid];
+      img = rw.img[tid];
+      n = rw.n[tid];
+      rn = rw.rn[tid];
+      fp = rw.fp[tid];
+      float rec_abs[kMaxK];
+      for (int k = 0; k < K; ++k) {
+        rf[k] = rw.rf[k * M + tid];
+        rt[k] = rw.rt[k * M + tid];
+        rec_abs[k] = fabsf(rf[k]);
+      }
+      // running K smallest |f| (ties keep the earlier step)
+      const float af = fabsf(f);
+      const int pos = topk_rank(af, rec_abs, K);
+      for (int k = K - 1; k > pos; --k) {
+        rf[k] = rf[k - 1];
+        rt[k] = rt[k - 1];
+      }
+      if (pos < K) {
+        rf[pos] = f;
+        rt[pos] = d.w;
+        const unsigned keep = (1u << (8 * pos)) - 1u;      // steps of the records before pos stay, the others move up
+        rn = (rn & keep) | ((rn & ~keep) << 8) | ((unsigned)n << (8 * pos));
+      }
+      uint8_t st;
+      if (!(af == af) || af == INFINITY) {
+        st = ST_ERROR;                         // non-finite query: stop the ray, report it
+      } else if (af < a.eps) {
+        st = ST_HIT;
+      } else if (n == a.max_steps - 1) {
+        st = ST_UNCONVERGED;
+      } else {
+        d.w = fmaf(a.alpha, f, d.w);
+        st = (d.w > b.y || d.w < b.x) ? ST_ESCAPED : ST_ACTIVE;
+      }
+      ++n;
+      still = st == ST_ACTIVE && n < a.n_end;
+      stop = !still;
+      if (stop) {
+        pl.d[r] = d;
+        pl.st[r] = st;
+        pl.n[r] = (uint8_t)n;
+        pl.flast[r] = a.mark_long && st == ST_ACTIVE ? graze(fp.x, fp.y, f, a.alpha) : f;
+        for (int k = 0; k < K; ++k) {
+          pl.rec_f[(size_t)k * pl.cap + r] = rf[k];
+          pl.rec_t[(size_t)k * pl.cap + r] = rt[k];
+          pl.rec_n[(size_t)k * pl.cap + r] = (uint8_t)(rn >> (8 * k));
+        }
+      }
+    }
+    // a stopped ray's queries, one atomic per distinct image in a wave
+    unsigned long long todo = __ballot(stop);
+    while (todo) {
+      const int leader = __ffsll((long long)todo) - 1;
+      const int li = __shfl(img, leader);
+      const bool mine = stop && img == li;
+      int q = mine ? n - a.n_begin : 0;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+      if (lane == leader) atomicAdd(&a.qcount[li], (unsigned long long)q);
+      todo &= ~__ballot(mine);
+    }
+    rows += live;
     int tot;
     const int pos = wg_prefix<NT>(still, &tot);
-    if (still) ring[(tail + pos) % RC] = s.rid[tid];
-    head += k;
-    tail += tot;
-    live += tot - k;
-    rows += k;
+    if (still) {
+      rw.dt[pos] = d;
+      rw.c[pos] = c;
+      rw.b[pos] = b;
+      rw.img[pos] = img;
+      rw.n[pos] = n;
+      rw.rn[pos] = rn;
+      if (a.mark_long) rw.fp[pos] = make_float2(fp.y, f);
+      for (int k = 0; k < K; ++k) {
+        rw.rf[k * M + pos] = rf[k];
+        rw.rt[k * M + pos] = rt[k];
+      }
+      s.rid[pos] = r;
+    }
+    live = tot;
     __syncthreads();
   }
   if (tid == 0 && a.rows_done && rows) atomicAdd(a.rows_done, (unsigned long long)rows);
@@ -1446,38 +1658,6 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
 // ---------------------------------------------------------------------------
 // Plain decoder queries (explicit points, or the 6-point normal stencil)
 // ---------------------------------------------------------------------------
-// A workgroup takes its rows in the tallest tiles first and the rest in the
-// tile that holds it at the least cost.  Measured per tile with every CU busy
-// (DeepSDF decoder): bf16 128 / 64 / 32 rows 86 / 52 / 41 us (below 64 rows the
-// weights' way into the CU is the bound), split 64 / 32 rows 128 / 88 us,
-// float32 64 / 32 / 16 rows 372 / 200 / 107 us (bound by the matrix cores
-// throughout).
-template <int P> constexpr int kGranule = P == kPrecF32 ? 16 : 32;
-
-template <int P>
-__device__ __forceinline__ int next_tile(int left) {
-  if constexpr (P == kPrecBF16) return left > 64 ? 128 : (left > 32 ? 64 : 32);
-  else if constexpr (P == kPrecF32) return left > 48 ? 64 : (left > 16 ? 32 : 16);
-  else return left > 32 ? 64 : 32;
-}
-
-// Rows [first, last) of `count` that this workgroup owns.  The rows are dealt
-// out in runs of the smallest tile, so that every workgroup has the same
-// number to one run; where the share leaves a rest that takes a full tile
-// anyway, in full tiles, so that some workgroups have none of the last round
-// and leave the others their bandwidth (bf16, 20,011 points: 79 us against
-// 83 us with 79 rows to every CU).
-template <int P>
-__device__ __forceinline__ void row_share(long long count, long long& first, long long& last) {
-  constexpr int M = Cfg<P>::M;
-  const long long G = gridDim.x, runs = (count + kGranule<P> - 1) / kGranule<P>;
-  const int rest = (int)((runs + G - 1) / G * kGranule<P> % M);
-  const int g = rest && next_tile<P>(rest) == M ? M : kGranule<P>;
-  const long long t = (count + g - 1) / g;
-  first = t * blockIdx.x / G * g;
-  last = min(count, t * (blockIdx.x + 1) / G * g);
-}
-
 template <int P, int M>
 __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, long long base, int k) {
   const int tid = threadIdx.x;
@@ -2092,7 +2272,8 @@ void launch_dw(int precision, const DwArgs& a, hipStream_t st) {
 
 template <int P>
 static hipError_t setup_p(int bytes) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_march<P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  hipError_t e = hipFuncSetAttribute((const void*)k_march_run<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     bytes + (int)march_row_bytes() * Cfg<P>::M);
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)k_eval<P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
@@ -2116,15 +2297,17 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
   if (precision == 1) {
     hipError_t e = hipFuncSetAttribute((const void*)k_dw_bf16, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
     if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void*)k_march, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
     return setup_p<1>(bytes);
   }
   if (precision == 2) return setup_p<2>(bytes);
   return setup_p<0>(bytes);
 }
 
-#define DIST_DISPATCH(KERNEL, ARGS)                                                                    \
+#define DIST_DISPATCH(KERNEL, ARGS, MORE)                                                              \
   do {                                                                                                 \
-    const size_t sm = mlp_smem_bytes(precision, ARGS.net);                                             \
+    const size_t sm = mlp_smem_bytes(precision, ARGS.net) + (MORE);                                    \
     const dim3 blk(fwd_threads(precision));                                                            \
     if (precision == 1) hipLaunchKernelGGL(KERNEL<1>, dim3(grid), blk, sm, st, ARGS);                  \
     else if (precision == 2) hipLaunchKernelGGL(KERNEL<2>, dim3(grid), blk, sm, st, ARGS);             \
@@ -2140,8 +2323,12 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
     else if (precision == 0) hipLaunchKernelGGL(KERNEL<0>, dim3(grid), blk, sm, st, ARGS);             \
   } while (0)
 
-void launch_march(int precision, const MarchArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_march, a); }
-void launch_march_ring(int precision, const MarchArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_march_ring, a); }
+void launch_march(const MarchArgs& a, int grid, hipStream_t st) {
+  hipLaunchKernelGGL(k_march, dim3(grid), dim3(fwd_threads(kPrecBF16)), mlp_smem_bytes(kPrecBF16, a.net), st, a);
+}
+void launch_march_run(int precision, const MarchArgs& a, int grid, hipStream_t st) {
+  DIST_DISPATCH(k_march_run, a, march_row_bytes() * rows_for(precision));
+}
 void launch_color(int precision, const ColorArgs& a, int grid, hipStream_t st) {
   const size_t sm = mlp_smem_bytes(precision, a.net);
   if (precision == 1) hipLaunchKernelGGL(k_color<1>, dim3(grid), dim3(kFwdWaves<1> * 64), sm, st, a);
@@ -2152,7 +2339,7 @@ void launch_color_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t
   if (precision == 2) hipLaunchKernelGGL(k_color_adjoint<2>, dim3(grid), dim3(kBwdWaves * 64), sm, st, a);
   else if (precision == 0) hipLaunchKernelGGL(k_color_adjoint<0>, dim3(grid), dim3(kBwdWaves * 64), sm, st, a);
 }
-void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_eval, a); }
+void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_eval, a, 0); }
 void launch_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t st) { DIST_DISPATCH_BWD(k_adjoint, a); }
 static_assert(kAdjWaves * 64 == 512, "the recompute-and-VJP dispatch assumes 8 waves");
 int mlp_row_groups(int waves, int width) { return (waves == 8 && width <= 128) ? 2 : 1; }

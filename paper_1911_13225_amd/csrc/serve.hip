@@ -196,7 +196,7 @@ static int capture_tick(Server* s, int par) {
   ma.count = s->counters + nxt;
   ma.qcount = s->qcount;          // queries counted where they are made
   ma.ecount = s->ecount;          // and non-finite ones
-  launch_march(kPrecBF16, ma, ctx->n_cu, s->st);
+  launch_march(ma, ctx->n_cu, s->st);
   hipGraph_t g = nullptr;
   HIPCHK_S(hipStreamEndCapture(s->st, &g));
   HIPCHK_S(hipGraphInstantiate(&s->exec[par], g, nullptr, nullptr, 0));

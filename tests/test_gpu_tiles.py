@@ -69,3 +69,34 @@ def test_codes_fold_one_by_one(name, n_lat):
         one = api.dist_sdf_eval(ctx, Pt[i:i + 1].contiguous(), torch.zeros(1, device="cuda", dtype=torch.int32),
                                 Zt[i:i + 1].contiguous(), 0)
         assert torch.equal(one, f[i:i + 1]), i
+
+
+# Rays per CU from under one to over the tallest tile, so that the march fills
+# its tiles to every height; K records, and a step limit that ends rays.
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["fp32", "bf16", "split"])
+@pytest.mark.parametrize("levels,k,steps", [(0, 1, 9), (1, 4, 50), (2, 3, 50)])
+def test_march_does_not_depend_on_the_tile(prec, levels, k, steps):
+    """An image's rays march the same alone, with few, and with many others."""
+    from paper_1911_13225_amd import api
+    spec = MIXED_SPEC
+    ctx, _ = ctx_for("mixed")
+    prm = di.TraceParams(max_steps=steps, c2f_levels=levels, k_samples=k, precision=prec, want_normals=0,
+                         keep_history=1)
+    z = torch.tensor(di.make_latents(1, spec.latent_dim, sigma=0.05), device="cuda")
+    cams = di.random_sphere_cameras(48, 28, 36)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    gd, gs = (torch.randn(1, 28, 36, generator=g, device="cuda") for _ in range(2))
+    ref = None
+    for n in (1, 9, 48):
+        out = api.dist_render_fwd(ctx, cams[:n], z, prm, save=True)
+        one = {key: out[key][:1].clone() for key in ("depth", "dist", "sil", "status", "nsteps", "queries")}
+        gd_n, gs_n = torch.zeros_like(out["depth"]), torch.zeros_like(out["sil"])
+        gd_n[:1], gs_n[:1] = gd * torch.isfinite(one["depth"]), gs        # seeds on the first image alone
+        one["g_z"] = api.dist_render_bwd(ctx, out["saved"], gd_n, None, gs_n, n_latents=1)
+        one["g_unrolled"] = api.dist_render_bwd_unrolled(ctx, out["saved"], gd_n, gs_n, n_latents=1)
+        out["saved"].free()
+        assert int(out["queries"].sum()) > 0
+        if ref is None:
+            ref = one
+        for key in ref:
+            assert torch.equal(ref[key], one[key]), (n, key)
