@@ -1041,39 +1041,58 @@ __global__ void k_zero_f32(float* p, long long n) {
 // kernel captures h and Delta of every row of a chunk in the blocked
 // feature-major layout of the capture (64-row blocks, a block's features
 // contiguous; bfloat16 on the bf16 paths, float32 on the float32 path); each layer's
-// contraction over the chunk's rows runs on MFMA (one k_dw launch per layer
-// and chunk, every input segment and the bias in it).  The contraction is
-// long (all samples) and the output small (a layer's weights), so the rows of
-// a chunk are cut into slices of kThetaSlice that run in parallel; slice s of
-// every chunk adds to its own partial, and one launch per layer sums the
-// partials in slice order into g_W / g_b: the sum order is fixed, so the
-// result is reproducible bit for bit.  The capture and partial buffers belong
-// to the context and are reused; the one host synchronisation reads the
-// sample count that sizes the chunk loop.
+// contraction over the chunk's rows runs on MFMA (one k_dw launch per chunk
+// for all layers, with every input segment and the bias).  The contraction is
+// long (all samples) and the output small (the weights), so the rows of a
+// chunk are cut into slices that run in parallel; slice s of every chunk adds
+// to its own partial, and one launch sums the partials in slice order into
+// g_W / g_b: the sum order is fixed, so the result is reproducible bit for
+// bit.  The capture and partial buffers belong to the context and are reused;
+// the one host synchronisation reads the sample count that sizes the chunk
+// loop.
 static constexpr int kThetaChunkRows = 65536;
-static constexpr int kThetaSlice = 2048;
-static constexpr int kThetaSlices = kThetaChunkRows / kThetaSlice;
-static_assert(kThetaSlice % kDwRows == 0, "slices are whole LDS blocks of the contraction");
+// Slices: 8 (one per XCD) fill the chip on the bf16 path.  On the float32 path
+// a slice keeps to some 2,048 rows, so that its float32 sums stay as short as
+// their rounding error wants.
+static int theta_max_slices(int prec) { return prec == kPrecF32 ? kThetaChunkRows / 2048 : 8; }
+static int theta_slices(int prec, int blocks) {
+  const int by_rows = (blocks * kCapBlock + 2047) / 2048;
+  return std::min(std::min(std::max((by_rows + 7) / 8 * 8, 8), theta_max_slices(prec)), blocks);
+}
 
-// g_W[n][k] = sum over slices s (in order) of P[s][n][k] for k < k_in, and
-// g_b[n] the same sum of column k_in.
-__global__ void k_slice_sum(const float* __restrict__ P, int S, int n_out, int k_in, float* __restrict__ gW,
-                            float* __restrict__ gb) {
-  const int ldp = k_in + 1;
-  const long long total = (long long)n_out * ldp;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-    float acc = 0.f;
-    for (int sl = 0; sl < S; ++sl) acc += P[sl * total + i];
-    const long long n = i / ldp, k = i - n * ldp;
-    if (k < k_in) gW[n * k_in + k] = acc;
-    else gb[n] = acc;
+// Per layer (blockIdx.y): g_W[n][k] = sum over slices s (in order) of
+// P[s][n][k] for k < k_in, and g_b[n] the same sum of column k_in.
+struct SliceSum {
+  const float* P[kMaxLayers];
+  float *gW[kMaxLayers], *gb[kMaxLayers];
+  int n_out[kMaxLayers], k_in[kMaxLayers];
+  int S;
+};
+__global__ void k_slice_sum(SliceSum a) {
+  const int l = blockIdx.y, k_in = a.k_in[l], ldp = k_in + 1, S = a.S;
+  const float* __restrict__ P = a.P[l];
+  const int total = a.n_out[l] * ldp;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    double acc = 0.0;                     // free here: the loop waits for its reads
+    int sl = 0;
+    for (; sl + 8 <= S; sl += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = P[(size_t)(sl + u) * total + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; sl < S; ++sl) acc += P[(size_t)sl * total + i];
+    const int n = i / ldp, k = i - n * ldp;
+    if (k < k_in) a.gW[l][(size_t)n * k_in + k] = (float)acc;
+    else a.gb[l][n] = (float)acc;
   }
 }
 
-static size_t theta_partials(const dist_ctx* ctx) {
+static size_t theta_partials(const dist_ctx* ctx, int prec) {
   size_t f = 0;
   for (int l = 0; l < ctx->nl; ++l) f += (size_t)ctx->out_dims[l] * (ctx->in_dims[l] + 1);
-  return f * kThetaSlices;
+  return f * theta_max_slices(prec);
 }
 
 static int theta_space(dist_ctx* ctx, int prec, int rows) {
@@ -1090,7 +1109,7 @@ static int theta_space(dist_ctx* ctx, int prec, int rows) {
   auto up = [&](size_t x) { return (x + al - 1) / al * al; };
   const size_t hb = up(rows * nfeat * es), gb = up(rows * es), zb = up((size_t)rows * ctx->L * es),
                pb = up((size_t)rows * 4 * es);
-  const size_t sb = up(theta_partials(ctx) * 4);
+  const size_t sb = up(theta_partials(ctx, prec) * 4);
   ThetaSpace* n = new ThetaSpace();
   n->bytes = 2 * hb + 2 * gb + zb + pb + sb;
   int rc = ctx_alloc(ctx, &n->mem, n->bytes);
@@ -1131,13 +1150,8 @@ static int run_theta(dist_ctx* ctx, Workspace* w, BwdSpace* b, int prec, const f
     return DIST_OK;
   }
   const int chunk = std::max(1, std::min(tiles, kThetaChunkRows / tile));
-  // contraction rows per chunk: whole slices (rows past the chunk's samples are zero)
-  auto gemm_rows_of = [](int valid) {
-    return valid >= kThetaSlice ? (valid + kThetaSlice - 1) / kThetaSlice * kThetaSlice : valid;
-  };
-  const int R = gemm_rows_of(chunk * tile);
-  if (R % kCapBlock != 0 || tile != kCapBlock || (prec != kPrecF32 && R % kDwRows != 0))
-    return dist_set_error(DIST_EINVAL, "weight-gradient chunk of %d rows is not whole blocks", R);
+  const int R = chunk * tile;
+  if (tile != kCapBlock) return dist_set_error(DIST_EINVAL, "a recompute tile of %d rows is not a capture block", tile);
   int rc = theta_space(ctx, prec, R);
   if (rc) return rc;
   ThetaSpace* t = ctx->theta;
@@ -1159,19 +1173,19 @@ static int run_theta(dist_ctx* ctx, Workspace* w, BwdSpace* b, int prec, const f
   aa.cap_rows = R;
   const int L = ctx->L, nl = ctx->nl;
   // per layer: its partials and the input segments of its contraction
-  std::vector<DwArgs> da(nl);
+  DwBatch dw{};
+  dw.n = nl;
   {
     size_t off = 0;
     for (int l = 0; l < nl; ++l) {
-      DwArgs& d = da[l];
+      DwArgs& d = dw.layer[l];
       d.D = l < nl - 1 ? at(t->dbuf, (size_t)l * kmax * R) : (const void*)t->gmbuf;
       d.FD = l < nl - 1 ? kmax : 1;
-      d.R = R;
       d.n_out = ctx->out_dims[l];
       d.k_in = ctx->in_dims[l];
       d.ldp = d.k_in + 1;
       d.P = t->slices + off;
-      off += (size_t)kThetaSlices * d.n_out * d.ldp;
+      off += (size_t)theta_max_slices(prec) * d.n_out * d.ldp;
       int e = 0;
       // a segment: its base, the features it contributes and its features per capture block
       auto seg = [&](const void* p, int n, int F) {
@@ -1193,13 +1207,9 @@ static int run_theta(dist_ctx* ctx, Workspace* w, BwdSpace* b, int prec, const f
       d.bias = prec == kPrecF32 ? 0 : 1;
     }
   }
-  int S0 = 0;
+  dw.S = theta_slices(prec, chunk);
   for (int t0 = 0; t0 < tiles; t0 += chunk) {
     const int t1 = std::min(tiles, t0 + chunk);
-    const int valid = (t1 - t0) * tile;
-    const int rows = gemm_rows_of(valid);
-    const int S = rows >= kThetaSlice ? rows / kThetaSlice : 1;
-    if (t0 == 0) S0 = S;
     aa.tile_begin = t0;
     aa.tile_end = t1;
     {
@@ -1207,22 +1217,26 @@ static int run_theta(dist_ctx* ctx, Workspace* w, BwdSpace* b, int prec, const f
       TimedLaunch tl(ctx, 2, st, t0 == 0 ? b->n_samples : nullptr, 1);
       launch_adjoint(prec, aa, std::max(1, std::min(t1 - t0, ctx->n_cu)), st);
     }
-    launch_theta_rows(prec, b->samples + (size_t)t0 * tile, b->sample_lat + (size_t)t0 * tile, z, L, valid, R,
-                      t->zrows, t->prows, t->ones, t->hbuf, t->dbuf, t->gmbuf, nl - 1, kmax, st);
-    for (int l = 0; l < nl; ++l) {
-      DwArgs d = da[l];
-      d.S = S;
-      d.K = rows / S;
-      d.acc = t0 > 0;
-      TimedLaunch tl(ctx, 4, st);
-      launch_dw(prec, d, st);
-    }
+    launch_theta_rows(prec, b->samples + (size_t)t0 * tile, b->sample_lat + (size_t)t0 * tile, z, L, (t1 - t0) * tile,
+                      t->zrows, t->prows, t->ones, st);
+    dw.blocks = t1 - t0;
+    dw.acc = t0 > 0;
+    TimedLaunch tl(ctx, 4, st);
+    launch_dw(prec, dw, st);
   }
+  SliceSum ss{};
+  ss.S = dw.S;
+  int widest = 0;
   for (int l = 0; l < nl; ++l) {
-    const long long total = (long long)da[l].n_out * da[l].ldp;
-    hipLaunchKernelGGL(k_slice_sum, dim3((int)std::min<long long>((total + 255) / 256, 4096)), dim3(256), 0, st,
-                       da[l].P, S0, da[l].n_out, da[l].k_in, g_W[l], g_b[l]);
+    const DwArgs& d = dw.layer[l];
+    ss.P[l] = d.P;
+    ss.gW[l] = g_W[l];
+    ss.gb[l] = g_b[l];
+    ss.n_out[l] = d.n_out;
+    ss.k_in[l] = d.k_in;
+    widest = std::max(widest, d.n_out * d.ldp);
   }
+  hipLaunchKernelGGL(k_slice_sum, dim3((widest + 255) / 256, nl), dim3(256), 0, st, ss);
   HIPCHK(hipGetLastError());
   return rc;
 }

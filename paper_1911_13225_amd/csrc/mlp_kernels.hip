@@ -1980,65 +1980,58 @@ size_t adj_mask_words(int precision, const NetDev& net) {
 
 // Per captured row, in the blocked layout of the capture (features of a
 // kCapBlock-row block contiguous): z of its latent, its point (and a 0) and a
-// 1, in the capture type; for the rows in [valid, R) that only pad the
-// contraction to whole slices, zeros there and in the captured h, Delta and
-// row factor (whole blocks: valid is a multiple of kCapBlock).
+// 1, in the capture type.
 template <class T>
 __global__ void k_theta_rows(const float4* __restrict__ pts, const int* __restrict__ lat, const float* __restrict__ z,
-                             int L, int valid, int R, T* zrows, T* prows, T* ones, T* hbuf, T* dbuf, T* gmbuf,
-                             int n_layers, int kmax) {
+                             int L, int R, T* zrows, T* prows, T* ones) {
   const long long step = (long long)gridDim.x * blockDim.x, t0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   constexpr int B = kCapBlock;
   for (long long i = t0; i < (long long)L * R; i += step) {
     // i walks the blocked layout: block b, feature j, row r % B
     const long long b = i / ((long long)L * B);
     const int j = (int)(i / B % L), r = (int)(b * B + i % B);
-    zrows[i] = (T)(r < valid ? z[(size_t)lat[r] * L + j] : 0.f);
+    zrows[i] = (T)z[(size_t)lat[r] * L + j];
   }
   for (long long r = t0; r < R; r += step) {
-    const bool ok = r < valid;
-    const float4 p = ok ? pts[r] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 p = pts[r];
     T* pr = prows + (r / B) * 4 * B + r % B;
     pr[0] = (T)p.x;
     pr[B] = (T)p.y;
     pr[2 * B] = (T)p.z;
     pr[3 * B] = (T)0.f;
-    ones[r] = (T)(ok ? 1.f : 0.f);
-    if (!ok) gmbuf[r] = (T)0.f;
-  }
-  // padding blocks of every layer: one contiguous range per layer
-  const long long per = (long long)(R - valid) * kmax;
-  for (long long i = t0; i < (long long)n_layers * per; i += step) {
-    const long long l = i / per, o = l * kmax * R + (long long)valid * kmax + (i - l * per);
-    hbuf[o] = (T)0.f;
-    dbuf[o] = (T)0.f;
+    ones[r] = (T)1.f;
   }
 }
 
-void launch_theta_rows(int precision, const float4* pts, const int* lat, const float* z, int L, int valid, int R,
-                       void* zrows, void* prows, void* ones, float* hbuf, float* dbuf, float* gmbuf, int n_layers,
-                       int kmax, hipStream_t st) {
+void launch_theta_rows(int precision, const float4* pts, const int* lat, const float* z, int L, int R, void* zrows,
+                       void* prows, void* ones, hipStream_t st) {
   const long long total = (long long)std::max(L, 1) * R;
   const int grid = (int)std::min<long long>((total + 255) / 256, 4096);
   if (precision == 0)
-    hipLaunchKernelGGL(k_theta_rows<float>, dim3(grid), dim3(256), 0, st, pts, lat, z, L, valid, R, (float*)zrows,
-                       (float*)prows, (float*)ones, hbuf, dbuf, gmbuf, n_layers, kmax);
+    hipLaunchKernelGGL(k_theta_rows<float>, dim3(grid), dim3(256), 0, st, pts, lat, z, L, R, (float*)zrows,
+                       (float*)prows, (float*)ones);
   else
-    hipLaunchKernelGGL(k_theta_rows<bf16>, dim3(grid), dim3(256), 0, st, pts, lat, z, L, valid, R, (bf16*)zrows,
-                       (bf16*)prows, (bf16*)ones, (bf16*)hbuf, (bf16*)dbuf, (bf16*)gmbuf, n_layers, kmax);
+    hipLaunchKernelGGL(k_theta_rows<bf16>, dim3(grid), dim3(256), 0, st, pts, lat, z, L, R, (bf16*)zrows, (bf16*)prows,
+                       (bf16*)ones);
 }
 
 // Weight-gradient contraction over the captured rows (Sec. 3.4: dW_l = sum
-// over samples of Delta_l x_l^T, db_l = sum of Delta_l): for each slice sl of
-// K rows, P[sl][n][k] = sum over the slice's rows r of D[n][r] X[k][r], with
-// D and X in the capture's blocked layout (64-row blocks, a block's features
-// contiguous, each segment with its own features per block).  The input features X of a layer
-// are up to four segments in input order (h, z, p, and on the float32 path a
-// ones row that yields the bias column).  With acc set the slice adds to the
-// partial it holds from the previous chunk; every slice is owned by one
-// workgroup per launch, so the sum order is fixed.  Slices are mapped to
-// workgroups so that all tiles of one slice run on one XCD (workgroups are
-// dealt to the 8 XCDs round robin) and share its L2 for the slice's rows.
+// over samples of Delta_l x_l^T, db_l = sum of Delta_l): for each layer and
+// each slice sl of the rows, P[sl][n][k] = sum over the slice's rows r of
+// D[n][r] X[k][r], with D and X in the capture's blocked layout (64-row blocks,
+// a block's features contiguous, each segment with its own features per
+// block).  The input features X of a layer are up to four segments in input
+// order (h, z, p, and on the float32 path a ones row that yields the bias
+// column).  With acc set the slice adds to the partial it holds from the
+// previous chunk; every slice is owned by one workgroup per launch, so the sum
+// order is fixed.  Slices are mapped to workgroups so that all tiles of one
+// slice run on one XCD (workgroups are dealt to the 8 XCDs round robin) and
+// share its L2 for the slice's rows.
+//   All layers go in one launch: their 120 tiles (DeepSDF) fill the chip with
+// 8 slices of any length, where one launch per layer needed slices of 2,048
+// rows.  A partial holds every weight in float32, so fewer slices also mean
+// fewer partials to write and to add up (7.3 MB each).  60,007 samples, bf16:
+// contraction 533 -> 355 us (620 TFLOP/s), adding up the partials 138 -> 14 us.
 // input feature k: its rows of block 0 and the block stride (elements)
 __device__ __forceinline__ const char* dw_feature(const DwX& x, int k, int es, int& bstride) {
   const void* b = x.p[0];
@@ -2050,10 +2043,10 @@ __device__ __forceinline__ const char* dw_feature(const DwX& x, int k, int es, i
   return (const char*)b + (size_t)(k - base) * kCapBlock * es;
 }
 
-// workgroup -> (tile of the output, slice), all tiles of a slice on one XCD
-__device__ __forceinline__ void dw_block(int T, int S, int& tile, int& slice) {
-  const int id = blockIdx.x;
-  if (S % 8 == 0) {
+// workgroup -> (layer, tile of its output, slice), all tiles of a slice on one XCD
+__device__ __forceinline__ const DwArgs& dw_block(const DwBatch& b, int& tile, int& slice) {
+  const int id = blockIdx.x, T = b.tiles[b.n];
+  if (b.S % 8 == 0) {
     const int x = id & 7, y = id >> 3;
     slice = (y / T) * 8 + x;
     tile = y % T;
@@ -2061,11 +2054,18 @@ __device__ __forceinline__ void dw_block(int T, int S, int& tile, int& slice) {
     slice = id / T;
     tile = id % T;
   }
+  int l = 0;
+  while (l + 1 < b.n && tile >= b.tiles[l + 1]) ++l;
+  tile -= b.tiles[l];
+  return b.layer[l];
 }
 
-__device__ __forceinline__ void dw_put(const DwArgs& a, float* P, int n, int k, float v) {
+// first 64-row block of a slice: the chunk's blocks dealt out evenly
+__device__ __forceinline__ long long dw_first(const DwBatch& b, int slice) { return (long long)b.blocks * slice / b.S; }
+
+__device__ __forceinline__ void dw_put(const DwArgs& a, bool acc, float* P, int n, int k, float v) {
   float* d = P + (size_t)n * a.ldp + k;
-  *d = a.acc ? *d + v : v;
+  *d = acc ? *d + v : v;
 }
 
 // bf16: a workgroup of 4 waves owns a 128 (n) x 128 (k) block.  Blocks of
@@ -2078,20 +2078,21 @@ __device__ __forceinline__ void dw_put(const DwArgs& a, float* P, int n, int k, 
 // column also sum the staged Delta rows: the bias column (k_in) of the
 // partial.  Features past n_out or kcols are clamped to the last one and
 // their outputs dropped.
-__global__ __launch_bounds__(256, 2) void k_dw_bf16(DwArgs a) {
+__global__ __launch_bounds__(256, 2) void k_dw_bf16(DwBatch batch) {
   bf16* lds = (bf16*)dyn_smem;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, ln = lane & 31, g = lane >> 5;
-  const int Tn = (a.n_out + 127) / 128, Tk = (a.kcols + 127) / 128;
   int tile, slice;
-  dw_block(Tn * Tk, a.S, tile, slice);
+  const DwArgs& a = dw_block(batch, tile, slice);
+  const int Tn = (a.n_out + 127) / 128;
   const int n0 = (tile % Tn) * 128, k0 = (tile / Tn) * 128;
-  const size_t r0 = (size_t)slice * a.K;
+  const size_t b0 = dw_first(batch, slice);                        // the slice's blocks of 64 rows
+  const int nblk = (int)(dw_first(batch, slice + 1) - b0);
+  if (nblk == 0) return;                                           // a later chunk of fewer blocks than slices
   const int rc = t & 7, fl = t >> 3;
   const bf16* ga[4];
   const bf16* gx[4];
   int sx[4];                              // block strides of the input features (segments differ)
   const int sa = a.FD * kCapBlock;
-  const size_t b0 = r0 / kCapBlock;       // the slice's first block
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int n = min(n0 + fl + 32 * i, a.n_out - 1), k = min(k0 + fl + 32 * i, a.kcols - 1);
@@ -2134,7 +2135,6 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwArgs a) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
   const int wn = wave & 1, wk = wave >> 1;
-  const int nblk = a.K / kDwRows;
   auto mma = [&](int buf) {
     const bf16* A = lds + (size_t)buf * 2 * 128 * kDwLd;
     const bf16* X = A + 128 * kDwLd;
@@ -2189,7 +2189,7 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = n0 + 64 * wn + 32 * i + 8 * q + 4 * g + e, k = k0 + 64 * wk + 32 * j + ln;
-          if (n < a.n_out && k < a.kcols) dw_put(a, P, n, k, acc[i][j][4 * q + e]);
+          if (n < a.n_out && k < a.kcols) dw_put(a, batch.acc, P, n, k, acc[i][j][4 * q + e]);
         }
   if (bias) {
 #pragma unroll
@@ -2199,7 +2199,7 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwArgs a) {
       x += __shfl_xor(x, 2);
       x += __shfl_xor(x, 4);
       const int n = n0 + fl + 32 * i;
-      if (rc == 0 && n < a.n_out) dw_put(a, P, n, a.k_in, x);
+      if (rc == 0 && n < a.n_out) dw_put(a, batch.acc, P, n, a.k_in, x);
     }
   }
 }
@@ -2207,20 +2207,20 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwArgs a) {
 // float32: the operands are read straight from memory (float4 of 4 rows per
 // lane), a workgroup of 4 waves owns 128 x 128 and a wave 64 x 64 as 2 x 2
 // 32x32x2 tiles, the rows paired (i, i + 4) (any pairing of the contraction
-// index gives the same sum); the bias comes from the ones segment.
-__global__ __launch_bounds__(256) void k_dw_f32(DwArgs a) {
+// index gives the same sum); the bias comes from the ones segment.  The sums
+// run over kDwRun rows at a time and those are added up, so that no float32
+// sum is long whatever the slice's length.
+constexpr int kDwRun = 256;
+__global__ __launch_bounds__(256) void k_dw_f32(DwBatch batch) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int ln = lane & 31, g = lane >> 5;
-  const int Tn = (a.n_out + 127) / 128, Tk = (a.kcols + 127) / 128;
   int tile, slice;
-  dw_block(Tn * Tk, a.S, tile, slice);
+  const DwArgs& a = dw_block(batch, tile, slice);
+  const int Tn = (a.n_out + 127) / 128;
   const int nb = (tile % Tn) * 128 + (wave & 1) * 64, kb = (tile / Tn) * 128 + (wave >> 1) * 64;
-  const size_t r0 = (size_t)slice * a.K;
+  const size_t r0 = (size_t)dw_first(batch, slice) * kCapBlock, r1 = (size_t)dw_first(batch, slice + 1) * kCapBlock;
+  if (r0 == r1) return;
   f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
   const float* pa[2];
   const float* pb[2];
   int sb[2];
@@ -2230,25 +2230,41 @@ __global__ __launch_bounds__(256) void k_dw_f32(DwArgs a) {
     pa[i] = (const float*)a.D + (size_t)min(nb + 32 * i + ln, a.n_out - 1) * kCapBlock + 4 * g;
     pb[i] = (const float*)dw_feature(a.x, min(kb + 32 * i + ln, a.kcols - 1), 4, sb[i]) + 4 * g;
   }
-  for (int r = 0; r < a.K; r += 8) {
-    const size_t blk = (r0 + r) / kCapBlock, w = (r0 + r) % kCapBlock;
-    float4 av[2], bv[2];
+  f32x16 tot[2][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      av[i] = *(const float4*)(pa[i] + blk * sa + w);
-      bv[i] = *(const float4*)(pb[i] + blk * sb[i] + w);
-    }
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) tot[i][j] = f32x16{};
+  for (size_t q0 = r0; q0 < r1; q0 += kDwRun) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].x, bv[j].x, acc[i][j], 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].y, bv[j].y, acc[i][j], 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].z, bv[j].z, acc[i][j], 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].w, bv[j].w, acc[i][j], 0, 0, 0);
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+    const size_t q1 = min(q0 + kDwRun, r1);
+    for (size_t r = q0; r < q1; r += 8) {
+      const size_t blk = r / kCapBlock, w = r % kCapBlock;
+      float4 av[2], bv[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        av[i] = *(const float4*)(pa[i] + blk * sa + w);
+        bv[i] = *(const float4*)(pb[i] + blk * sb[i] + w);
       }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].x, bv[j].x, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].y, bv[j].y, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].z, bv[j].z, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].w, bv[j].w, acc[i][j], 0, 0, 0);
+        }
+    }
+    mfma_drain();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) tot[i][j] += acc[i][j];
   }
-  mfma_drain();
   float* P = a.P + (size_t)slice * a.n_out * a.ldp;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -2259,15 +2275,17 @@ __global__ __launch_bounds__(256) void k_dw_f32(DwArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = nb + 32 * i + 8 * q + 4 * g + e, k = kb + 32 * j + ln;
-          if (n < a.n_out && k < a.kcols) dw_put(a, P, n, k, acc[i][j][4 * q + e]);
+          if (n < a.n_out && k < a.kcols) dw_put(a, batch.acc, P, n, k, tot[i][j][4 * q + e]);
         }
 }
 
-void launch_dw(int precision, const DwArgs& a, hipStream_t st) {
-  const int T = ((a.n_out + 127) / 128) * ((a.kcols + 127) / 128);
-  const dim3 grid(T * a.S);
-  if (precision == 0) hipLaunchKernelGGL(k_dw_f32, grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(k_dw_bf16, grid, dim3(256), kDwLds, st, a);
+void launch_dw(int precision, DwBatch& b, hipStream_t st) {
+  b.tiles[0] = 0;
+  for (int l = 0; l < b.n; ++l)
+    b.tiles[l + 1] = b.tiles[l] + ((b.layer[l].n_out + 127) / 128) * ((b.layer[l].kcols + 127) / 128);
+  const dim3 grid(b.tiles[b.n] * b.S);
+  if (precision == 0) hipLaunchKernelGGL(k_dw_f32, grid, dim3(256), 0, st, b);
+  else hipLaunchKernelGGL(k_dw_bf16, grid, dim3(256), kDwLds, st, b);
 }
 
 template <int P>

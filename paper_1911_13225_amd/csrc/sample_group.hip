@@ -17,14 +17,31 @@ __global__ void k_group_zero(int* p, int n) {
 }
 
 // keys = latent ids clamped to [0, n_lat) (as the plain decoder query does),
-// values = sample indices; counts per latent (integer atomics: exact)
-__global__ void k_group_keys(const int32_t* __restrict__ lat, int n_lat, int n, int* __restrict__ keys,
-                             int* __restrict__ vals, int* __restrict__ cnt) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+// values = sample indices; counts per latent (integer atomics: exact).  Up to
+// kLdsLat latents are counted per workgroup in LDS and added once: with one
+// global atomic per sample, 60,007 samples of 5 latents queued on 5 addresses
+// for 286 us (now 6 us).  More latents than that seldom meet on one address.
+constexpr int kLdsLat = 4096;
+__global__ __launch_bounds__(256) void k_group_keys(const int32_t* __restrict__ lat, int n_lat, int n,
+                                                    int* __restrict__ keys, int* __restrict__ vals,
+                                                    int* __restrict__ cnt) {
+  __shared__ int h[kLdsLat];
+  const bool lds = n_lat <= kLdsLat;
+  if (lds) {
+    for (int l = threadIdx.x; l < n_lat; l += 256) h[l] = 0;
+    __syncthreads();
+  }
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
     const int l = min(max((int)lat[i], 0), n_lat - 1);
     keys[i] = l;
     vals[i] = i;
-    atomicAdd(&cnt[l], 1);
+    if (lds) atomicAdd(&h[l], 1);
+    else atomicAdd(&cnt[l], 1);
+  }
+  if (lds) {
+    __syncthreads();
+    for (int l = threadIdx.x; l < n_lat; l += 256)
+      if (h[l]) atomicAdd(&cnt[l], h[l]);
   }
 }
 

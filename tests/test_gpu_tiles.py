@@ -100,3 +100,34 @@ def test_march_does_not_depend_on_the_tile(prec, levels, k, steps):
             ref = one
         for key in ref:
             assert torch.equal(ref[key], one[key]), (n, key)
+
+
+# The weight gradient's rows run in chunks of 65,536 and each chunk's 64-row
+# blocks in up to 8 (bf16) or 32 (float32) slices: fewer blocks than slices, in
+# the only chunk and in the last one.
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("before,n", [(0, 1), (0, 64 * 3), (0, 64 * 41 + 5), (65536, 1), (65536, 64 * 5 + 3)])
+def test_weight_gradient_slices(prec, before, n):
+    """n samples behind `before` samples with zero seeds have the gradient of
+    the n samples alone (in small groups, where every sum is short)."""
+    from paper_1911_13225_amd import api
+    ctx, _ = ctx_for("c1")
+    rng = np.random.Generator(np.random.PCG64(11))
+    P = torch.tensor(rng.uniform(-0.6, 0.6, (before + n, 3)).astype(np.float32), device="cuda")
+    sd = torch.tensor(rng.standard_normal(before + n).astype(np.float32), device="cuda")
+    sd[:before] = 0.0
+    Z = torch.tensor(di.make_latents(1, 64, sigma=0.1), device="cuda")
+    ids = torch.zeros(before + n, dtype=torch.int32, device="cuda")
+    _, gW, gb = api.dist_sdf_vjp(ctx, P, ids, sd, Z, prec, want_theta=True)
+    ref = None
+    for i in range(before, before + n, 64):
+        k = slice(i, min(i + 64, before + n))
+        _, w, b = api.dist_sdf_vjp(ctx, P[k].contiguous(), ids[k].contiguous(), sd[k].contiguous(), Z, prec,
+                                   want_theta=True)
+        part = [x.double() for x in w + b]
+        ref = part if ref is None else [x + y for x, y in zip(ref, part)]
+    # both add the same float32 products, the one in sums of up to 256 rows and
+    # their sums, the other in sums of 64: |difference| <= 256 ulp of the largest
+    # sum of magnitudes, itself at most sqrt(n) times the (random-sign) sum's size
+    for x, y in zip(gW + gb, ref):
+        assert (x.double() - y).norm() <= 256 * 2.0 ** -24 * max(1.0, n ** 0.5) * y.norm()
