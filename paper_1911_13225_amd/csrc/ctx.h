@@ -76,6 +76,16 @@ struct GroupSpace {
   void* temp = nullptr;
 };
 
+// Rows of a group of steps of the unrolled gradient: delta at layer 0 and the
+// skip layer, and the row factor.
+struct UlRows {
+  char* mem = nullptr;
+  size_t bytes = 0;
+  long long cap = 0;
+  float* delta = nullptr;
+  float* gm = nullptr;
+};
+
 struct UnrollSpace {
   char* mem = nullptr;
   size_t bytes = 0;
@@ -107,6 +117,7 @@ struct Workspace {
   NrmSave* ns = nullptr;
   CamSpace* cs = nullptr;
   UnrollSpace* us = nullptr;
+  UlRows* ur = nullptr;
   // pinned staging of the per-call descriptors
   dist::ImgDesc* h_imgs = nullptr;
   int* h_ints = nullptr;

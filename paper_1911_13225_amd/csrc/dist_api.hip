@@ -531,6 +531,10 @@ static void ws_destroy(dist_ctx* ctx, Workspace* w) {
     ctx_free(ctx, w->gs->mem, w->gs->bytes);
     delete w->gs;
   }
+  if (w->ur) {
+    ctx_free(ctx, w->ur->mem, w->ur->bytes);
+    delete w->ur;
+  }
   delete w;
 }
 
@@ -651,6 +655,26 @@ static int us_get(dist_ctx* ctx, Workspace* w, long long cap_lam, int steps) {
   u->t_hist = (float*)u->mem;
   u->lam = (float*)(u->mem + hb);
   w->us = u;
+  return DIST_OK;
+}
+
+// Rows of cap samples, dw delta floats each, of a group of unrolled steps.
+static int ur_get(dist_ctx* ctx, Workspace* w, long long cap, int dw) {
+  if (w->ur && w->ur->cap >= cap) return DIST_OK;
+  if (w->ur) {
+    ctx_free(ctx, w->ur->mem, w->ur->bytes);
+    delete w->ur;
+    w->ur = nullptr;
+  }
+  UlRows* u = new UlRows();
+  u->cap = cap;
+  const size_t db = (size_t)cap * dw * sizeof(float);
+  u->bytes = db + (size_t)cap * sizeof(float) + 256;
+  int rc = ctx_alloc(ctx, (void**)&u->mem, u->bytes);
+  if (rc != DIST_OK) { delete u; return rc; }
+  u->delta = (float*)u->mem;
+  u->gm = (float*)(u->mem + db);
+  w->ur = u;
   return DIST_OK;
 }
 
@@ -1416,6 +1440,12 @@ extern "C" int dist_render_bwd_camera(dist_ctx* ctx, const dist_saved* saved, co
   return DIST_OK;
 }
 
+// Samples a group of unrolled steps may hold (4 KB of delta rows each for the
+// DeepSDF decoder), and the fewest steps it is made for: from 512 K pixels on a
+// step fills the chip by itself (eight images of 256^2: 16.3 ms step by step).
+static constexpr long long kUlGroupSamples = 1 << 19;
+static constexpr int kUlMinSteps = 2;
+
 extern "C" int dist_render_bwd_unrolled(dist_ctx* ctx, const dist_saved* saved, const float* g_depth,
                                         const float* g_sil, float* g_z, void* stream) {
   if (!ctx || !saved || !g_z) return dist_set_error(DIST_EINVAL, "null argument");
@@ -1428,13 +1458,39 @@ extern "C" int dist_render_bwd_unrolled(dist_ctx* ctx, const dist_saved* saved, 
   const int n_img = saved->n_img, hw = saved->hw, n_lat = saved->n_lat;
   const int Lv = saved->prm.c2f_levels, steps = saved->prm.max_steps;
   // one sample per ray of the step's level at most, padded per latent
-  const long long cap = (long long)n_img * hw + (long long)n_lat * tile;
+  const long long rays = (long long)n_img * hw, pad = (long long)n_lat * tile;
+  long long cap = rays + pad;
   if (cap > (1LL << 31) - 1) return dist_set_error(DIST_EINVAL, "too many gradient samples");
   const int bpi = (hw + 255) / 256;
+  const int w0 = ctx->wpad[0];
+  const int ws = ctx->skip >= 0 ? ctx->wpad[ctx->skip] : 0;
+  // several steps at once, as many as the group's rows allow; without the
+  // memory for them (the context's budget), or for images so large that a step
+  // fills the chip by itself, step by step
+  int per = (int)std::min<long long>(kUlGroupSamples / rays, steps - 3 * Lv);
+  bool group = per >= kUlMinSteps;
+  const size_t mw = adj_mask_words(prec, ctx->net[prec]);
+  int rc = DIST_OK;
+  if (group) {
+    const long long gcap = per * rays + pad;
+    rc = bw_get(ctx, w, (int)gcap, n_img * bpi, n_lat, tile, mw * mlp_grid(ctx, gcap, prec));
+    if (!rc) rc = cs_get(ctx, w, gcap);
+    if (!rc) rc = ur_get(ctx, w, gcap, w0 + ws);
+    if (!rc) {
+      cap = gcap;
+    } else {
+      // give back what the group was to use and take what a step needs
+      group = false;
+      if (w->bw) { ctx_free(ctx, w->bw->mem, w->bw->bytes); delete w->bw; w->bw = nullptr; }
+      if (w->cs) { ctx_free(ctx, w->cs->mem, w->cs->bytes); delete w->cs; w->cs = nullptr; }
+    }
+  }
+  if (!group) {
+    rc = bw_get(ctx, w, (int)cap, n_img * bpi, n_lat, tile, mw * mlp_grid(ctx, cap, prec));
+    if (!rc) rc = cs_get(ctx, w, cap);
+    if (rc) return rc;
+  }
   const int grid = mlp_grid(ctx, cap, prec);
-  int rc = bw_get(ctx, w, (int)cap, n_img * bpi, n_lat, tile, adj_mask_words(prec, ctx->net[prec]) * grid);
-  if (!rc) rc = cs_get(ctx, w, cap);
-  if (rc) return rc;
   BwdSpace* b = w->bw;
   UnrollSpace* u = w->us;
   const int spi = slots_per_image(hw, Lv);
@@ -1450,25 +1506,49 @@ extern "C" int dist_render_bwd_unrolled(dist_ctx* ctx, const dist_saved* saved, 
   aa.mask_ws = b->mask_ws;
   aa.partial = b->partial;
   aa.gp_part = w->cs->gp;
-  const int w0 = ctx->wpad[0];
-  const int ws = ctx->skip >= 0 ? ctx->wpad[ctx->skip] : 0;
-  for (int n = steps - 1; n >= 0; --n) {
-    const int lv = std::max(Lv - n / 3, 0);
-    // the rays of level lv + ... have all been processed: after the split
-    // that follows step n, the children's adjoints flow to their parents
-    if (n % 3 == 2 && lv > 0) launch_ul_split(w->pool, w->imgs, w->img_order, n_img, hw >> (2 * lv), lv, u->lam, st);
-    UlIn in{n, lv, g_depth, g_sil, u->t_hist + (size_t)n * w->pool.cap, u->lam};
-    launch_ul_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, hw >> (2 * lv), n_lat, tile, in, b->bsum,
-                      b->boff, b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, b->sample_lat,
-                      w->cs->sample_cam, st);
-    {
-      TimedLaunch tl(ctx, 2, st, b->n_samples, 1);
-      launch_adjoint(prec, aa, grid, st);
+  if (group) {
+    aa.delta_out = w->ur->delta;
+    aa.gm_out = w->ur->gm;
+  }
+  auto reduce = [&](int mg0, int mgs) {
+    launch_gz_reduce(b->partial, ctx->kmax, tile, (int)(cap / tile) + 1, b->seg_base, b->seg_padded, n_lat, w0, mg0,
+                     ctx->w0z, ws, mgs, ctx->skip >= 0 ? ctx->wsz : nullptr, ctx->L, g_z, st, 0, 1);
+  };
+  auto steps_of = [&](int lv, int s0, int s1) {
+    return UlGroup{s0, s1, lv, g_depth, g_sil, u->t_hist, (size_t)w->pool.cap, u->lam};
+  };
+  // in reverse over the levels; after the split that follows a level's last
+  // step, the children's adjoints flow to their parents
+  for (int lv = 0; lv <= Lv; ++lv) {
+    const int first = 3 * (Lv - lv), last = lv == 0 ? steps - 1 : first + 2;     // the level's steps
+    const int nr = hw >> (2 * lv);
+    if (lv > 0) launch_ul_split(w->pool, w->imgs, w->img_order, n_img, nr, lv, u->lam, st);
+    for (int s1 = last; s1 >= first; s1 -= group ? per : 1) {
+      if (group) {
+        const UlGroup in = steps_of(lv, std::max(first, s1 - per + 1), s1);
+        launch_ulg_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, nr, n_lat, tile, in, b->bsum, b->boff,
+                           b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, b->sample_lat, st);
+      } else {
+        const UlIn in{s1, lv, g_depth, g_sil, u->t_hist + (size_t)s1 * w->pool.cap, u->lam};
+        launch_ul_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, nr, n_lat, tile, in, b->bsum, b->boff,
+                          b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, b->sample_lat,
+                          w->cs->sample_cam, st);
+      }
+      {
+        TimedLaunch tl(ctx, 2, st, b->n_samples, 1);
+        launch_adjoint(prec, aa, grid, st);
+      }
+      if (group) {
+        const UlGroup in = steps_of(lv, std::max(first, s1 - per + 1), s1);
+        launch_ulg_lambda(w->pool, w->imgs, w->img_order, n_img, nr, in, b->boff, b->samples, w->cs->gp, w->ur->gm,
+                          st);
+        launch_ul_colsum(w->ur->delta, w->ur->gm, b->n_samples, (int)cap, w0, ws, ctx->kmax, b->partial, st);
+        reduce(1, 1);
+      } else {
+        reduce(groups_s0(ctx, adjoint_waves()), groups_skip(ctx, adjoint_waves()));
+        launch_ul_lambda(w->pool, b->samples, w->cs->sample_cam, w->cs->gp, b->n_samples, (int)cap, u->lam, st);
+      }
     }
-    launch_gz_reduce(b->partial, ctx->kmax, tile, (int)(cap / tile) + 1, b->seg_base, b->seg_padded, n_lat, w0,
-                     groups_s0(ctx, adjoint_waves()), ctx->w0z, ws, groups_skip(ctx, adjoint_waves()),
-                     ctx->skip >= 0 ? ctx->wsz : nullptr, ctx->L, g_z, st, 0, 1);
-    launch_ul_lambda(w->pool, b->samples, w->cs->sample_cam, w->cs->gp, b->n_samples, (int)cap, u->lam, st);
   }
   HIPCHK(hipGetLastError());
   return DIST_OK;

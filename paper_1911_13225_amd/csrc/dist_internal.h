@@ -162,6 +162,11 @@ struct AdjArgs {
   // [sample][kGpSlots][3] (the spatial gradient of m, weighted by the row's
   // factor; slots beyond a layer's wave count hold zeros)
   float* gp_part;
+  // k_adjoint, optional, in place of the column sums: every row's delta at
+  // layer 0 and at the skip layer, [sample][wpad 0 + wpad skip], and its factor
+  // gm, for column sums weighted later (k_ul_colsum)
+  float* delta_out;
+  float* gm_out;
   // colour network (k_color_adjoint): per sample dL/d(colour), (r, g, b, 0)
   const float4* cseed;
 };

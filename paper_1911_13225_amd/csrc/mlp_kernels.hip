@@ -559,6 +559,8 @@ struct EpCtx {
   float* gp;                // camera gradient: per-row point-gradient partials [row][kGpSlots][3] (or null)
   int gp_row0;              // global row index of the tile's first row
   bool gp_accum;            // add to the partials (the skip layer wrote them first)
+  float* delta;             // rows of this layer's delta, from the tile's first row (or null)
+  int dstride;              // floats per delta row
 };
 
 // 1 if x > 0, else 0, as an integer clamp med3(bits, 0, 1) of the float's bits
@@ -895,7 +897,19 @@ __device__ __forceinline__ void ep_vjp(const NetDev& net, const EpCtx& ec, f32x1
       }
     }
   }
-  if (ec.which >= 0) {
+  if (GP && ec.delta && ec.which >= 0) {
+    // the rows themselves, for column sums with weights that are not known yet
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) {
+      float* row = ec.delta + (size_t)((mt0 + i) * 32 + r) * ec.dstride;
+#pragma unroll
+      for (int j = 0; j < NTW; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *(float4*)(row + feat(nt0, j, q, g)) = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1],
+                                                             acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    }
+  } else if (ec.which >= 0) {
     // column sums over the tile's rows, each row scaled by its seed gm[m]
 #pragma unroll
     for (int j = 0; j < NTW; ++j) {
@@ -1750,6 +1764,11 @@ __device__ __forceinline__ void vjp_layers(const AdjArgs& a, const Sm<P>& s, con
     ec.gp = a.gp_part;
     ec.gp_row0 = tile * Cfg<P>::M;
     ec.gp_accum = (l - 1 == 0) && net.skip >= 1;   // the skip layer comes first in this loop
+    if (GP && a.delta_out) {
+      // row layout: layer 0's features, then the skip layer's
+      ec.dstride = net.wpad[0] + (net.skip >= 1 ? net.wpad[net.skip] : 0);
+      ec.delta = a.delta_out + (size_t)tile * Cfg<P>::M * ec.dstride + (ec.which == 1 ? net.wpad[0] : 0);
+    }
     if constexpr (CAP) {
       ec.drow = cap_ptr<P>(a.dbuf, (size_t)(l - 1) * net.kmax * a.cap_rows + blk0);
       ec.rstride = kCapBlock;
@@ -1797,6 +1816,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
       const float th = tanhf(m);
       s.gm[tid] = s.fval[tid] * 0.05f * (1.f - th * th);
       if (theta) cap_put<P>(a.gmbuf, row0 + tid, s.gm[tid]);
+      else if (a.gm_out) a.gm_out[(size_t)tile * M + tid] = s.gm[tid];
     }
     __syncthreads();
     if (theta) {

@@ -51,6 +51,30 @@ struct UlIn {
   const float* lam;
 };
 
+// Several steps of that gradient at once (see k_ulg_lambda): the rays of level
+// lvl at their steps in [s0, s1], t_hist [step][t_stride].
+struct UlGroup {
+  int s0, s1, lvl;
+  const float* g_depth;
+  const float* g_sil;
+  const float* t_hist;
+  size_t t_stride;
+  float* lam;
+};
+// Rows of one group: unit-seed samples (launch_ulg_samples), then, with the
+// adjoint's point gradients, every sample's seed and the rays' adjoints
+// (launch_ulg_lambda), then the column sums of the saved delta rows
+// (launch_ul_colsum, partials as the adjoint writes them: one row group).
+void launch_ulg_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent, int n_img,
+                        int nr, int n_lat, int tile, const UlGroup& in, int* bsum, int* boff, int* seg_base,
+                        int* seg_total, int* seg_padded, int* n_samples, float4* samples, int* sample_lat,
+                        hipStream_t s);
+void launch_ulg_lambda(const RayPool& pl, const ImgDesc* imgs, const int* img_order, int n_img, int nr,
+                       const UlGroup& in, const int* boff, const float4* samples, const float* gp_part, float* gm,
+                       hipStream_t s);
+void launch_ul_colsum(const float* delta, const float* gm, const int* n_samples, int max_samples, int w0, int ws,
+                      int kmax, float* partial, hipStream_t s);
+
 // Second sample list of the split layout (normal-stencil samples).
 struct SplitList {
   int* bsum;
