@@ -92,9 +92,10 @@ struct MarchArgs {
   const int* list;                 // active ray slots
   const int* count;                // number of entries in list
   unsigned long long* qcount;      // per-image decoder queries
-  int* ecount;                     // k_march: per-image count of non-finite queries (or null)
-  // k_march_run: steps [n_begin, n_end) of every ray of the list (ACTIVE, its
-  // records empty), with the call's tracing parameters
+  // batch: steps [n_begin, n_end) of every ray of the list (ACTIVE, its
+  // records empty), with the call's tracing parameters.  Pool: up to n_end -
+  // n_begin steps of every ray from where it stands, with its image's
+  // parameters (alpha here only weighs the tile heights).
   int n_begin, n_end, max_steps, K;
   float alpha, eps;
   // a second run of *count_tail entries stored backwards from
@@ -107,6 +108,12 @@ struct MarchArgs {
   int mark_long;
   float* t_hist;                   // [max_steps][pool.cap]: t of each ray at each of its steps (or null)
   unsigned long long* rows_done;   // queries made, added at the end (or null)
+  // pool: full-resolution rays still ACTIVE, and their number per image; the
+  // non-finite queries per image
+  int* next_list;
+  int* next_count;
+  int* img_active;
+  int* ecount;
 };
 
 struct EvalArgs {
@@ -226,10 +233,10 @@ size_t mlp_smem_bytes(int precision, const NetDev& net);
 size_t adj_mask_words(int precision, const NetDev& net);   // per workgroup
 hipError_t mlp_setup(int precision, const NetDev& net);    // raise LDS limits
 
-// one step of every ray of the list (bf16, the serving pool)
-void launch_march(const MarchArgs& a, int grid, hipStream_t s);
 // all steps of one coarse-to-fine level
 void launch_march_run(int precision, const MarchArgs& a, int grid, hipStream_t s);
+// a few steps of every ray of the serving pool (bf16)
+void launch_march_pool(const MarchArgs& a, int grid, hipStream_t s);
 void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t s);
 // recompute-and-VJP: precision kPrecSplit or kPrecF32 (no bf16 variant; other
 // values launch nothing); VJP from saved masks: any precision

@@ -1249,127 +1249,6 @@ __device__ __forceinline__ void row_share(long long count, long long& first, lon
   last = min(count, t * (blockIdx.x + 1) / G * g);
 }
 
-// ---------------------------------------------------------------------------
-// March step of the serving pool (Alg. 1 with aggressive steps, convergence
-// and escape; Sec. 3.2): one query of every ray of the active list.
-// ---------------------------------------------------------------------------
-// Load the rays of one tile: row i < k takes ray slot rid_of(i), the other
-// rows of the M-row tile stay idle (rid -1).
-template <int P, int M, class RidOf>
-__device__ __forceinline__ void march_load(const MarchArgs& a, const Sm<P>& s, int k, RidOf rid_of) {
-  const int tid = threadIdx.x;
-  if (tid < M) {
-    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-    int lt = 0, r = -1;
-    if (tid < k) {
-      r = rid_of(tid);
-      const ImgDesc& im = a.imgs[a.pool.img[r]];
-      const float4 d = a.pool.d[r];
-      p = make_float4(fmaf(d.w, d.x, im.c[0]), fmaf(d.w, d.y, im.c[1]), fmaf(d.w, d.z, im.c[2]), 0.f);
-      lt = im.latent;
-    }
-    s.pts[tid] = p;
-    s.lat[tid] = lt;
-    s.rid[tid] = r;
-  }
-  __syncthreads();
-}
-
-// One decoder query per loaded row and the march epilogue: running top-K of
-// |f|, convergence (|f| < eps, Eq. 1), the step limit, the aggressive step
-// t += alpha f and the unit-sphere escape test.  The queries are counted per
-// image.
-template <int P, int M>
-__device__ __forceinline__ void march_eval(const MarchArgs& a, const Sm<P>& s) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wn = mlp_forward<P, kFwdWaves<P>, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
-  if (tid < M && s.rid[tid] >= 0) {
-    float m = a.net.blast;
-    for (int w = 0; w < wn; ++w) m += s.part[w * M + tid];
-    const float4 p = s.pts[tid];
-    const float f = sdf_from_m(p, m);
-    const int r = s.rid[tid];
-    const RayPool& pl = a.pool;
-    const ImgDesc& im = a.imgs[pl.img[r]];
-    const int n = pl.n[r];
-    float* dw = reinterpret_cast<float*>(pl.d) + 4 * (size_t)r + 3;   // t, the ray's distance
-    const float t = *dw;
-    // running K smallest |f| (ties keep the earlier step)
-    const float af = fabsf(f);
-    const int Kr = im.K;
-    float rec_abs[kMaxK];
-    for (int k = 0; k < Kr; ++k) rec_abs[k] = fabsf(pl.rec_f[(size_t)k * pl.cap + r]);
-    const int pos = topk_rank(af, rec_abs, Kr);
-    for (int k = Kr - 1; k > pos; --k) {
-      pl.rec_f[(size_t)k * pl.cap + r] = pl.rec_f[(size_t)(k - 1) * pl.cap + r];
-      pl.rec_t[(size_t)k * pl.cap + r] = pl.rec_t[(size_t)(k - 1) * pl.cap + r];
-      pl.rec_n[(size_t)k * pl.cap + r] = pl.rec_n[(size_t)(k - 1) * pl.cap + r];
-    }
-    if (pos < Kr) {
-      pl.rec_f[(size_t)pos * pl.cap + r] = f;
-      pl.rec_t[(size_t)pos * pl.cap + r] = t;
-      pl.rec_n[(size_t)pos * pl.cap + r] = (uint8_t)n;
-    }
-    pl.flast[r] = f;
-    uint8_t st;
-    if (!(af == af) || af == INFINITY) {
-      st = ST_ERROR;                         // non-finite query: stop the ray, report it
-      if (a.ecount) atomicAdd(&a.ecount[pl.img[r]], 1);
-    } else if (af < im.eps) {
-      st = ST_HIT;
-    } else if (n == im.max_steps - 1) {
-      st = ST_UNCONVERGED;
-    } else {
-      const float tn = fmaf(im.alpha, f, t);
-      const float2 b = pl.b[r];
-      st = (tn > b.y || tn < b.x) ? ST_ESCAPED : ST_ACTIVE;
-      *dw = tn;
-    }
-    pl.st[r] = st;
-    pl.n[r] = (uint8_t)(n + 1);
-  }
-  if (a.qcount && tid < M) {
-    // queries of this tile per image, one atomic per distinct image in a wave
-    const int r = s.rid[tid];
-    const bool valid = r >= 0;
-    const int img = valid ? a.pool.img[r] : -1;
-    unsigned long long todo = __ballot(valid);
-    while (todo) {
-      const int leader = __ffsll((long long)todo) - 1;
-      const int li = __shfl(img, leader);
-      const unsigned long long same = __ballot(valid && img == li);
-      if (lane == leader) atomicAdd(&a.qcount[li], (unsigned long long)__popcll(same));
-      todo &= ~same;
-    }
-  }
-}
-
-// One march step over the active list, its rays dealt out as the rows of a
-// query (row_share).
-__global__ __launch_bounds__(kFwdWaves<1> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<1> / 4, kFwdWaves<1> / 4))) void k_march(MarchArgs a) {
-  Sm<1> s(dyn_smem, a.net.kmax);
-  long long first, last;
-  row_share<1>(*a.count, first, last);
-  int base = (int)first;
-  while (base < (int)last) {
-    const int left = min((int)last - base, Cfg<1>::M), m = next_tile<1>(left);
-    auto rid_of = [&](int i) { return a.list[base + i]; };
-    const int k = min(left, m);
-    if (m == 32) {
-      march_load<1, 32>(a, s, k, rid_of);
-      march_eval<1, 32>(a, s);
-    } else if (m == 64) {
-      march_load<1, 64>(a, s, k, rid_of);
-      march_eval<1, 64>(a, s);
-    } else {
-      march_load<1, 128>(a, s, k, rid_of);
-      march_eval<1, 128>(a, s);
-    }
-    base += k;
-    __syncthreads();
-  }
-}
-
 // Offset of this thread among the workgroup's threads with flag set (thread
 // order) and their total, without atomics.
 template <int NT>
@@ -1391,8 +1270,10 @@ __device__ __forceinline__ int wg_prefix(bool flag, int* total) {
 }
 
 // ---------------------------------------------------------------------------
-// The march of a batch render: every step of one coarse-to-fine level in one
-// launch (Alg. 1, Sec. 3.2; the steps after the last split run to max_steps).
+// The march (Alg. 1 with aggressive steps, convergence and escape; Sec. 3.2).
+// A batch render runs every step of one coarse-to-fine level in one launch (the
+// steps after the last split run to max_steps), the serving pool (POOL) three
+// steps of every pooled ray, whatever its request, level and step.
 // A ray's trajectory depends on that ray alone, so the rays need not advance
 // in lockstep: a workgroup holds up to `top` rays in the rows of its tile and
 // keeps their whole state (direction, t, interval, camera centre, top-K
@@ -1418,6 +1299,7 @@ struct MarchRows {
   float2* b;               // t_lo, t_hi
   int* img;
   int* n;                  // next global step
+  int* start;              // its step at the start of the launch
   unsigned* rn;            // records' steps, one byte each
   float2* fp;              // the two queries before the last one (f of steps n - 2 and n - 1)
   float* rf;               // records [kMaxK][M]
@@ -1429,12 +1311,13 @@ struct MarchRows {
     fp = b + M;
     img = (int*)(fp + M);
     n = img + M;
-    rn = (unsigned*)(n + M);
+    start = n + M;
+    rn = (unsigned*)(start + M);
     rf = (float*)(rn + M);
     rt = rf + kMaxK * M;
   }
 };
-__host__ __device__ constexpr size_t march_row_bytes() { return 16 + 16 + 8 + 8 + 4 + 4 + 4 + 2 * 4 * kMaxK; }
+__host__ __device__ constexpr size_t march_row_bytes() { return 16 + 16 + 8 + 8 + 4 + 4 + 4 + 4 + 2 * 4 * kMaxK; }
 
 // Smallest tile height that holds `live` rays.
 template <int P>
@@ -1494,7 +1377,7 @@ __device__ __forceinline__ float graze(float f0, float f1, float f2, float alpha
   return f2 * c - 0.5f * sl * sl;
 }
 
-template <int P>
+template <int P, bool POOL>
 __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_march_run(MarchArgs a) {
   constexpr int M = Cfg<P>::M, NW = kFwdWaves<P>, NT = NW * 64;
   __shared__ int claim_lds;
@@ -1502,7 +1385,7 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
   MarchRows rw((char*)(s.part + 8 * M), M);
   const int tid = threadIdx.x, lane = tid & 63;
   const RayPool& pl = a.pool;
-  const int nh = *a.count, n0 = nh + (a.count_tail ? *a.count_tail : 0), K = a.K;
+  const int nh = *a.count, n0 = nh + (a.count_tail ? *a.count_tail : 0), steps = a.n_end - a.n_begin;
   const int top = march_top<P>(a, n0, nh, gridDim.x), chunk = top / 2;
   int live = 0, rb = 0, re = 0;          // rows in use; claimed list entries not loaded yet
   bool more = true;
@@ -1520,7 +1403,7 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
     }
     const int fresh = have + min(need - have, got);
     if (tid >= live && tid < live + fresh) {
-      // the ray's whole state: its records start empty at every level
+      // the ray's whole state; its records start empty at every level
       const int i = tid - live, j = i < have ? rb + i : st0 + i - have;
       const int r = j < nh ? a.list[j] : a.list[a.tail_end - 1 - (j - nh)];
       const int img = pl.img[r];
@@ -1531,12 +1414,16 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       rw.c[tid] = make_float4(im.c[0], im.c[1], im.c[2], __int_as_float(im.latent));
       rw.b[tid] = b;
       rw.img[tid] = img;
-      rw.n[tid] = a.n_begin;
-      rw.rn[tid] = 0u;
-      for (int k = 0; k < K; ++k) {
-        rw.rf[k * M + tid] = INFINITY;
-        rw.rt[k * M + tid] = 0.f;
+      const int n = POOL ? pl.n[r] : a.n_begin;
+      rw.n[tid] = n;
+      rw.start[tid] = n;
+      unsigned rn = 0u;
+      for (int k = 0; k < (POOL ? im.K : a.K); ++k) {
+        rw.rf[k * M + tid] = POOL ? pl.rec_f[(size_t)k * pl.cap + r] : INFINITY;
+        rw.rt[k * M + tid] = POOL ? pl.rec_t[(size_t)k * pl.cap + r] : 0.f;
+        if (POOL) rn |= (unsigned)pl.rec_n[(size_t)k * pl.cap + r] << (8 * k);
       }
+      rw.rn[tid] = rn;
       s.rid[tid] = r;
     }
     if (have < need) {                   // the reserve is spent; what is left of the claim replaces it
@@ -1555,7 +1442,7 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
         const float4 d = rw.dt[tid], c = rw.c[tid];
         p = make_float4(fmaf(d.w, d.x, c.x), fmaf(d.w, d.y, c.y), fmaf(d.w, d.z, c.z), 0.f);
         lt = __float_as_int(c.w);
-        if (a.t_hist) a.t_hist[(size_t)rw.n[tid] * pl.cap + s.rid[tid]] = d.w;
+        if (!POOL && a.t_hist) a.t_hist[(size_t)rw.n[tid] * pl.cap + s.rid[tid]] = d.w;
       }
       s.pts[tid] = p;
       s.lat[tid] = lt;
@@ -1570,11 +1457,11 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
     else wn = mlp_forward<P, NW, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
     // epilogue: top-K of |f|, convergence (Eq. 1), step limit, the aggressive
     // step and the escape test
-    bool still = false, stop = false;
+    bool still = false, stop = false, next = false;
     float f = 0.f;
     float4 d{}, c{};
     float2 b{}, fp{};
-    int r = 0, img = 0, n = 0;
+    int r = 0, img = 0, n = 0, start = 0, K = a.K;
     unsigned rn = 0;
     float rf[kMaxK] = {}, rt[kMaxK] = {};
     if (tid < live) {
@@ -1587,8 +1474,13 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       r = s.rid[tid];
       img = rw.img[tid];
       n = rw.n[tid];
+      start = rw.start[tid];
       rn = rw.rn[tid];
-      fp = rw.fp[tid];
+      if (!POOL) fp = rw.fp[tid];
+      const ImgDesc& im = a.imgs[img];         // the pool's rays follow their own request's parameters
+      const float eps = POOL ? im.eps : a.eps, alpha = POOL ? im.alpha : a.alpha;
+      const int max_steps = POOL ? im.max_steps : a.max_steps;
+      if (POOL) K = im.K;
       float rec_abs[kMaxK];
       for (int k = 0; k < K; ++k) {
         rf[k] = rw.rf[k * M + tid];
@@ -1611,22 +1503,26 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       uint8_t st;
       if (!(af == af) || af == INFINITY) {
         st = ST_ERROR;                         // non-finite query: stop the ray, report it
-      } else if (af < a.eps) {
+        if (POOL) atomicAdd(&a.ecount[img], 1);
+      } else if (af < eps) {
         st = ST_HIT;
-      } else if (n == a.max_steps - 1) {
+      } else if (n == max_steps - 1) {
         st = ST_UNCONVERGED;
       } else {
-        d.w = fmaf(a.alpha, f, d.w);
+        d.w = fmaf(alpha, f, d.w);
         st = (d.w > b.y || d.w < b.x) ? ST_ESCAPED : ST_ACTIVE;
       }
       ++n;
-      still = st == ST_ACTIVE && n < a.n_end;
+      still = st == ST_ACTIVE && n - start < steps;
       stop = !still;
+      // a full-resolution ray of the pool marches on in the next launch (the
+      // coarse levels end with their three steps: a split follows)
+      if (POOL) next = stop && st == ST_ACTIVE && r - im.slot_base < im.H * im.W;
       if (stop) {
         pl.d[r] = d;
         pl.st[r] = st;
         pl.n[r] = (uint8_t)n;
-        pl.flast[r] = a.mark_long && st == ST_ACTIVE ? graze(fp.x, fp.y, f, a.alpha) : f;
+        pl.flast[r] = !POOL && a.mark_long && st == ST_ACTIVE ? graze(fp.x, fp.y, f, a.alpha) : f;
         for (int k = 0; k < K; ++k) {
           pl.rec_f[(size_t)k * pl.cap + r] = rf[k];
           pl.rec_t[(size_t)k * pl.cap + r] = rt[k];
@@ -1640,11 +1536,22 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       const int leader = __ffsll((long long)todo) - 1;
       const int li = __shfl(img, leader);
       const bool mine = stop && img == li;
-      int q = mine ? n - a.n_begin : 0;
+      int q = mine ? n - start : 0;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
       if (lane == leader) atomicAdd(&a.qcount[li], (unsigned long long)q);
+      if (POOL) {
+        const unsigned long long on = __ballot(mine && next);
+        if (on && lane == leader) atomicAdd(&a.img_active[li], __popcll(on));
+      }
       todo &= ~__ballot(mine);
+    }
+    if (POOL) {
+      const unsigned long long on = __ballot(next);
+      int at = 0;
+      if (on && lane == 0) at = atomicAdd(a.next_count, __popcll(on));
+      at = __shfl(at, 0);
+      if (next) a.next_list[at + __popcll(on & ((1ull << lane) - 1ull))] = r;
     }
     rows += live;
     int tot;
@@ -1655,8 +1562,9 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       rw.b[pos] = b;
       rw.img[pos] = img;
       rw.n[pos] = n;
+      rw.start[pos] = start;
       rw.rn[pos] = rn;
-      if (a.mark_long) rw.fp[pos] = make_float2(fp.y, f);
+      if (!POOL && a.mark_long) rw.fp[pos] = make_float2(fp.y, f);
       for (int k = 0; k < K; ++k) {
         rw.rf[k * M + pos] = rf[k];
         rw.rt[k * M + pos] = rt[k];
@@ -2310,7 +2218,7 @@ void launch_dw(int precision, DwBatch& b, hipStream_t st) {
 
 template <int P>
 static hipError_t setup_p(int bytes) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_march_run<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  hipError_t e = hipFuncSetAttribute((const void*)k_march_run<P, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      bytes + (int)march_row_bytes() * Cfg<P>::M);
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)k_eval<P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -2335,7 +2243,8 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
   if (precision == 1) {
     hipError_t e = hipFuncSetAttribute((const void*)k_dw_bf16, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)k_march, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    e = hipFuncSetAttribute((const void*)k_march_run<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            bytes + (int)march_row_bytes() * Cfg<1>::M);
     if (e != hipSuccess) return e;
     return setup_p<1>(bytes);
   }
@@ -2343,9 +2252,9 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
   return setup_p<0>(bytes);
 }
 
-#define DIST_DISPATCH(KERNEL, ARGS, MORE)                                                              \
+#define DIST_DISPATCH(KERNEL, ARGS)                                                                    \
   do {                                                                                                 \
-    const size_t sm = mlp_smem_bytes(precision, ARGS.net) + (MORE);                                    \
+    const size_t sm = mlp_smem_bytes(precision, ARGS.net);                                             \
     const dim3 blk(fwd_threads(precision));                                                            \
     if (precision == 1) hipLaunchKernelGGL(KERNEL<1>, dim3(grid), blk, sm, st, ARGS);                  \
     else if (precision == 2) hipLaunchKernelGGL(KERNEL<2>, dim3(grid), blk, sm, st, ARGS);             \
@@ -2361,11 +2270,16 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
     else if (precision == 0) hipLaunchKernelGGL(KERNEL<0>, dim3(grid), blk, sm, st, ARGS);             \
   } while (0)
 
-void launch_march(const MarchArgs& a, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_march, dim3(grid), dim3(fwd_threads(kPrecBF16)), mlp_smem_bytes(kPrecBF16, a.net), st, a);
-}
 void launch_march_run(int precision, const MarchArgs& a, int grid, hipStream_t st) {
-  DIST_DISPATCH(k_march_run, a, march_row_bytes() * rows_for(precision));
+  const size_t sm = mlp_smem_bytes(precision, a.net) + march_row_bytes() * rows_for(precision);
+  const dim3 blk(fwd_threads(precision));
+  if (precision == 1) hipLaunchKernelGGL((k_march_run<1, false>), dim3(grid), blk, sm, st, a);
+  else if (precision == 2) hipLaunchKernelGGL((k_march_run<2, false>), dim3(grid), blk, sm, st, a);
+  else hipLaunchKernelGGL((k_march_run<0, false>), dim3(grid), blk, sm, st, a);
+}
+void launch_march_pool(const MarchArgs& a, int grid, hipStream_t st) {
+  hipLaunchKernelGGL((k_march_run<kPrecBF16, true>), dim3(grid), dim3(fwd_threads(kPrecBF16)),
+                     mlp_smem_bytes(kPrecBF16, a.net) + march_row_bytes() * rows_for(kPrecBF16), st, a);
 }
 void launch_color(int precision, const ColorArgs& a, int grid, hipStream_t st) {
   const size_t sm = mlp_smem_bytes(precision, a.net);
@@ -2377,7 +2291,7 @@ void launch_color_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t
   if (precision == 2) hipLaunchKernelGGL(k_color_adjoint<2>, dim3(grid), dim3(kBwdWaves * 64), sm, st, a);
   else if (precision == 0) hipLaunchKernelGGL(k_color_adjoint<0>, dim3(grid), dim3(kBwdWaves * 64), sm, st, a);
 }
-void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_eval, a, 0); }
+void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_eval, a); }
 void launch_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t st) { DIST_DISPATCH_BWD(k_adjoint, a); }
 static_assert(kAdjWaves * 64 == 512, "the recompute-and-VJP dispatch assumes 8 waves");
 int mlp_row_groups(int waves, int width) { return (waves == 8 && width <= 128) ? 2 : 1; }

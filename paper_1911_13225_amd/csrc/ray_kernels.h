@@ -125,10 +125,9 @@ void launch_color_samples(const RayPool& pl, const ImgDesc* imgs, const int* img
                           int* seg_base, int* seg_total, int* seg_padded, int* n_samples, float4* samples,
                           float4* cseed, int* sample_lat, long long cap, hipStream_t s);
 void launch_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* hdr, int max_entries, hipStream_t s);
-// Two launches: the previous list's survivors, then the rays that start this
-// tick (split children and (re)started images).
-void launch_advance(const RayPool& pl, const ImgDesc* imgs, const int* in_list, const int* in_count, int* out_list,
-                    int* out_count, const AdvEntry* table, const int* hdr, int* img_active, int grid, hipStream_t s);
+// The rays that start this tick (split children and (re)started images) join the list.
+void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
+                    const int* hdr, int grid, hipStream_t s);
 // Per-image loss of inverse optimisation (L1 depth, silhouette hinge, normal
 // term) and its map gradients; one workgroup per image, fixed order.
 void launch_render_loss(const float* depth, const float* normal, const float* sil, const float* depth_t,

@@ -692,14 +692,9 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
 }
 
 // ---------------------------------------------------------------------------
-// Serving: the next pooled active list is built from (a) the rays still active
-// in the previous list and then (b) the children of images that split this
-// tick and the coarsest rays of newly (re)started images, counting per image
-// the rays it has in the new list.  (a) and (b) are separate launches: a ray
-// slot released by a finished request can be handed to a request that starts
-// this tick while the previous list still names it, and the stale entry must
-// be read (and dropped, its ray having stopped) before the slot is
-// re-initialised.
+// Serving: the rays that start this tick, the children of images that split
+// and the coarsest rays of newly (re)started images, join the pooled active
+// list behind the rays that the last march left active.
 // ---------------------------------------------------------------------------
 __global__ void k_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* hdr) {
   const int n = hdr[0];
@@ -707,50 +702,13 @@ __global__ void k_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* 
     imgs[table[i].img].cur_level = table[i].lvl;
 }
 
-// per-image count of the wave's flagged entries: one atomic per distinct image
-__device__ __forceinline__ void count_per_image(bool flag, int img, int* img_active) {
-  const int lane = threadIdx.x & 63;
-  unsigned long long todo = __ballot(flag);
-  while (todo) {
-    const int leader = __ffsll((long long)todo) - 1;
-    const int li = __shfl(img, leader);
-    const unsigned long long same = __ballot(flag && img == li);
-    if (lane == leader) atomicAdd(&img_active[li], __popcll(same));
-    todo &= ~same;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_advance_old(RayPool pl, const ImgDesc* imgs, const int* in_list,
-                                                     const int* in_count, int* out_list, int* out_count,
-                                                     int* img_active) {
-  const int n_old = *in_count;
-  for (int base = blockIdx.x * 256; base < n_old; base += gridDim.x * 256) {
-    const int i = base + threadIdx.x;
-    bool keep = false;
-    int r = 0, img = -1;
-    if (i < n_old) {
-      r = in_list[i];
-      if (pl.st[r] == ST_ACTIVE) {
-        img = pl.img[r];
-        const ImgDesc& im = imgs[img];
-        const int off = r - im.slot_base;
-        const int hw = im.H * im.W;
-        const int lvl = off < hw ? 0 : (off < hw + (hw >> 2) ? 1 : 2);
-        keep = lvl == im.cur_level;
-      }
-    }
-    count_per_image(keep, img, img_active);
-    block_append(keep, r, out_list, out_count);
-  }
-}
-
 __global__ __launch_bounds__(256) void k_advance_new(RayPool pl, const ImgDesc* imgs, int* out_list, int* out_count,
-                                                     const AdvEntry* table, const int* hdr, int* img_active) {
+                                                     const AdvEntry* table, const int* hdr) {
   const int n_tab = hdr[0], n_new = hdr[1];
   for (int base = blockIdx.x * 256; base < n_new; base += gridDim.x * 256) {
     const int j = base + threadIdx.x;
     bool keep = false;
-    int r = 0, img = -1;
+    int r = 0;
     if (j < n_new) {
       int lo = 0, hi = n_tab - 1;          // last entry with begin <= j
       while (lo < hi) {
@@ -758,8 +716,7 @@ __global__ __launch_bounds__(256) void k_advance_new(RayPool pl, const ImgDesc* 
         if (table[mid].begin <= j) lo = mid; else hi = mid - 1;
       }
       const AdvEntry e = table[lo];
-      img = e.img;
-      const ImgDesc& im = imgs[img];
+      const ImgDesc& im = imgs[e.img];
       const int c = j - e.begin;
       const int lvl = e.lvl;
       const int Wl = im.W >> lvl;
@@ -776,10 +733,9 @@ __global__ __launch_bounds__(256) void k_advance_new(RayPool pl, const ImgDesc* 
         t = fminf(fmaxf(tp, t_lo), t_hi);
       }
       r = im.slot_base + im.lvl_off[lvl] + c;
-      init_ray(pl, im, img, r, d, t, t_lo, t_hi, inside, e.step);
+      init_ray(pl, im, e.img, r, d, t, t_lo, t_hi, inside, e.step);
       keep = inside;
     }
-    count_per_image(keep, img, img_active);
     block_append(keep, r, out_list, out_count);
   }
 }
@@ -1308,12 +1264,9 @@ void launch_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* hdr, i
   hipLaunchKernelGGL(k_apply_levels, dim3(nblk(max_entries > 0 ? max_entries : 1, 256)), dim3(256), 0, s, imgs, table,
                      hdr);
 }
-void launch_advance(const RayPool& pl, const ImgDesc* imgs, const int* in_list, const int* in_count, int* out_list,
-                    int* out_count, const AdvEntry* table, const int* hdr, int* img_active, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_advance_old, dim3(grid), dim3(256), 0, s, pl, imgs, in_list, in_count, out_list, out_count,
-                     img_active);
-  hipLaunchKernelGGL(k_advance_new, dim3(grid), dim3(256), 0, s, pl, imgs, out_list, out_count, table, hdr,
-                     img_active);
+void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
+                    const int* hdr, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(k_advance_new, dim3(grid), dim3(256), 0, s, pl, imgs, list, count, table, hdr);
 }
 void launch_render_loss(const float* depth, const float* normal, const float* sil, const float* depth_t,
                         const float* normal_t, const float* sil_t, int n_img, int hw, float w_d, float w_s, float w_n,

@@ -105,6 +105,9 @@ struct Backend {
   // the job holds its ray slots, image slots and latent: descriptors,
   // latent code, optimiser state, first render
   virtual void begin(Job* j) = 0;
+  // marching steps of one tick: 1 or 3 (the coarse-to-fine splits, every third
+  // step, fall between ticks)
+  virtual int steps_per_tick() const { return 1; }
   // one tick: start the table's rays, march every pooled active ray, and
   // make active(img) / queries(img) current; DIST_OK or an error code
   virtual int tick(const std::vector<TickEntry>& table, int n_new) = 0;
@@ -301,7 +304,7 @@ class Core {
       // progress and completion
       std::vector<Job*> keep;
       for (Job* j : running_) {
-        j->step += 1;
+        j->step += be_->steps_per_tick();
         bool all = true;
         for (int v = 0; v < j->n_views; ++v) {
           if (!j->img_done[v]) {

@@ -3,11 +3,15 @@
 //
 // One persistent ray pool holds the rays of every admitted request.  Each
 // tick replays a captured hipGraph on the server stream:
-//     clear counters -> apply level changes -> advance (previous active list
-//     + coarse-to-fine splits + newly started images -> next active list)
-//     -> march (the bf16 decoder on every active ray of every request)
+//     clear counters -> apply level changes -> advance (coarse-to-fine splits
+//     and newly started images join the active list) -> march (three steps of
+//     every active ray of every request with the bf16 decoder; the rays left
+//     active form the next list)
 // so requests of different resolutions share every decoder launch, and a
-// request that arrives while others are marching joins at the next tick.
+// request that arrives while others are marching joins at the next tick.  Three
+// steps are what lies between two splits: a tick of one step spent more time
+// on its copies, launches and host synchronisation (120 us) than on its march
+// (89 us), and 158 of them served the nine requests of a burst.
 // Between ticks the scheduler thread reads the per-image active counts,
 // finalises finished requests (maps, normals), and for latent-optimisation
 // requests computes the loss, the paper's approximate gradient (adjoint) and
@@ -62,7 +66,7 @@ struct Server : sched::Backend {
   RayPool pool{};
   ImgDesc* imgs = nullptr;
   int* lists[2] = {nullptr, nullptr};
-  int* counters = nullptr;       // [2]
+  int* counters = nullptr;       // [0], [1] lengths of the lists, [2] list entries claimed by the march
   AdvEntry* table = nullptr;
   int* hdr = nullptr;            // [0] entries, [1] new rays
   int* img_active = nullptr;
@@ -70,10 +74,10 @@ struct Server : sched::Backend {
   int* ecount = nullptr;         // per image slot: queries that returned a non-finite f
   float *z_pool = nullptr, *bias0 = nullptr, *biasS = nullptr, *adam_m = nullptr, *adam_v = nullptr;
   // pinned staging
+  int* h_hdr = nullptr;          // header and table, copied together
   AdvEntry* h_table = nullptr;
-  int* h_hdr = nullptr;
+  unsigned long long* h_q = nullptr;   // queries, active rays and errors per image, copied together
   int* h_active = nullptr;
-  unsigned long long* h_q = nullptr;
   int* h_err = nullptr;
   ImgDesc* h_desc = nullptr;
   float* h_loss = nullptr;
@@ -87,6 +91,7 @@ struct Server : sched::Backend {
   bool acquire(sched::Job* j) override;
   void release(sched::Job* j) override;
   void begin(sched::Job* j) override;
+  int steps_per_tick() const override { return 3; }
   int tick(const std::vector<sched::TickEntry>& table, int n_new) override;
   int active(int img) const override { return h_active[img]; }
   int64_t queries(int img) const override { return (int64_t)h_q[img]; }
@@ -144,6 +149,9 @@ static T* carve(char*& p, size_t n) {
   return r;
 }
 
+constexpr size_t kHdrBytes = 4 * sizeof(int);                                        // before the table
+constexpr size_t kStatBytes = sizeof(unsigned long long) + 2 * sizeof(int);          // per image
+
 static size_t pool_layout(Server* s, char* base) {
   char* p = base;
   const size_t cap = s->cap_rays;
@@ -163,11 +171,11 @@ static size_t pool_layout(Server* s, char* base) {
   s->lists[0] = carve<int>(p, cap);
   s->lists[1] = carve<int>(p, cap);
   s->counters = carve<int>(p, 4);
-  s->table = carve<AdvEntry>(p, s->cap_imgs);
-  s->hdr = carve<int>(p, 4);
-  s->img_active = carve<int>(p, s->cap_imgs);
-  s->qcount = carve<unsigned long long>(p, s->cap_imgs);
-  s->ecount = carve<int>(p, s->cap_imgs);
+  s->hdr = (int*)carve<char>(p, kHdrBytes + sizeof(AdvEntry) * s->cap_imgs);
+  s->table = (AdvEntry*)((char*)s->hdr + kHdrBytes);
+  s->qcount = (unsigned long long*)carve<char>(p, kStatBytes * s->cap_imgs);
+  s->img_active = (int*)(s->qcount + s->cap_imgs);
+  s->ecount = s->img_active + s->cap_imgs;
   const int L = s->ctx->L;
   s->z_pool = carve<float>(p, (size_t)s->cap_lat * L);
   s->bias0 = carve<float>(p, (size_t)s->cap_lat * kMaxWidth);
@@ -182,21 +190,27 @@ static int capture_tick(Server* s, int par) {
   const int cur = par, nxt = par ^ 1;
   HIPCHK_S(hipStreamBeginCapture(s->st, hipStreamCaptureModeThreadLocal));
   launch_fill_i32(s->counters + nxt, 0, 1, s->st);
+  launch_fill_i32(s->counters + 2, 0, 1, s->st);
   launch_fill_i32(s->img_active, 0, s->cap_imgs, s->st);
   launch_apply_levels(s->imgs, s->table, s->hdr, s->cap_imgs, s->st);
-  launch_advance(s->pool, s->imgs, s->lists[cur], s->counters + cur, s->lists[nxt], s->counters + nxt, s->table,
-                 s->hdr, s->img_active, s->adv_grid, s->st);
+  launch_advance(s->pool, s->imgs, s->lists[cur], s->counters + cur, s->table, s->hdr, s->adv_grid, s->st);
   MarchArgs ma{};
   ma.net = ctx->net[kPrecBF16];
   ma.pool = s->pool;
   ma.imgs = s->imgs;
   ma.bias0_lat = s->bias0;
   ma.biasS_lat = s->biasS;
-  ma.list = s->lists[nxt];
-  ma.count = s->counters + nxt;
+  ma.list = s->lists[cur];
+  ma.count = s->counters + cur;
+  ma.claim = s->counters + 2;
+  ma.n_end = s->steps_per_tick();
+  ma.alpha = 1.5f;
   ma.qcount = s->qcount;          // queries counted where they are made
   ma.ecount = s->ecount;          // and non-finite ones
-  launch_march(ma, ctx->n_cu, s->st);
+  ma.next_list = s->lists[nxt];
+  ma.next_count = s->counters + nxt;
+  ma.img_active = s->img_active;
+  launch_march_pool(ma, ctx->n_cu, s->st);
   hipGraph_t g = nullptr;
   HIPCHK_S(hipStreamEndCapture(s->st, &g));
   HIPCHK_S(hipGraphInstantiate(&s->exec[par], g, nullptr, nullptr, 0));
@@ -220,11 +234,11 @@ static int pool_init(Server* s) {
   s->mem = (char*)p;
   pool_layout(s, s->mem);
   HIPCHK_S(hipMemsetAsync(s->mem, 0, s->mem_bytes, s->st));
-  HIPCHK_S(hipHostMalloc((void**)&s->h_table, sizeof(AdvEntry) * s->cap_imgs));
-  HIPCHK_S(hipHostMalloc((void**)&s->h_hdr, sizeof(int) * 4));
-  HIPCHK_S(hipHostMalloc((void**)&s->h_active, sizeof(int) * s->cap_imgs));
-  HIPCHK_S(hipHostMalloc((void**)&s->h_q, sizeof(unsigned long long) * s->cap_imgs));
-  HIPCHK_S(hipHostMalloc((void**)&s->h_err, sizeof(int) * s->cap_imgs));
+  HIPCHK_S(hipHostMalloc((void**)&s->h_hdr, kHdrBytes + sizeof(AdvEntry) * s->cap_imgs));
+  s->h_table = (AdvEntry*)((char*)s->h_hdr + kHdrBytes);
+  HIPCHK_S(hipHostMalloc((void**)&s->h_q, kStatBytes * s->cap_imgs));
+  s->h_active = (int*)(s->h_q + s->cap_imgs);
+  s->h_err = s->h_active + s->cap_imgs;
   HIPCHK_S(hipHostMalloc((void**)&s->h_desc, sizeof(ImgDesc) * s->cap_imgs));
   HIPCHK_S(hipHostMalloc((void**)&s->h_loss, sizeof(float) * s->cap_lat));
   HIPCHK_S(hipStreamSynchronize(s->st));
@@ -434,13 +448,10 @@ int Server::tick(const std::vector<sched::TickEntry>& tab, int n_new) {
   }
   h_hdr[0] = n_tab;
   h_hdr[1] = n_new;
-  if (n_tab) (void)hipMemcpyAsync(table, h_table, sizeof(AdvEntry) * n_tab, hipMemcpyHostToDevice, st);
-  (void)hipMemcpyAsync(hdr, h_hdr, sizeof(int) * 2, hipMemcpyHostToDevice, st);
+  (void)hipMemcpyAsync(hdr, h_hdr, kHdrBytes + sizeof(AdvEntry) * n_tab, hipMemcpyHostToDevice, st);
   hipError_t e = hipGraphLaunch(exec[parity], st);
   parity ^= 1;
-  (void)hipMemcpyAsync(h_active, img_active, sizeof(int) * cap_imgs, hipMemcpyDeviceToHost, st);
-  (void)hipMemcpyAsync(h_q, qcount, sizeof(unsigned long long) * cap_imgs, hipMemcpyDeviceToHost, st);
-  (void)hipMemcpyAsync(h_err, ecount, sizeof(int) * cap_imgs, hipMemcpyDeviceToHost, st);
+  (void)hipMemcpyAsync(h_q, qcount, kStatBytes * cap_imgs, hipMemcpyDeviceToHost, st);
   hipError_t e2 = hipStreamSynchronize(st);
   return (e != hipSuccess || e2 != hipSuccess) ? DIST_EHIP : DIST_OK;
 }
@@ -471,11 +482,8 @@ void serve_shutdown(dist_ctx* ctx) {
     if (s->exec[p]) (void)hipGraphExecDestroy(s->exec[p]);
   for (auto& kv : s->cache) ctx_free(ctx, kv.second, kv.first);
   if (s->mem) ctx_free(ctx, s->mem, s->mem_bytes);
-  (void)hipHostFree(s->h_table);
   (void)hipHostFree(s->h_hdr);
-  (void)hipHostFree(s->h_active);
   (void)hipHostFree(s->h_q);
-  (void)hipHostFree(s->h_err);
   (void)hipHostFree(s->h_desc);
   (void)hipHostFree(s->h_loss);
   if (s->st) (void)hipStreamDestroy(s->st);
