@@ -62,7 +62,7 @@ __host__ __device__ inline int fwd_threads(int P) { return (P == 0 ? 4 : 8) * 64
 __host__ __device__ inline size_t smem_bytes_for(int P, int kmax, int nout = 1) {
   const int M = rows_for(P);
   const int ES = P == 1 ? 2 : 4;
-  return (size_t)M * (kmax * ES + 16) + (size_t)M * (16 + 4 + 4 + 4 + 4) + (size_t)8 * M * 4 * nout;
+  return (size_t)M * (kmax * ES + 16) + (size_t)M * (16 + 4 + 4 + 4 + 4) + 16 + (size_t)8 * M * 4 * nout;
 }
 
 template <int P> struct Sm {
@@ -72,6 +72,7 @@ template <int P> struct Sm {
   int* rid;
   float* fval;
   float* gm;
+  int* uni;                 // per 64 rows: their one latent (see set_latents)
   float* part;
   int rowb;
   __device__ Sm(char* base, int kmax) {
@@ -84,6 +85,7 @@ template <int P> struct Sm {
     rid = (int*)(base + off);    off += (size_t)M * 4;
     fval = (float*)(base + off); off += (size_t)M * 4;
     gm = (float*)(base + off);   off += (size_t)M * 4;
+    uni = (int*)(base + off);    off += 16;
     part = (float*)(base + off);
   }
   __device__ __forceinline__ char* chunk(int m, int ch) const {
@@ -92,6 +94,31 @@ template <int P> struct Sm {
 };
 
 extern __shared__ __attribute__((aligned(16))) char dyn_smem[];
+
+// The latent lt of this thread's row of an M-row tile (valid: the row holds a
+// ray or sample), and per 64 rows the latent that all of them share: the
+// per-latent biases of layer 0 and of the skip layer are then one matrix-core
+// operand (acc_points).  Called by every thread before the barrier that ends
+// the tile's setup; row 0 is always valid.
+constexpr int kAnyLatent = -2;
+template <int P, int M>
+__device__ __forceinline__ void set_latents(const Sm<P>& s, int lt, bool valid) {
+  const int tid = threadIdx.x;
+  if (tid < (M > 64 ? M : 64)) {
+    const unsigned long long on = __ballot(valid);
+    const int first = __shfl(lt, on ? __ffsll((long long)on) - 1 : 0);
+    const unsigned long long other = __ballot(valid && lt != first);
+    if ((tid & 63) == 0) s.uni[tid >> 6] = on == 0 ? kAnyLatent : (other == 0 ? first : -1);
+    if (tid < M) s.lat[tid] = lt;
+  }
+}
+
+// The tile's one latent, or -1 (uniform over the workgroup).
+template <int P, int M>
+__device__ __forceinline__ int one_latent(const Sm<P>& s) {
+  const int u0 = s.uni[0], u1 = M > 64 ? s.uni[1] : kAnyLatent;
+  return __builtin_amdgcn_readfirstlane(u1 == kAnyLatent || u1 == u0 ? u0 : -1);
+}
 
 // An opaque copy of a lane-dependent value: addresses derived from it are
 // computed where they are used instead of being hoisted out of the layer and
@@ -546,6 +573,7 @@ struct EpCtx {
   const float* wsp;         // skip point columns [3][wpad]
   int wpad;                 // output width of this layer (stride of biasS/wsp)
   bool skip;                // this layer reads [h, z, p]
+  int ul;                   // the tile's one latent, or -1
   int layer;                // index of the layer whose output this epilogue produces
   MaskRef mk;               // where the ReLU mask bits of each row live
   int ntmax;                // words per mask row of one layer
@@ -699,6 +727,136 @@ __device__ __forceinline__ void acc_bias(f32x16 (&acc)[MTW][NTW], const EpCtx& e
           acc[i][j][4 * q + 3] = fmaf(wx.w, p[i].x, fmaf(wy.w, p[i].y, fmaf(wz.w, p[i].z, b.w)));
         }
       }
+  }
+}
+
+// W_p p + bias of a layer that reads the point, for a tile of one latent: two
+// float32 MFMAs per 32x32 tile instead of three fma per value and lane.  The
+// contraction runs over (bias, W_z, W_y, W_x) x (1, z, y, x), one product after
+// the other with one rounding each, so the values are those of
+// fma(W_x, x, fma(W_y, y, fma(W_z, z, bias))) bit for bit.
+// Layer 0 and the skip layer's start took 16 K of a 128-row bf16 tile's 160 K
+// cycles.  524,288 points of one latent: bf16 1235 -> 1195 us, split 3616 ->
+// 3578 us, the small decoder 102 -> 97 us.
+template <int P, int MTW, int NTW>
+__device__ __forceinline__ void acc_points(f32x16 (&acc)[MTW][NTW], const float* __restrict__ bias,
+                                           const float* __restrict__ wp, int wstride, const Sm<P>& s, int nt0, int mt0,
+                                           int lane) {
+  const int r = lane & 31, g = lane >> 5;
+  float a1[NTW], a2[NTW];
+#pragma unroll
+  for (int j = 0; j < NTW; ++j) {
+    const int n = (nt0 + j) * 32 + r;
+    a1[j] = g ? wp[2 * wstride + n] : bias[n];
+    a2[j] = wp[g ? n : wstride + n];
+  }
+  const f32x16 zero = {};
+#pragma unroll
+  for (int i = 0; i < MTW; ++i) {
+    const float4 p = s.pts[(mt0 + i) * 32 + r];
+    const float b1 = g ? p.z : 1.f, b2 = g ? p.x : p.y;
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) {
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[j], b1, zero, 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[j], b2, acc[i][j], 0, 0, 0);
+    }
+  }
+}
+
+// Layer 0 of a tile of one latent: acc_points, then ReLU (and mask bits) to LDS.
+template <int P, int NW, int MR, int MTW, int NTW, int WN, bool MASK>
+__device__ __forceinline__ void layer0_run(const NetDev& net, const float* bias0, const Sm<P>& s, const MaskRef& mk) {
+  const int t = opaque((int)threadIdx.x);
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  const int nw = wave % WN, mg = wave / WN;
+  const int nt0 = nw * NTW, mt0 = mg * MTW;
+  if (WN * (MR / 32 / MTW) < NW && mg > 0) return;
+  f32x16 acc[MTW][NTW];
+  acc_points<P, MTW, NTW>(acc, bias0, net.w0p, net.wpad[0], s, nt0, mt0, lane);
+  mfma_drain();
+  const int r = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < MTW; ++i) {
+    const int m = (mt0 + i) * 32 + r;
+    const int row = MASK ? mask_row(mk, s, m) : 0;
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) {
+      unsigned bits = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // the maximum before rounding and before the mask bit, as layer0_fill:
+        // a NaN becomes 0
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = fmaxf(acc[i][j][4 * q + e], 0.f);
+          if constexpr (MASK) bits |= pos_bit(v[e]) << (8 * q + e);
+        }
+        store4<P>(s, m, feat(nt0, j, q, g), g, v);
+      }
+      if constexpr (MASK) {
+        bits <<= 4 * g;
+        bits |= __shfl_xor(bits, 32);
+        if (g == 0 && row >= 0) mk.p[mask_at(mk, row, 0, nt0 + j)] = bits;
+      }
+    }
+  }
+}
+
+// 16-row float32 tile: one 16x16x4 MFMA per 16 outputs holds the whole sum.
+template <int NTW>
+__device__ __forceinline__ void acc_points_m16(f32x4 (&acc)[NTW], const float* __restrict__ bias,
+                                               const float* __restrict__ wp, int wstride, const Sm<0>& s, int nt0,
+                                               int lane) {
+  const int r = lane & 15, g4 = lane >> 4;
+  const float4 p = s.pts[r];
+  const float b = g4 == 0 ? 1.f : (g4 == 1 ? p.z : (g4 == 2 ? p.y : p.x));
+  const float* src = g4 == 0 ? bias : wp + (3 - g4) * wstride;
+  const f32x4 zero = {};
+#pragma unroll
+  for (int j = 0; j < NTW; ++j)
+    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(src[16 * (nt0 + j) + r], b, zero, 0, 0, 0);
+}
+
+template <int NTW>
+__device__ __forceinline__ void layer0_run_m16(const NetDev& net, const float* bias0, const Sm<0>& s) {
+  const int t = opaque((int)threadIdx.x);
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  f32x4 acc[NTW];
+  acc_points_m16<NTW>(acc, bias0, net.w0p, net.wpad[0], s, wave * NTW, lane);
+  mfma_drain();
+#pragma unroll
+  for (int j = 0; j < NTW; ++j) {
+    const float v[4] = {fmaxf(acc[j][0], 0.f), fmaxf(acc[j][1], 0.f), fmaxf(acc[j][2], 0.f), fmaxf(acc[j][3], 0.f)};
+    store4<0>(s, lane & 15, 16 * (wave * NTW + j) + 4 * (lane >> 4), 0, v);
+  }
+}
+
+// Layer 0 of a tile: on the matrix cores if its rows share a latent (ul >= 0).
+template <int P, int NW, int MR, bool MASK>
+__device__ __forceinline__ void layer0(const NetDev& net, const float* bias0_lat, const Sm<P>& s, int tid, int ul,
+                                       const MaskRef& mk) {
+  if (ul < 0) {
+    layer0_fill<P, NW * 64, MR, MASK>(net, bias0_lat, s, tid, mk);
+    return;
+  }
+  const int N = net.wpad[0];
+  const float* b = bias0_lat + (size_t)ul * N;
+  if constexpr (MR == 16) {
+    if (N == 512) layer0_run_m16<8>(net, b, s);
+    else if (N == 256) layer0_run_m16<4>(net, b, s);
+    else layer0_run_m16<2>(net, b, s);
+  } else {
+    constexpr int MT = MR / 32;
+    if constexpr (NW == 8) {
+      if (N == 512) layer0_run<P, NW, MR, MT, 2, 8, MASK>(net, b, s, mk);
+      else if (N == 256) layer0_run<P, NW, MR, MT, 1, 8, MASK>(net, b, s, mk);
+      else layer0_run<P, NW, MR, (MT > 1 ? MT / 2 : 1), 1, 4, MASK>(net, b, s, mk);
+    } else {
+      if (N == 512) layer0_run<P, NW, MR, MT, 4, 4, MASK>(net, b, s, mk);
+      else if (N == 256) layer0_run<P, NW, MR, MT, 2, 4, MASK>(net, b, s, mk);
+      else layer0_run<P, NW, MR, MT, 1, 4, MASK>(net, b, s, mk);
+    }
   }
 }
 
@@ -977,7 +1135,10 @@ __device__ __forceinline__ void layer_run(const NetDev& net, const EpCtx& ec, co
   if (on) {
     if constexpr (VJP && EARLY) load_masks();
     if constexpr (VJP) acc_mfma_start<P, MTW, NTW>(acc, nullptr, nt0, lane);
-    else if constexpr (SKIP) acc_bias<P, MTW, NTW, true>(acc, ec, s, nt0, mt0, lane);
+    else if constexpr (SKIP) {
+      if (ec.ul >= 0) acc_points<P, MTW, NTW>(acc, ec.biasS_lat + (size_t)ec.ul * ec.wpad, ec.wsp, ec.wpad, s, nt0, mt0, lane);
+      else acc_bias<P, MTW, NTW, true>(acc, ec, s, nt0, mt0, lane);
+    }
     else acc_mfma_start<P, MTW, NTW>(acc, net.bfrag[ec.layer], nt0, lane);
     if constexpr (P == 1) {
       gemm_bf16<MTW, NTW, 4>(acc, s, (const bf16x8*)wp, ksteps, nt0, mt0, lane, nbytes);
@@ -1077,6 +1238,8 @@ __device__ __forceinline__ void layer_run_m16(const NetDev& net, const EpCtx& ec
   const int nt0 = wave * NTW;
   const int r = lane & 15, g4 = lane >> 4;
   f32x4 acc[NTW];
+  if (SKIP && ec.ul >= 0) acc_points_m16<NTW>(acc, ec.biasS_lat + (size_t)ec.ul * ec.wpad, ec.wsp, ec.wpad, s, nt0, lane);
+  else
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
     const int n = 16 * (nt0 + j) + 4 * g4;
@@ -1182,16 +1345,20 @@ __device__ __forceinline__ EpCtx fwd_ctx(const NetDev& net, const float* biasS_l
 // and the output-layer seed for the adjoint; CAP keeps float32 copies of every
 // hidden activation in hcap (the capture from the tile's first row, chunk
 // rows capR) for the weight gradient.
-template <int P, int NW, int MR, bool ADJ, bool CAP, int NOUT = 1>
+// UNI: the tile may have one latent (set_latents was called).
+template <int P, int NW, int MR, bool ADJ, bool CAP, int NOUT = 1, bool UNI = true>
 __device__ __forceinline__ int mlp_forward(const NetDev& net, const float* bias0_lat, const float* biasS_lat,
                                            const Sm<P>& s, int tid, const MaskRef& mk, float* hcap = nullptr,
                                            int capR = 0) {
-  layer0_fill<P, NW * 64, MR, ADJ>(net, bias0_lat, s, tid, mk);
+  const int ul = UNI ? one_latent<P, MR>(s) : -1;
+  if constexpr (UNI) layer0<P, NW, MR, ADJ>(net, bias0_lat, s, tid, ul, mk);
+  else layer0_fill<P, NW * 64, MR, ADJ>(net, bias0_lat, s, tid, mk);
   __syncthreads();
   if constexpr (CAP) cap_tile<P>(s, 0, hcap, kCapBlock, net.wpad[0], nullptr);
   int wn = 4;
   for (int l = 1; l <= net.nl - 2; ++l) {
     EpCtx ec = fwd_ctx(net, biasS_lat, l);
+    ec.ul = ul;
     ec.mk = mk;
     if constexpr (CAP) {
       ec.hrow = cap_ptr<P>(hcap, (size_t)l * net.kmax * capR);
@@ -1232,7 +1399,8 @@ __device__ __forceinline__ int next_tile(int left) {
   else return left > 32 ? 64 : 32;
 }
 
-// Rows [first, last) of `count` that this workgroup owns.  The rows are dealt
+// Rows [first, last) of `count` (what full rounds of full tiles leave) that
+// this workgroup owns.  The rows are dealt
 // out in runs of the smallest tile, so that every workgroup has the same
 // number to one run; where the share leaves a rest that takes a full tile
 // anyway, in full tiles, so that some workgroups have none of the last round
@@ -1435,9 +1603,9 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
     live += fresh;
     if (live == 0) break;
     const int h = march_height<P>(live);
+    int lt = 0;
     if (tid < h) {
       float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-      int lt = 0;
       if (tid < live) {
         const float4 d = rw.dt[tid], c = rw.c[tid];
         p = make_float4(fmaf(d.w, d.x, c.x), fmaf(d.w, d.y, c.y), fmaf(d.w, d.z, c.z), 0.f);
@@ -1445,8 +1613,9 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
         if (!POOL && a.t_hist) a.t_hist[(size_t)rw.n[tid] * pl.cap + s.rid[tid]] = d.w;
       }
       s.pts[tid] = p;
-      s.lat[tid] = lt;
     }
+    if (h > 64) set_latents<P, M>(s, lt, tid < live);
+    else set_latents<P, 64>(s, lt, tid < live);
     __syncthreads();
     int wn;
     if (P == kPrecF32 && h == 16)
@@ -1482,21 +1651,27 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       const int max_steps = POOL ? im.max_steps : a.max_steps;
       if (POOL) K = im.K;
       float rec_abs[kMaxK];
-      for (int k = 0; k < K; ++k) {
-        rf[k] = rw.rf[k * M + tid];
-        rt[k] = rw.rt[k * M + tid];
+#pragma unroll
+      for (int k = 0; k < kMaxK; ++k) {
+        rf[k] = k < K ? rw.rf[k * M + tid] : INFINITY;
+        rt[k] = k < K ? rw.rt[k * M + tid] : 0.f;
         rec_abs[k] = fabsf(rf[k]);
       }
-      // running K smallest |f| (ties keep the earlier step)
+      // running K smallest |f| (ties keep the earlier step); the records past
+      // K are empty, so the rank among all of them is the rank among K
       const float af = fabsf(f);
-      const int pos = topk_rank(af, rec_abs, K);
-      for (int k = K - 1; k > pos; --k) {
-        rf[k] = rf[k - 1];
-        rt[k] = rt[k - 1];
-      }
+      const int pos = topk_rank(af, rec_abs, kMaxK);
       if (pos < K) {
-        rf[pos] = f;
-        rt[pos] = d.w;
+#pragma unroll
+        for (int k = kMaxK - 1; k >= 0; --k) {
+          if (k > pos) {
+            rf[k] = rf[k > 0 ? k - 1 : 0];
+            rt[k] = rt[k > 0 ? k - 1 : 0];
+          } else if (k == pos) {
+            rf[k] = f;
+            rt[k] = d.w;
+          }
+        }
         const unsigned keep = (1u << (8 * pos)) - 1u;      // steps of the records before pos stay, the others move up
         rn = (rn & keep) | ((rn & ~keep) << 8) | ((unsigned)n << (8 * pos));
       }
@@ -1523,11 +1698,13 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
         pl.st[r] = st;
         pl.n[r] = (uint8_t)n;
         pl.flast[r] = !POOL && a.mark_long && st == ST_ACTIVE ? graze(fp.x, fp.y, f, a.alpha) : f;
-        for (int k = 0; k < K; ++k) {
-          pl.rec_f[(size_t)k * pl.cap + r] = rf[k];
-          pl.rec_t[(size_t)k * pl.cap + r] = rt[k];
-          pl.rec_n[(size_t)k * pl.cap + r] = (uint8_t)(rn >> (8 * k));
-        }
+#pragma unroll
+        for (int k = 0; k < kMaxK; ++k)
+          if (k < K) {
+            pl.rec_f[(size_t)k * pl.cap + r] = rf[k];
+            pl.rec_t[(size_t)k * pl.cap + r] = rt[k];
+            pl.rec_n[(size_t)k * pl.cap + r] = (uint8_t)(rn >> (8 * k));
+          }
       }
     }
     // a stopped ray's queries, one atomic per distinct image in a wave
@@ -1565,10 +1742,12 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
       rw.start[pos] = start;
       rw.rn[pos] = rn;
       if (!POOL && a.mark_long) rw.fp[pos] = make_float2(fp.y, f);
-      for (int k = 0; k < K; ++k) {
-        rw.rf[k * M + pos] = rf[k];
-        rw.rt[k * M + pos] = rt[k];
-      }
+#pragma unroll
+      for (int k = 0; k < kMaxK; ++k)
+        if (k < K) {
+          rw.rf[k * M + pos] = rf[k];
+          rw.rt[k * M + pos] = rt[k];
+        }
       s.rid[pos] = r;
     }
     live = tot;
@@ -1580,7 +1759,7 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
 // ---------------------------------------------------------------------------
 // Plain decoder queries (explicit points, or the 6-point normal stencil)
 // ---------------------------------------------------------------------------
-template <int P, int M>
+template <int P, int M, bool UNI>
 __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, long long base, int k) {
   const int tid = threadIdx.x;
   // stencil queries may keep their ReLU masks for the backward (the host
@@ -1588,10 +1767,11 @@ __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, lon
   const bool keep = P != kPrecBF16 && M > 16 && a.mode == 1 && a.mask_out != nullptr;
   const int ntmax = a.net.kmax / 32;
   const MaskRef mk{a.mask_out, (a.net.nl - 1) * ntmax, ntmax, true};
+  int lt = 0;
   if (tid < M) {
     const long long idx = base + tid;
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-    int lt = 0, row = -1;
+    int row = -1;
     if (tid < k) {
       row = (int)min(idx, (long long)INT_MAX);
       if (a.mode == 0) {
@@ -1611,16 +1791,17 @@ __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, lon
       }
     }
     s.pts[tid] = p;
-    s.lat[tid] = lt;
     s.rid[tid] = row;
   }
+  if constexpr (UNI) set_latents<P, M>(s, lt, tid < k);
+  else if (tid < M) s.lat[tid] = lt;
   __syncthreads();
   int wn;
   if constexpr (P != kPrecBF16 && M > 16)
-    wn = keep ? mlp_forward<P, kFwdWaves<P>, M, true, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, mk)
-              : mlp_forward<P, kFwdWaves<P>, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+    wn = keep ? mlp_forward<P, kFwdWaves<P>, M, true, false, 1, UNI>(a.net, a.bias0_lat, a.biasS_lat, s, tid, mk)
+              : mlp_forward<P, kFwdWaves<P>, M, false, false, 1, UNI>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
   else
-    wn = mlp_forward<P, kFwdWaves<P>, M, false, false>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
+    wn = mlp_forward<P, kFwdWaves<P>, M, false, false, 1, UNI>(a.net, a.bias0_lat, a.biasS_lat, s, tid, MaskRef{});
   if (tid < M && s.rid[tid] >= 0) {
     float m = a.net.blast;
     for (int w = 0; w < wn; ++w) m += s.part[w * M + tid];
@@ -1633,21 +1814,30 @@ __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, lon
   __syncthreads();
 }
 
-template <int P>
+// UNI: tiles of one latent are looked for (one latent in all, or the stencil of
+// hits, which come image by image).  Points of several latents come in any
+// order, and their kernel is spared the second form of layer 0 (small decoder,
+// 524,288 points of three latents: 102 against 108 us).
+template <int P, bool UNI>
 __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_eval(EvalArgs a) {
+  constexpr int M = Cfg<P>::M;
   Sm<P> s(dyn_smem, a.net.kmax);
   const long long count = a.mode == 0 ? a.n : 6ll * (long long)(*a.hit_count);
+  const long long round = (long long)M * gridDim.x, full = count / round * round;
+  for (long long base = (long long)blockIdx.x * M; base < full; base += round) eval_tile<P, M, UNI>(a, s, base, M);
   long long base, last;
-  row_share<P>(count, base, last);
+  row_share<P>(count - full, base, last);
+  base += full;
+  last += full;
   while (base < last) {
-    const int left = (int)min(last - base, (long long)Cfg<P>::M);
+    const int left = (int)min(last - base, (long long)M);
     int m = next_tile<P>(left);
     if (m == 16 && a.mode == 1) m = 32;               // the masks of a stencil query need whole words
     const int k = min(left, m);
-    if (P == kPrecF32 && m == 16) eval_tile<P, P == kPrecF32 ? 16 : 32>(a, s, base, k);
-    else if (m == 32) eval_tile<P, 32>(a, s, base, k);
-    else if (P == kPrecBF16 && m == 64) eval_tile<P, 64>(a, s, base, k);
-    else eval_tile<P, Cfg<P>::M>(a, s, base, k);
+    if (P == kPrecF32 && m == 16) eval_tile<P, P == kPrecF32 ? 16 : 32, UNI>(a, s, base, k);
+    else if (m == 32) eval_tile<P, 32, UNI>(a, s, base, k);
+    else if (P == kPrecBF16 && m == 64) eval_tile<P, 64, UNI>(a, s, base, k);
+    else eval_tile<P, M, UNI>(a, s, base, k);
     base += k;
   }
 }
@@ -1707,13 +1897,15 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     const size_t row0 = theta ? (size_t)(tile - a.tile_begin) * M : 0;   // first row in the chunk
     const size_t blk0 = row0 * net.kmax;                                  // the tile's capture block
     float* hcap = theta ? cap_ptr<P>(a.hbuf, blk0) : nullptr;
+    int lt = 0;
     if (tid < M) {
       const int idx = tile * M + tid;
       const float4 smp = a.samples[idx];
       s.pts[tid] = make_float4(smp.x, smp.y, smp.z, 0.f);
       s.fval[tid] = smp.w;
-      s.lat[tid] = a.sample_lat[idx];
+      lt = a.sample_lat[idx];
     }
+    set_latents<P, M>(s, lt, tid < M);
     __syncthreads();
     const int wn = theta ? mlp_forward<P, kAdjWaves, Cfg<P>::M, true, true>(net, a.bias0_lat, a.biasS_lat, s, tid, mk, hcap,
                                                                             rstride)
@@ -1795,10 +1987,11 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
   const int tid = threadIdx.x;
   const int count = *a.count;
   for (int tile = blockIdx.x; tile * M < count; tile += gridDim.x) {
+    int lt = 0;
     if (tid < M) {
       const int idx = tile * M + tid;
       float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-      int lt = 0, r = -1;
+      int r = -1;
       if (idx < count) {
         r = a.list[idx];
         const ImgDesc& im = a.imgs[a.pool.img[r]];
@@ -1808,9 +2001,9 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
         lt = im.latent;
       }
       s.pts[tid] = p;
-      s.lat[tid] = lt;
       s.rid[tid] = r;
     }
+    set_latents<P, M>(s, lt, tid < M && tile * M + tid < count);
     __syncthreads();
     const int wn = mlp_forward<P, kFwdWaves<P>, M, false, false, 3>(a.net, a.bias0_lat, a.biasS_lat, s, tid,
                                                                       MaskRef{});
@@ -1846,11 +2039,13 @@ __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(
   const MaskRef mk{a.mask_ws + (size_t)blockIdx.x * (size_t)(net.nl) * M * ntmax, ntmax, M * ntmax, false};
   const int ll = net.nl - 2, W = net.wpad[ll], q4 = W / 4;
   for (int tile = blockIdx.x; tile * M < count; tile += gridDim.x) {
+    int lt = 0;
     if (tid < M) {
       const float4 smp = a.samples[tile * M + tid];
       s.pts[tid] = make_float4(smp.x, smp.y, smp.z, 0.f);
-      s.lat[tid] = a.sample_lat[tile * M + tid];
+      lt = a.sample_lat[tile * M + tid];
     }
+    set_latents<P, M>(s, lt, tid < M);
     __syncthreads();
     const int wn = mlp_forward<P, kBwdWaves, M, true, false, 3>(net, a.bias0_lat, a.biasS_lat, s, tid, mk);
     if (tid < M) {
@@ -2221,8 +2416,10 @@ static hipError_t setup_p(int bytes) {
   hipError_t e = hipFuncSetAttribute((const void*)k_march_run<P, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      bytes + (int)march_row_bytes() * Cfg<P>::M);
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void*)k_eval<P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e != hipSuccess) return e;
+  for (const void* f : {(const void*)k_eval<P, false>, (const void*)k_eval<P, true>}) {
+    e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+  }
   e = hipFuncSetAttribute((const void*)k_vjp_saved<P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess || P == kPrecBF16) return e;          // the recompute has no bf16 kernel
   return hipFuncSetAttribute((const void*)k_adjoint<P == kPrecBF16 ? kPrecSplit : P>,
@@ -2251,15 +2448,6 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
   if (precision == 2) return setup_p<2>(bytes);
   return setup_p<0>(bytes);
 }
-
-#define DIST_DISPATCH(KERNEL, ARGS)                                                                    \
-  do {                                                                                                 \
-    const size_t sm = mlp_smem_bytes(precision, ARGS.net);                                             \
-    const dim3 blk(fwd_threads(precision));                                                            \
-    if (precision == 1) hipLaunchKernelGGL(KERNEL<1>, dim3(grid), blk, sm, st, ARGS);                  \
-    else if (precision == 2) hipLaunchKernelGGL(KERNEL<2>, dim3(grid), blk, sm, st, ARGS);             \
-    else hipLaunchKernelGGL(KERNEL<0>, dim3(grid), blk, sm, st, ARGS);                                 \
-  } while (0)
 
 // the recompute-and-VJP kernel exists in split and float32 precision only
 #define DIST_DISPATCH_BWD(KERNEL, ARGS)                                                                \
@@ -2291,7 +2479,18 @@ void launch_color_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t
   if (precision == 2) hipLaunchKernelGGL(k_color_adjoint<2>, dim3(grid), dim3(kBwdWaves * 64), sm, st, a);
   else if (precision == 0) hipLaunchKernelGGL(k_color_adjoint<0>, dim3(grid), dim3(kBwdWaves * 64), sm, st, a);
 }
-void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) { DIST_DISPATCH(k_eval, a); }
+template <int P>
+static void launch_eval_p(const EvalArgs& a, int grid, hipStream_t st) {
+  const size_t sm = mlp_smem_bytes(P, a.net);
+  const dim3 blk(fwd_threads(P));
+  if (a.mode == 0 && a.n_lat > 1) hipLaunchKernelGGL((k_eval<P, false>), dim3(grid), blk, sm, st, a);
+  else hipLaunchKernelGGL((k_eval<P, true>), dim3(grid), blk, sm, st, a);
+}
+void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) {
+  if (precision == 1) launch_eval_p<1>(a, grid, st);
+  else if (precision == 2) launch_eval_p<2>(a, grid, st);
+  else launch_eval_p<0>(a, grid, st);
+}
 void launch_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t st) { DIST_DISPATCH_BWD(k_adjoint, a); }
 static_assert(kAdjWaves * 64 == 512, "the recompute-and-VJP dispatch assumes 8 waves");
 int mlp_row_groups(int waves, int width) { return (waves == 8 && width <= 128) ? 2 : 1; }

@@ -165,3 +165,28 @@ def test_unrolled_gradient_step_by_step_and_in_groups(prec):
         ctx.close()
     assert used[1] <= 24 << 20 < used[0]        # the second did run without the group's rows
     assert (grads[0] - grads[1]).norm() <= 64 * 2.0 ** -23 * grads[0].norm()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["fp32", "bf16", "split"])
+@pytest.mark.parametrize("name", list(SPECS))
+def test_tiles_of_one_latent_and_of_several(name, prec):
+    """Layer 0 and the skip layer start on the matrix cores in a tile of one
+    latent and on the vector units in a mixed one: the same bits either way, a
+    latent that is not a number included (the ReLU of layer 0 makes it 0)."""
+    from paper_1911_13225_amd import api
+    ctx, _ = ctx_for(name)
+    n = 256 * 128 + 70
+    P = torch.tensor(np.random.Generator(np.random.PCG64(12)).uniform(-0.7, 0.7, (n, 3)).astype(np.float32),
+                     device="cuda")
+    Z = torch.tensor(di.make_latents(2, SPECS[name].latent_dim, sigma=0.1), device="cuda")
+    Z[1] = Z[0]
+    one = torch.zeros(n, device="cuda", dtype=torch.int32)
+    two = (torch.arange(n, device="cuda") % 2).to(torch.int32)
+    for k in (n, 33, 5):
+        a = api.dist_sdf_eval(ctx, P[:k].contiguous(), one[:k].contiguous(), Z[:1].contiguous(), prec)
+        b = api.dist_sdf_eval(ctx, P[:k].contiguous(), two[:k].contiguous(), Z, prec)
+        assert torch.equal(a, b), k
+    Z[:, 0] = float("nan")
+    a = api.dist_sdf_eval(ctx, P, one, Z[:1].contiguous(), prec)
+    b = api.dist_sdf_eval(ctx, P, two, Z, prec)
+    assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(a.nan_to_num(), b.nan_to_num())
