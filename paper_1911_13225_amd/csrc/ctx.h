@@ -100,10 +100,11 @@ struct Workspace {
   size_t bytes = 0;
   int cap_rays = 0, cap_pix = 0, cap_img = 0, cap_lat = 0, cap_steps = 0;
   dist::RayPool pool{};
+  char* stage = nullptr;            // descriptors, image order, latents, views (one copy)
   dist::ImgDesc* imgs = nullptr;
-  int* imgs_list = nullptr;
   int* img_order = nullptr;
   int* img_latent = nullptr;
+  int* img_view = nullptr;
   int* list[2] = {nullptr, nullptr};
   int* counters = nullptr;
   unsigned long long* qcount = nullptr;
@@ -113,14 +114,12 @@ struct Workspace {
   float* fv = nullptr;
   float4* nraw = nullptr;
   int* hit_pix = nullptr;
-  int* img_view = nullptr;
   NrmSave* ns = nullptr;
   CamSpace* cs = nullptr;
   UnrollSpace* us = nullptr;
   UlRows* ur = nullptr;
   // pinned staging of the per-call descriptors
-  dist::ImgDesc* h_imgs = nullptr;
-  int* h_ints = nullptr;
+  char* h_stage = nullptr;
   hipEvent_t staged = nullptr;
   bool staged_pending = false;
   BwdSpace* bw = nullptr;
@@ -228,6 +227,6 @@ int fold_biases(dist_ctx* ctx, Workspace* w, const float* z, int n_lat, hipStrea
 int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_params* prm, hipStream_t st,
               float* t_hist = nullptr);
 int run_finalize(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_params* prm, float* depth,
-                 float* dist, float* normal, float* sil, uint8_t* status, uint8_t* nsteps, hipStream_t st,
-                 bool keep_masks = false);
+                 float* dist, float* normal, float* sil, uint8_t* status, uint8_t* nsteps, int64_t* queries,
+                 hipStream_t st, bool keep_masks = false);
 void ws_put(dist_ctx* ctx, Workspace* w);

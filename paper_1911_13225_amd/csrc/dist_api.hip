@@ -406,6 +406,8 @@ struct Carver {
   }
 };
 
+static size_t stage_bytes(int n_img) { return (sizeof(ImgDesc) + 3 * sizeof(int)) * (size_t)n_img; }
+
 static void ws_layout(Workspace& w, Carver& c) {
   const size_t cap = w.cap_rays;
   w.pool.d = c.take<float4>(cap);
@@ -418,21 +420,19 @@ static void ws_layout(Workspace& w, Carver& c) {
   w.pool.rec_t = c.take<float>(cap * kMaxK);
   w.pool.rec_n = c.take<uint8_t>(cap * kMaxK);
   w.pool.cap = (int)cap;
-  w.imgs = c.take<ImgDesc>(w.cap_img);
-  w.imgs_list = c.take<int>(w.cap_img);
-  w.img_order = c.take<int>(w.cap_img);
-  w.img_latent = c.take<int>(w.cap_img);
+  // descriptors and index arrays, staged by one copy (see stage_images)
+  w.stage = c.take<char>(stage_bytes(w.cap_img));
   w.list[0] = c.take<int>(cap);
   w.list[1] = c.take<int>(cap);
-  w.counters = c.take<int>(w.cap_steps + 8);
-  w.qcount = c.take<unsigned long long>(w.cap_img);
+  // zeroed together at the start of a render
+  w.qcount = c.take<unsigned long long>(w.cap_img + (w.cap_steps + 8 + 1) / 2);
+  w.counters = (int*)(w.qcount + w.cap_img);
   w.bias0_lat = c.take<float>((size_t)w.cap_lat * kMaxWidth);
   w.biasS_lat = c.take<float>((size_t)w.cap_lat * kMaxWidth);
   w.hits = c.take<int>(w.cap_pix);
   w.fv = c.take<float>((size_t)w.cap_pix * 6);
   w.nraw = c.take<float4>(w.cap_pix);
   w.hit_pix = c.take<int>(w.cap_pix);
-  w.img_view = c.take<int>(w.cap_img);
 }
 
 static void bw_layout(BwdSpace& w, Carver& c) {
@@ -488,8 +488,7 @@ static int ws_get(dist_ctx* ctx, int cap_rays, int cap_pix, int cap_img, int cap
   c.base = w->mem;
   c.off = 0;
   ws_layout(*w, c);
-  if (hipHostMalloc((void**)&w->h_imgs, sizeof(ImgDesc) * cap_img) != hipSuccess ||
-      hipHostMalloc((void**)&w->h_ints, sizeof(int) * 4 * cap_img) != hipSuccess ||
+  if (hipHostMalloc((void**)&w->h_stage, stage_bytes(cap_img)) != hipSuccess ||
       hipEventCreateWithFlags(&w->staged, hipEventDisableTiming) != hipSuccess) {
     ctx_free(ctx, w->mem, w->bytes);
     delete w;
@@ -508,8 +507,7 @@ void ws_put(dist_ctx* ctx, Workspace* w) {
 static void ws_destroy(dist_ctx* ctx, Workspace* w) {
   if (w->staged_pending) (void)hipEventSynchronize(w->staged);
   (void)hipEventDestroy(w->staged);
-  (void)hipHostFree(w->h_imgs);
-  (void)hipHostFree(w->h_ints);
+  (void)hipHostFree(w->h_stage);
   ctx_free(ctx, w->mem, w->bytes);
   if (w->bw) {
     ctx_free(ctx, w->bw->mem, w->bw->bytes);
@@ -715,7 +713,7 @@ static void fill_desc(ImgDesc& d, const dist_camera& c, const dist_trace_params*
   for (int i = 0; i < 3; ++i) d.c[i] = c.c[i];
   d.alpha = p->alpha; d.eps = p->eps; d.near_ = p->near_; d.far_ = p->far_;
   d.H = c.H; d.W = c.W; d.levels = p->c2f_levels; d.latent = latent;
-  d.max_steps = p->max_steps; d.K = p->k_samples; d.cur_level = p->c2f_levels;
+  d.max_steps = p->max_steps; d.K = p->k_samples;
   d.slot_base = slot_base;
   const int hw = c.H * c.W;
   d.lvl_off[0] = 0;
@@ -740,23 +738,22 @@ int slots_per_image(int hw, int levels) {
   return std::max(s, hw + hw / 4 + (levels >= 2 ? hw / 16 : 0));
 }
 
-// Stage image descriptors and the per-image index arrays (pinned -> device).
+// Stage image descriptors and the per-image index arrays (pinned -> device) in
+// one copy.
 static int stage_images(Workspace* w, const std::vector<ImgDesc>& d, const std::vector<int>& order,
                         const std::vector<int>& lat, const std::vector<int>& view, hipStream_t st) {
   if (w->staged_pending) HIPCHK(hipEventSynchronize(w->staged));
-  const int n = (int)d.size();
-  memcpy(w->h_imgs, d.data(), sizeof(ImgDesc) * n);
-  for (int i = 0; i < n; ++i) {
-    w->h_ints[i] = i;
-    w->h_ints[n + i] = order[i];
-    w->h_ints[2 * n + i] = lat[i];
-    w->h_ints[3 * n + i] = view[i];
-  }
-  HIPCHK(hipMemcpyAsync(w->img_view, w->h_ints + 3 * n, sizeof(int) * n, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(w->imgs, w->h_imgs, sizeof(ImgDesc) * n, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(w->imgs_list, w->h_ints, sizeof(int) * n, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(w->img_order, w->h_ints + n, sizeof(int) * n, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(w->img_latent, w->h_ints + 2 * n, sizeof(int) * n, hipMemcpyHostToDevice, st));
+  const size_t n = d.size();
+  w->imgs = (ImgDesc*)w->stage;
+  w->img_order = (int*)(w->imgs + n);
+  w->img_latent = w->img_order + n;
+  w->img_view = w->img_latent + n;
+  memcpy(w->h_stage, d.data(), sizeof(ImgDesc) * n);
+  int* ints = (int*)(w->h_stage + sizeof(ImgDesc) * n);
+  memcpy(ints, order.data(), sizeof(int) * n);
+  memcpy(ints + n, lat.data(), sizeof(int) * n);
+  memcpy(ints + 2 * n, view.data(), sizeof(int) * n);
+  HIPCHK(hipMemcpyAsync(w->stage, w->h_stage, stage_bytes((int)n), hipMemcpyHostToDevice, st));
   HIPCHK(hipEventRecord(w->staged, st));
   w->staged_pending = true;
   return DIST_OK;
@@ -792,16 +789,16 @@ static int eval_grid(dist_ctx* ctx, long long rows, int prec) {
 int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_params* prm, hipStream_t st,
               float* t_hist) {
   const int L = prm->c2f_levels, prec = prm->precision;
-  launch_fill_i32(w->counters, 0, prm->max_steps + 8, st);
-  launch_fill_u64(w->qcount, n_img, st);
-  launch_init_level(w->pool, w->imgs, w->imgs_list, n_img, hw >> (2 * L), w->list[0], w->counters, st);
+  // the counters and, before them, the images' query counts (one run of memory)
+  launch_fill_i32((int*)(w->qcount + w->cap_img - n_img), 0, 2 * n_img + prm->max_steps + 8, st);
+  launch_init_level(w->pool, w->imgs, n_img, hw >> (2 * L), w->list[0], w->counters, st);
   MarchArgs ma{};
   ma.net = ctx->net[prec];
   ma.pool = w->pool;
   ma.imgs = w->imgs;
   ma.bias0_lat = w->bias0_lat;
   ma.biasS_lat = w->biasS_lat;
-  ma.qcount = w->qcount;
+  ma.qcount = w->qcount + w->cap_img - n_img;
   ma.t_hist = t_hist;
   ma.max_steps = prm->max_steps;
   ma.K = prm->k_samples;
@@ -829,7 +826,7 @@ int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_p
       launch_march_run(prec, ma, eval_grid(ctx, (long long)n_img * (hw >> (2 * lv)), prec), st);
     }
     if (lv > 0)
-      launch_split(w->pool, w->imgs, w->imgs_list, n_img, hw >> (2 * (lv - 1)), lv - 1, 3 * (i + 1),
+      launch_split(w->pool, w->imgs, n_img, hw >> (2 * (lv - 1)), lv - 1, 3 * (i + 1),
                    w->list[(i + 1) & 1], w->counters + i + 1, st, lv == 1 ? tail_cnt : nullptr, w->pool.cap);
   }
   HIPCHK(hipGetLastError());
@@ -838,8 +835,8 @@ int run_trace(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_p
 
 // Finalise outputs and compute normals with float32 queries.
 int run_finalize(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trace_params* prm, float* depth,
-                 float* dist, float* normal, float* sil, uint8_t* status, uint8_t* nsteps, hipStream_t st,
-                 bool keep_masks) {
+                 float* dist, float* normal, float* sil, uint8_t* status, uint8_t* nsteps, int64_t* queries,
+                 hipStream_t st, bool keep_masks) {
   FinalizeOut fo{};
   fo.depth = depth;
   fo.dist = dist;
@@ -852,8 +849,9 @@ int run_finalize(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trac
   fo.hit_count = w->counters + prm->max_steps + 4;
   fo.want_hits = prm->want_normals ? 1 : 0;
   fo.hit_pix = keep_masks ? w->hit_pix : nullptr;
-  launch_fill_i32(fo.hit_count, 0, 1, st);
-  launch_finalize(w->pool, w->imgs, nullptr, n_img, hw, fo, st);
+  fo.qcount = w->qcount + w->cap_img - n_img;
+  fo.queries = queries;
+  launch_finalize(w->pool, w->imgs, nullptr, n_img, hw, fo, st);        // (the hit count is zero since run_trace)
   if (prm->want_normals) {
     // normal queries: float32, or split bf16 (float32-class accuracy) on the bf16 paths
     const int np = prm->precision == DIST_FP32 ? kPrecF32 : kPrecSplit;
@@ -881,11 +879,6 @@ int run_finalize(dist_ctx* ctx, Workspace* w, int n_img, int hw, const dist_trac
   }
   HIPCHK(hipGetLastError());
   return DIST_OK;
-}
-
-__global__ void k_u64_to_i64(const unsigned long long* a, int64_t* b, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = (int64_t)a[i];
 }
 
 extern "C" int dist_render_fwd(dist_ctx* ctx, const dist_camera* cams, int32_t n_views, const float* z,
@@ -940,8 +933,7 @@ extern "C" int dist_render_fwd(dist_ctx* ctx, const dist_camera* cams, int32_t n
   const bool hist = saved && prm->keep_history;
   if (!rc && hist) rc = us_get(ctx, w, w->pool.cap, prm->max_steps);
   if (!rc) rc = run_trace(ctx, w, n_img, hw, prm, st, hist ? w->us->t_hist : nullptr);
-  if (!rc) rc = run_finalize(ctx, w, n_img, hw, prm, depth, dist, normal, sil, status, nsteps, st, keep);
-  if (!rc && queries) hipLaunchKernelGGL(k_u64_to_i64, dim3((n_img + 255) / 256), dim3(256), 0, st, w->qcount, queries, n_img);
+  if (!rc) rc = run_finalize(ctx, w, n_img, hw, prm, depth, dist, normal, sil, status, nsteps, queries, st, keep);
   if (rc) {
     ws_put(ctx, w);
     return rc;
@@ -1667,7 +1659,7 @@ extern "C" int dist_render_color_bwd(dist_ctx* cctx, const dist_saved* geom, con
   fold_into(cctx, zc, n_latents, c->bias0, c->biasS, st);
   launch_color_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, hw, n_latents, tile, g_rgb, b->bsum,
                        b->boff, b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, c->cseed,
-                       b->sample_lat, std::min<long long>(cap, c->cap_seed), st);
+                       b->sample_lat, st);
   AdjArgs aa{};
   aa.net = cctx->net[prec];
   aa.bias0_lat = c->bias0;

@@ -30,7 +30,7 @@ struct ImgDesc {
   float c[3];                 // camera centre
   float alpha, eps, near_, far_;
   int H, W, levels, latent;
-  int max_steps, K, cur_level, slot_base;
+  int max_steps, K, slot_base;
   int lvl_off[3];             // slot offset of level 0, 1, 2 from slot_base
   int out_base;               // first output pixel of this image
 };

@@ -16,6 +16,8 @@ struct FinalizeOut {
   int* hit_count;
   int want_hits;
   int* hit_pix;      // per output pixel: its index in hits, -1 if none (or null)
+  const unsigned long long* qcount;   // per image in launch order: decoder queries, copied to
+  int64_t* queries;                   // this output (or null)
 };
 
 // One image that starts rays this tick: split into level `lvl` (split = 1) or
@@ -85,11 +87,10 @@ struct SplitList {
   int* sample_idx;
 };
 
-void launch_init_level(const RayPool& pl, ImgDesc* imgs, const int* imgs_list, int n_img, int max_rays, int* list,
-                       int* counter, hipStream_t s);
-void launch_split(const RayPool& pl, ImgDesc* imgs, const int* imgs_list, int n_img, int max_children,
-                  int child_lvl, int child_step, int* list, int* counter, hipStream_t s,
-                  int* counter_tail = nullptr, int tail_end = 0);
+void launch_init_level(const RayPool& pl, const ImgDesc* imgs, int n_img, int max_rays, int* list, int* counter,
+                       hipStream_t s);
+void launch_split(const RayPool& pl, const ImgDesc* imgs, int n_img, int max_children, int child_lvl, int child_step,
+                  int* list, int* counter, hipStream_t s, int* counter_tail = nullptr, int tail_end = 0);
 void launch_finalize(const RayPool& pl, const ImgDesc* imgs, const int* imgs_list, int n_img, int hw,
                      const FinalizeOut& o, hipStream_t s);
 void launch_normals(const RayPool& pl, const ImgDesc* imgs, const int* hits, const int* hit_count, int max_hits,
@@ -98,8 +99,6 @@ void launch_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order
                     int hw, int n_lat, int tile, const SeedIn& in, int* bsum, int* boff, int* seg_base,
                     int* seg_total, int* seg_padded, int* n_samples, float4* samples, int* sample_lat, hipStream_t s,
                     int lat_fixed = 0, const SplitList* split = nullptr, int4* sample_cam = nullptr);
-void launch_samples_pad(int n_lat, const int* seg_base, const int* seg_total, const int* seg_padded, float4* samples,
-                        int* sample_lat, hipStream_t s);
 void launch_gz_reduce(float* partial, int kmax, int tile, int max_tiles, const int* seg_base,
                       const int* seg_padded, int n_lat, int w0, int mg0, const float* W0z, int ws, int mgs,
                       const float* Wsz, int L, float* gz, hipStream_t s, int lat0 = 0, int accumulate = 0);
@@ -123,8 +122,7 @@ void launch_color_hits(const RayPool& pl, const ImgDesc* imgs, int n_img, int hw
 void launch_color_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent,
                           int n_img, int hw, int n_lat, int tile, const float* g_rgb, int* bsum, int* boff,
                           int* seg_base, int* seg_total, int* seg_padded, int* n_samples, float4* samples,
-                          float4* cseed, int* sample_lat, long long cap, hipStream_t s);
-void launch_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* hdr, int max_entries, hipStream_t s);
+                          float4* cseed, int* sample_lat, hipStream_t s);
 // The rays that start this tick (split children and (re)started images) join the list.
 void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
                     const int* hdr, int grid, hipStream_t s);

@@ -92,11 +92,11 @@ __device__ __forceinline__ void init_ray(const RayPool& pl, const ImgDesc& im, i
 
 // ---------------------------------------------------------------------------
 // Coarsest level: one ray per 2^L x 2^L block, starting at the sphere entry.
-// grid: (blocks over rays of the largest image, n_images in `imgs_list`)
+// grid: (blocks over rays of the largest image, n_images)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_init_level(RayPool pl, ImgDesc* imgs, const int* imgs_list,
-                                                    int* list, int* counter) {
-  const int img = imgs_list[blockIdx.y];
+__global__ __launch_bounds__(256) void k_init_level(RayPool pl, const ImgDesc* imgs, int* list,
+                                                    int* counter) {
+  const int img = blockIdx.y;
   const ImgDesc& im = imgs[img];
   const int lvl = im.levels;
   const int Wl = im.W >> lvl, Hl = im.H >> lvl;
@@ -113,7 +113,6 @@ __global__ __launch_bounds__(256) void k_init_level(RayPool pl, ImgDesc* imgs, c
     init_ray(pl, im, img, r, d, t_lo, t_lo, t_hi, inside, 0);
     act = inside;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) imgs[img].cur_level = lvl;
   block_append(act, r, list, counter);
 }
 
@@ -133,10 +132,10 @@ __global__ __launch_bounds__(256) void k_init_level(RayPool pl, ImgDesc* imgs, c
 // ---------------------------------------------------------------------------
 constexpr float kGraze = 0.02f;
 
-__global__ __launch_bounds__(1024) void k_split(RayPool pl, ImgDesc* imgs, const int* imgs_list, int child_lvl,
-                                               int child_step, int* list, int* counter, int* counter_tail,
+__global__ __launch_bounds__(1024) void k_split(RayPool pl, const ImgDesc* imgs, int child_lvl, int child_step,
+                                               int* list, int* counter, int* counter_tail,
                                                int tail_end) {
-  const int img = imgs_list[blockIdx.y];
+  const int img = blockIdx.y;
   const ImgDesc& im = imgs[img];
   const int Wl = im.W >> child_lvl, Hl = im.H >> child_lvl;
   const int Wp = im.W >> (child_lvl + 1);
@@ -165,11 +164,6 @@ __global__ __launch_bounds__(1024) void k_split(RayPool pl, ImgDesc* imgs, const
   } else {
     block_append<1024>(act, r, list, counter);
   }
-}
-
-__global__ void k_set_level(ImgDesc* imgs, const int* imgs_list, int n, int lvl) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) imgs[imgs_list[i]].cur_level = lvl;
 }
 
 // ---------------------------------------------------------------------------
@@ -216,6 +210,7 @@ __global__ __launch_bounds__(1024) void k_finalize(RayPool pl, const ImgDesc* im
     if (o.normal && !hit) { o.normal[3 * q] = 0.f; o.normal[3 * q + 1] = 0.f; o.normal[3 * q + 2] = 0.f; }
     if (o.nraw) o.nraw[q] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  if (o.queries && blockIdx.x == 0 && threadIdx.x == 0) o.queries[blockIdx.y] = (int64_t)o.qcount[blockIdx.y];
   const int h = block_append<1024>(hit && o.want_hits, r, o.hits, o.hit_count);
   if (o.hit_pix && pix < hw) o.hit_pix[(size_t)im.out_base + pix] = h;
 }
@@ -314,10 +309,20 @@ __global__ __launch_bounds__(256) void k_samples_count(RayPool pl, const ImgDesc
 // the padding at every latent segment so that each segment starts at a
 // multiple of the adjoint tile.  seg_* are indexed by latent id.  The list
 // starts at *pos0 (0 if null); n_out[0] receives its end, n_out[1] its length.
+// The padding samples at the end of a segment are written here: zero seed, the
+// segment's latent; stencil index 0 (split layout), a valid entry whose
+// contribution the zero seed cancels.
+struct PadOut {
+  float4* samples;
+  int* sample_lat;
+  int* sample_idx;                 // each of the last three may be null
+  int4* sample_cam;
+  float4* cseed;
+};
 __global__ __launch_bounds__(1024) void k_samples_scan(const int* bsum, int n_img, int bpi, const int* img_order,
                                                        const int* img_latent, int lat_fixed, int tile, int n_lat,
                                                        int* boff, int* seg_base, int* seg_total, int* seg_padded,
-                                                       const int* pos0, int* n_out) {
+                                                       const int* pos0, int* n_out, PadOut out) {
   __shared__ int buf[1024];
   __shared__ int carry_s;
   const int tid = threadIdx.x;
@@ -354,6 +359,13 @@ __global__ __launch_bounds__(1024) void k_samples_scan(const int* bsum, int n_im
     const int total = carry_s;
     const int padded = (total + tile - 1) / tile * tile;
     if (tid == 0) { seg_base[lat] = pos; seg_total[lat] = total; seg_padded[lat] = padded; }
+    for (int i = pos + total + tid; i < pos + padded; i += 1024) {
+      out.samples[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      out.sample_lat[i] = lat;
+      if (out.sample_idx) out.sample_idx[i] = 0;
+      if (out.sample_cam) out.sample_cam[i] = make_int4(-1, 0, 0, 0);
+      if (out.cseed) out.cseed[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     pos += padded;
     i0 = i1;
     __syncthreads();
@@ -468,21 +480,6 @@ __global__ __launch_bounds__(256) void k_samples_write(RayPool pl, const ImgDesc
       sample_lat[at] = im.latent;
       if (boff2) sample_idx[at] = 6 * h + j;
     }
-  }
-}
-
-// Padding samples (zero seed) at the end of each latent segment; their
-// stencil index (split layout) is 0, a valid entry whose contribution the zero
-// seed cancels.
-__global__ void k_samples_pad(const int* seg_base, const int* seg_total, const int* seg_padded, float4* samples,
-                              int* sample_lat, int* sample_idx, int4* sample_cam) {
-  const int l = blockIdx.x;
-  const int b = seg_base[l], t = seg_total[l], p = seg_padded[l];
-  for (int i = t + threadIdx.x; i < p; i += blockDim.x) {
-    samples[b + i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    sample_lat[b + i] = l;
-    if (sample_idx) sample_idx[b + i] = 0;
-    if (sample_cam) sample_cam[b + i] = make_int4(-1, 0, 0, 0);
   }
 }
 
@@ -696,12 +693,6 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
 // and the coarsest rays of newly (re)started images, join the pooled active
 // list behind the rays that the last march left active.
 // ---------------------------------------------------------------------------
-__global__ void k_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* hdr) {
-  const int n = hdr[0];
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    imgs[table[i].img].cur_level = table[i].lvl;
-}
-
 __global__ __launch_bounds__(256) void k_advance_new(RayPool pl, const ImgDesc* imgs, int* out_list, int* out_count,
                                                      const AdvEntry* table, const int* hdr) {
   const int n_tab = hdr[0], n_new = hdr[1];
@@ -1155,26 +1146,18 @@ __global__ __launch_bounds__(256) void k_color_write(RayPool pl, const ImgDesc* 
   sample_lat[o] = im.latent;
 }
 
-__global__ void k_fill_f4(float4* p, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
 static inline unsigned nblk(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
-void launch_init_level(const RayPool& pl, ImgDesc* imgs, const int* imgs_list, int n_img, int max_rays, int* list,
-                       int* counter, hipStream_t s) {
+void launch_init_level(const RayPool& pl, const ImgDesc* imgs, int n_img, int max_rays, int* list, int* counter,
+                       hipStream_t s) {
   if (n_img <= 0 || max_rays <= 0) return;
-  hipLaunchKernelGGL(k_init_level, dim3(nblk(max_rays, 256), n_img), dim3(256), 0, s, pl, imgs, imgs_list, list,
-                     counter);
+  hipLaunchKernelGGL(k_init_level, dim3(nblk(max_rays, 256), n_img), dim3(256), 0, s, pl, imgs, list, counter);
 }
-void launch_split(const RayPool& pl, ImgDesc* imgs, const int* imgs_list, int n_img, int max_children,
-                  int child_lvl, int child_step, int* list, int* counter, hipStream_t s, int* counter_tail,
-                  int tail_end) {
+void launch_split(const RayPool& pl, const ImgDesc* imgs, int n_img, int max_children, int child_lvl, int child_step,
+                  int* list, int* counter, hipStream_t s, int* counter_tail, int tail_end) {
   if (n_img <= 0 || max_children <= 0) return;
-  hipLaunchKernelGGL(k_split, dim3(nblk(max_children, 1024), n_img), dim3(1024), 0, s, pl, imgs, imgs_list,
-                     child_lvl, child_step, list, counter, counter_tail, tail_end);
-  hipLaunchKernelGGL(k_set_level, dim3(nblk(n_img, 256)), dim3(256), 0, s, imgs, imgs_list, n_img, child_lvl);
+  hipLaunchKernelGGL(k_split, dim3(nblk(max_children, 1024), n_img), dim3(1024), 0, s, pl, imgs, child_lvl, child_step,
+                     list, counter, counter_tail, tail_end);
 }
 void launch_finalize(const RayPool& pl, const ImgDesc* imgs, const int* imgs_list, int n_img, int hw,
                      const FinalizeOut& o, hipStream_t s) {
@@ -1195,23 +1178,14 @@ void launch_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order
   hipLaunchKernelGGL(k_samples_count, dim3(bpi, n_img), dim3(256), 0, s, pl, imgs, img_order, in, bsum,
                      split ? sl->bsum : nullptr);
   hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, bsum, n_img, bpi, img_order, img_latent, lat_fixed,
-                     tile, n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples);
+                     tile, n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples,
+                     PadOut{samples, sample_lat, nullptr, sample_cam, nullptr});
   if (split)
     hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, sl->bsum, n_img, bpi, img_order, img_latent,
                        lat_fixed, tile, n_lat, sl->boff, sl->seg_base, sl->seg_total, sl->seg_padded, n_samples,
-                       n_samples + 2);
+                       n_samples + 2, PadOut{samples, sample_lat, sl->sample_idx, nullptr, nullptr});
   hipLaunchKernelGGL(k_samples_write, dim3(bpi, n_img), dim3(256), 0, s, pl, imgs, img_order, in, boff,
                      split ? sl->boff : nullptr, samples, sample_lat, split ? sl->sample_idx : nullptr, sample_cam);
-  hipLaunchKernelGGL(k_samples_pad, dim3(n_lat), dim3(256), 0, s, seg_base, seg_total, seg_padded, samples,
-                     sample_lat, nullptr, sample_cam);
-  if (split)
-    hipLaunchKernelGGL(k_samples_pad, dim3(n_lat), dim3(256), 0, s, sl->seg_base, sl->seg_total, sl->seg_padded,
-                       samples, sample_lat, sl->sample_idx, nullptr);
-}
-void launch_samples_pad(int n_lat, const int* seg_base, const int* seg_total, const int* seg_padded, float4* samples,
-                        int* sample_lat, hipStream_t s) {
-  hipLaunchKernelGGL(k_samples_pad, dim3(n_lat), dim3(256), 0, s, seg_base, seg_total, seg_padded, samples,
-                     sample_lat, nullptr, nullptr);
 }
 // grad_p f . v at each hit's Eq. 1 point (unit seeds): the adjoint's per-wave
 // partials plus the residual term 0.5 p / |p|; 0 where the ray grazes the
@@ -1260,10 +1234,6 @@ void launch_gz_reduce(float* partial, int kmax, int tile, int max_tiles, const i
   hipLaunchKernelGGL(k_gz_reduce, dim3(n_lat), dim3(1024), 0, s, partial, kmax, tile, seg_base, seg_padded, w0, mg0,
                      W0z, ws, mgs, Wsz, L, gz, lat0, accumulate);
 }
-void launch_apply_levels(ImgDesc* imgs, const AdvEntry* table, const int* hdr, int max_entries, hipStream_t s) {
-  hipLaunchKernelGGL(k_apply_levels, dim3(nblk(max_entries > 0 ? max_entries : 1, 256)), dim3(256), 0, s, imgs, table,
-                     hdr);
-}
 void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
                     const int* hdr, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_advance_new, dim3(grid), dim3(256), 0, s, pl, imgs, list, count, table, hdr);
@@ -1293,11 +1263,10 @@ void launch_ul_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_or
   const int bpl = (int)nblk(nr, 256);
   hipLaunchKernelGGL(k_ul_count, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, bsum);
   hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, bsum, n_img, bpl, img_order, img_latent, 0, tile,
-                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples);
+                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples,
+                     PadOut{samples, sample_lat, nullptr, sample_cam, nullptr});
   hipLaunchKernelGGL(k_ul_write, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, boff, samples,
                      sample_lat, sample_cam);
-  hipLaunchKernelGGL(k_samples_pad, dim3(n_lat), dim3(256), 0, s, seg_base, seg_total, seg_padded, samples,
-                     sample_lat, nullptr, sample_cam);
 }
 void launch_ul_lambda(const RayPool& pl, const float4* samples, const int4* sample_cam, const float* gp_part,
                       const int* n_samples, int max_samples, float* lam, hipStream_t s) {
@@ -1312,11 +1281,10 @@ void launch_ulg_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_o
   const int bpl = (int)nblk(nr, 256);
   hipLaunchKernelGGL(k_ulg_count, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, bsum);
   hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, bsum, n_img, bpl, img_order, img_latent, 0, tile,
-                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples);
+                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples,
+                     PadOut{samples, sample_lat, nullptr, nullptr, nullptr});
   hipLaunchKernelGGL(k_ulg_write, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, boff, samples,
                      sample_lat);
-  hipLaunchKernelGGL(k_samples_pad, dim3(n_lat), dim3(256), 0, s, seg_base, seg_total, seg_padded, samples,
-                     sample_lat, nullptr, nullptr);
 }
 void launch_ulg_lambda(const RayPool& pl, const ImgDesc* imgs, const int* img_order, int n_img, int nr,
                        const UlGroup& in, const int* boff, const float4* samples, const float* gp_part, float* gm,
@@ -1341,16 +1309,14 @@ void launch_color_hits(const RayPool& pl, const ImgDesc* imgs, int n_img, int hw
 void launch_color_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent,
                           int n_img, int hw, int n_lat, int tile, const float* g_rgb, int* bsum, int* boff,
                           int* seg_base, int* seg_total, int* seg_padded, int* n_samples, float4* samples,
-                          float4* cseed, int* sample_lat, long long cap, hipStream_t s) {
+                          float4* cseed, int* sample_lat, hipStream_t s) {
   const int bpi = (int)nblk(hw, 256);
-  hipLaunchKernelGGL(k_fill_f4, dim3(256), dim3(256), 0, s, cseed, cap);
   hipLaunchKernelGGL(k_color_count, dim3(bpi, n_img), dim3(256), 0, s, pl, imgs, img_order, g_rgb, bsum);
   hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, bsum, n_img, bpi, img_order, img_latent, 0, tile,
-                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples);
+                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples,
+                     PadOut{samples, sample_lat, nullptr, nullptr, cseed});
   hipLaunchKernelGGL(k_color_write, dim3(bpi, n_img), dim3(256), 0, s, pl, imgs, img_order, g_rgb, boff, samples,
                      cseed, sample_lat);
-  hipLaunchKernelGGL(k_samples_pad, dim3(n_lat), dim3(256), 0, s, seg_base, seg_total, seg_padded, samples,
-                     sample_lat, nullptr, nullptr);
 }
 void launch_fill_i32(int* p, int v, int n, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(nblk(n, 256)), dim3(256), 0, s, p, v, n);

@@ -3,10 +3,9 @@
 //
 // One persistent ray pool holds the rays of every admitted request.  Each
 // tick replays a captured hipGraph on the server stream:
-//     clear counters -> apply level changes -> advance (coarse-to-fine splits
-//     and newly started images join the active list) -> march (three steps of
-//     every active ray of every request with the bf16 decoder; the rays left
-//     active form the next list)
+//     clear counters -> advance (coarse-to-fine splits and newly started images
+//     join the active list) -> march (three steps of every active ray of every
+//     request with the bf16 decoder; the rays left active form the next list)
 // so requests of different resolutions share every decoder launch, and a
 // request that arrives while others are marching joins at the next tick.  Three
 // steps are what lies between two splits: a tick of one step spent more time
@@ -66,7 +65,8 @@ struct Server : sched::Backend {
   RayPool pool{};
   ImgDesc* imgs = nullptr;
   int* lists[2] = {nullptr, nullptr};
-  int* counters = nullptr;       // [0], [1] lengths of the lists, [2] list entries claimed by the march
+  int* count[2] = {nullptr, nullptr};   // lengths of the lists
+  int* claim = nullptr;          // list entries claimed by the march
   AdvEntry* table = nullptr;
   int* hdr = nullptr;            // [0] entries, [1] new rays
   int* img_active = nullptr;
@@ -76,9 +76,9 @@ struct Server : sched::Backend {
   // pinned staging
   int* h_hdr = nullptr;          // header and table, copied together
   AdvEntry* h_table = nullptr;
-  unsigned long long* h_q = nullptr;   // queries, active rays and errors per image, copied together
-  int* h_active = nullptr;
+  unsigned long long* h_q = nullptr;   // queries, errors and active rays per image, copied together
   int* h_err = nullptr;
+  int* h_active = nullptr;
   ImgDesc* h_desc = nullptr;
   float* h_loss = nullptr;
   hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -150,7 +150,8 @@ static T* carve(char*& p, size_t n) {
 }
 
 constexpr size_t kHdrBytes = 4 * sizeof(int);                                        // before the table
-constexpr size_t kStatBytes = sizeof(unsigned long long) + 2 * sizeof(int);          // per image
+// queries, errors, a list length and active rays of n images
+static size_t stat_bytes(int n) { return (sizeof(unsigned long long) + 2 * sizeof(int)) * (size_t)n + sizeof(int); }
 
 static size_t pool_layout(Server* s, char* base) {
   char* p = base;
@@ -170,12 +171,16 @@ static size_t pool_layout(Server* s, char* base) {
   s->imgs = carve<ImgDesc>(p, s->cap_imgs);
   s->lists[0] = carve<int>(p, cap);
   s->lists[1] = carve<int>(p, cap);
-  s->counters = carve<int>(p, 4);
   s->hdr = (int*)carve<char>(p, kHdrBytes + sizeof(AdvEntry) * s->cap_imgs);
   s->table = (AdvEntry*)((char*)s->hdr + kHdrBytes);
-  s->qcount = (unsigned long long*)carve<char>(p, kStatBytes * s->cap_imgs);
-  s->img_active = (int*)(s->qcount + s->cap_imgs);
-  s->ecount = s->img_active + s->cap_imgs;
+  // what the host reads after a tick is one run of memory; what a tick zeroes
+  // is another, from the next list's length to the claims or the other way round
+  s->qcount = (unsigned long long*)carve<char>(p, stat_bytes(s->cap_imgs) + 2 * sizeof(int));
+  s->ecount = (int*)(s->qcount + s->cap_imgs);
+  s->count[0] = s->ecount + s->cap_imgs;
+  s->img_active = s->count[0] + 1;
+  s->claim = s->img_active + s->cap_imgs;
+  s->count[1] = s->claim + 1;
   const int L = s->ctx->L;
   s->z_pool = carve<float>(p, (size_t)s->cap_lat * L);
   s->bias0 = carve<float>(p, (size_t)s->cap_lat * kMaxWidth);
@@ -189,11 +194,9 @@ static int capture_tick(Server* s, int par) {
   dist_ctx* ctx = s->ctx;
   const int cur = par, nxt = par ^ 1;
   HIPCHK_S(hipStreamBeginCapture(s->st, hipStreamCaptureModeThreadLocal));
-  launch_fill_i32(s->counters + nxt, 0, 1, s->st);
-  launch_fill_i32(s->counters + 2, 0, 1, s->st);
-  launch_fill_i32(s->img_active, 0, s->cap_imgs, s->st);
-  launch_apply_levels(s->imgs, s->table, s->hdr, s->cap_imgs, s->st);
-  launch_advance(s->pool, s->imgs, s->lists[cur], s->counters + cur, s->table, s->hdr, s->adv_grid, s->st);
+  // active rays per image, claims and the next list's length
+  launch_fill_i32(nxt ? s->img_active : s->count[0], 0, s->cap_imgs + 2, s->st);
+  launch_advance(s->pool, s->imgs, s->lists[cur], s->count[cur], s->table, s->hdr, s->adv_grid, s->st);
   MarchArgs ma{};
   ma.net = ctx->net[kPrecBF16];
   ma.pool = s->pool;
@@ -201,14 +204,14 @@ static int capture_tick(Server* s, int par) {
   ma.bias0_lat = s->bias0;
   ma.biasS_lat = s->biasS;
   ma.list = s->lists[cur];
-  ma.count = s->counters + cur;
-  ma.claim = s->counters + 2;
+  ma.count = s->count[cur];
+  ma.claim = s->claim;
   ma.n_end = s->steps_per_tick();
   ma.alpha = 1.5f;
   ma.qcount = s->qcount;          // queries counted where they are made
   ma.ecount = s->ecount;          // and non-finite ones
   ma.next_list = s->lists[nxt];
-  ma.next_count = s->counters + nxt;
+  ma.next_count = s->count[nxt];
   ma.img_active = s->img_active;
   launch_march_pool(ma, ctx->n_cu, s->st);
   hipGraph_t g = nullptr;
@@ -236,9 +239,9 @@ static int pool_init(Server* s) {
   HIPCHK_S(hipMemsetAsync(s->mem, 0, s->mem_bytes, s->st));
   HIPCHK_S(hipHostMalloc((void**)&s->h_hdr, kHdrBytes + sizeof(AdvEntry) * s->cap_imgs));
   s->h_table = (AdvEntry*)((char*)s->h_hdr + kHdrBytes);
-  HIPCHK_S(hipHostMalloc((void**)&s->h_q, kStatBytes * s->cap_imgs));
-  s->h_active = (int*)(s->h_q + s->cap_imgs);
-  s->h_err = s->h_active + s->cap_imgs;
+  HIPCHK_S(hipHostMalloc((void**)&s->h_q, stat_bytes(s->cap_imgs)));
+  s->h_err = (int*)(s->h_q + s->cap_imgs);
+  s->h_active = s->h_err + s->cap_imgs + 1;
   HIPCHK_S(hipHostMalloc((void**)&s->h_desc, sizeof(ImgDesc) * s->cap_imgs));
   HIPCHK_S(hipHostMalloc((void**)&s->h_loss, sizeof(float) * s->cap_lat));
   HIPCHK_S(hipStreamSynchronize(s->st));
@@ -438,7 +441,7 @@ void Server::settle(sched::Job* j) {
 }
 
 // One tick: the table of images that start rays, the captured graph (clear
-// counters, apply level changes, advance, march), then the per-image active
+// counters, advance, march), then the per-image active
 // and query counts back on the host.
 int Server::tick(const std::vector<sched::TickEntry>& tab, int n_new) {
   const int n_tab = (int)tab.size();
@@ -451,13 +454,13 @@ int Server::tick(const std::vector<sched::TickEntry>& tab, int n_new) {
   (void)hipMemcpyAsync(hdr, h_hdr, kHdrBytes + sizeof(AdvEntry) * n_tab, hipMemcpyHostToDevice, st);
   hipError_t e = hipGraphLaunch(exec[parity], st);
   parity ^= 1;
-  (void)hipMemcpyAsync(h_q, qcount, kStatBytes * cap_imgs, hipMemcpyDeviceToHost, st);
+  (void)hipMemcpyAsync(h_q, qcount, stat_bytes(cap_imgs), hipMemcpyDeviceToHost, st);
   hipError_t e2 = hipStreamSynchronize(st);
   return (e != hipSuccess || e2 != hipSuccess) ? DIST_EHIP : DIST_OK;
 }
 
 void Server::drop_rays() {
-  launch_fill_i32(counters, 0, 2, st);
+  for (int* c : count) launch_fill_i32(c, 0, 1, st);
   (void)hipStreamSynchronize(st);
 }
 
