@@ -1427,7 +1427,8 @@ extern "C" int dist_render_bwd_camera(dist_ctx* ctx, const dist_saved* saved, co
     launch_adjoint(prec, aa, grid, st);
   }
   launch_cam_reduce(w->pool, w->imgs, w->img_view, n_img, saved->n_views, b->samples, w->cs->sample_cam, w->cs->gp,
-                    b->n_samples, g_sil, g_cam, st);
+                    b->n_samples, g_sil, b->partial2, (size_t)(b->cap_samples / b->tile + 1) * 4 * kMaxWidth, g_cam,
+                    st);
   HIPCHK(hipGetLastError());
   return DIST_OK;
 }

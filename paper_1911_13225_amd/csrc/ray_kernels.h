@@ -104,7 +104,7 @@ void launch_gz_reduce(float* partial, int kmax, int tile, int max_tiles, const i
                       const float* Wsz, int L, float* gz, hipStream_t s, int lat0 = 0, int accumulate = 0);
 void launch_cam_reduce(const RayPool& pl, const ImgDesc* imgs, const int* img_view, int n_img, int n_views,
                        const float4* samples, const int4* sample_cam, const float* gp_part, const int* n_samples,
-                       const float* g_sil, float* g_cam, hipStream_t s);
+                       const float* g_sil, float* scratch, size_t scratch_floats, float* g_cam, hipStream_t s);
 void launch_hit_gv(const RayPool& pl, const ImgDesc* imgs, const float4* samples, const int4* sample_cam,
                    const float* gp_part, const int* n_samples, int max_samples, float* gv, hipStream_t s);
 void launch_ul_init(const RayPool& pl, const ImgDesc* imgs, int n_img, int spi, const float* g_depth, float* lam,

@@ -483,23 +483,26 @@ __global__ __launch_bounds__(256) void k_samples_write(RayPool pl, const ImgDesc
   }
 }
 
-// Camera-extrinsic gradient of one view (blockIdx.x), fixed summation order:
+// Camera-extrinsic gradient of one view (blockIdx.y), fixed summation order:
 // every depth/silhouette sample of the view's images adds s grad_p f(p) to
 // dL/dc and s t grad_p f(p) u^T to dL/dR (p = c + t R u, t detached), with
 // s grad_p f = s 0.5 p/|p| + the adjoint's per-wave partials; every pixel whose
 // ray misses the unit sphere adds dL/dS dS/d(c, R) of S = sqrt(|c|^2 -
-// (c.v)^2) - 1 (App. A.3).  Output g_cam[v] = (dL/dc, dL/dR row-major).
+// (c.v)^2) - 1 (App. A.3).  Workgroup b of the view's B takes every B-th run
+// of 256 samples and pixels; its sums (dL/dc, dL/dR row-major) go to out[v][b]
+// and k_cam_sum adds them in order.  One workgroup per view took 118 us for two
+// views of 192^2; 64 take 12 us and their sum 5.
 __global__ __launch_bounds__(256) void k_cam_reduce(RayPool pl, const ImgDesc* imgs, const int* img_view, int n_img,
                                                     const float4* samples, const int4* sample_cam,
                                                     const float* gp_part, const int* n_samples, const float* g_sil,
-                                                    float* g_cam) {
+                                                    float* out) {
   __shared__ float red[256];
-  const int v = blockIdx.x;
+  const int v = blockIdx.y, i0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
   float acc[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) acc[k] = 0.f;
   const int ns = *n_samples;
-  for (int i = threadIdx.x; i < ns; i += 256) {
+  for (int i = i0; i < ns; i += step) {
     const int4 sc = sample_cam[i];
     if (sc.x < 0 || img_view[sc.x] != v) continue;
     const ImgDesc& im = imgs[sc.x];
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(256) void k_cam_reduce(RayPool pl, const ImgDesc* i
       if (img_view[img] != v) continue;
       const ImgDesc& im = imgs[img];
       const int hw = im.H * im.W;
-      for (int pix = threadIdx.x; pix < hw; pix += 256) {
+      for (int pix = i0; pix < hw; pix += step) {
         const int r = im.slot_base + im.lvl_off[0] + pix;
         const float gs = g_sil[(size_t)im.out_base + pix];
         if (pl.st[r] != ST_MISS || gs == 0.f) continue;
@@ -565,9 +568,23 @@ __global__ __launch_bounds__(256) void k_cam_reduce(RayPool pl, const ImgDesc* i
       if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
       __syncthreads();
     }
-    if (threadIdx.x == 0) g_cam[12 * v + k] = red[0];
+    if (threadIdx.x == 0) out[((size_t)v * gridDim.x + blockIdx.x) * 12 + k] = red[0];
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(64) void k_cam_sum(const float* part, int B, float* g_cam) {
+  const int v = blockIdx.x, k = threadIdx.x;
+  if (k >= 12) return;
+  float s = 0.f;
+  for (int b = 0; b < B; b += 16) {
+    float p[16];                           // in flight together, added in order
+#pragma unroll
+    for (int u = 0; u < 16; ++u) p[u] = b + u < B ? part[((size_t)v * B + b + u) * 12 + k] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += p[u];
+  }
+  g_cam[12 * (size_t)v + k] = s;
 }
 
 // g_z[l] = W0_z^T S0 + Ws_z^T Ss with S = sum over the latent's tiles.  The
@@ -578,35 +595,38 @@ __global__ __launch_bounds__(256) void k_cam_reduce(RayPool pl, const ImgDesc* i
 // memory latency, not bandwidth) and add them in tile order.
 constexpr int kFold = 64;
 
+// blockIdx.z: the column sums of one row group of layer 0 or of the skip layer
+// (the groups that the kernel did not write are left out).
 __global__ __launch_bounds__(512) void k_gz_fold(float* partial, int kmax, int tile, const int* seg_base,
-                                                 const int* seg_padded, int lat0) {
+                                                 const int* seg_padded, int lat0, int mg0) {
   const int l = lat0 + blockIdx.y;
   const int t0 = seg_base[l] / tile, nt = seg_padded[l] / tile;
   const int c0 = blockIdx.x * kFold;
-  if (c0 >= nt) return;
+  const int i = threadIdx.x;
+  if (c0 >= nt || i >= kmax) return;
   const int c1 = min(c0 + kFold, nt);
-  const int width = 4 * kmax;
-  for (int i = threadIdx.x; i < width; i += blockDim.x) {
-    const float* p = partial + (size_t)(t0 + c0) * width + i;
-    float a = 0.f;
-    int t = 0;
-    for (; t + 8 <= c1 - c0; t += 8) {
-      float v[8];
+  const int width = 4 * kmax, z = blockIdx.z;
+  float* p = partial + (size_t)(t0 + c0) * width + (z < mg0 ? z : 2 + z - mg0) * kmax + i;
+  float a = 0.f;
+  int t = 0;
+  for (; t + 16 <= c1 - c0; t += 16) {
+    float v[16];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(t + u) * width];
+    for (int u = 0; u < 16; ++u) v[u] = p[(size_t)(t + u) * width];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) a += v[u];
-    }
-    for (; t < c1 - c0; ++t) a += p[(size_t)t * width];
-    partial[(size_t)(t0 + c0) * width + i] = a;
+    for (int u = 0; u < 16; ++u) a += v[u];
   }
+  for (; t < c1 - c0; ++t) a += p[(size_t)t * width];
+  *p = a;
 }
 
-// One workgroup per latent.  The run heads of a column are summed in two
-// halves (each in head order, added half 0 + half 1), and each output of the
-// latent code in four quarters of the contracted rows [W0_z; Ws_z] (each in
-// row order, added in quarter order), so every chain is short and the order
-// is fixed.
+// One workgroup per latent and 64 values of its gradient (blockIdx.y).  The
+// run heads of a column are summed in two halves (each in head order, added
+// half 0 + half 1), and each output of the latent code in four quarters of the
+// contracted rows [W0_z; Ws_z] (each in row order, added in quarter order), so
+// every chain is short and the order is fixed.  The column sums are summed
+// again by each of the latent's workgroups: with one workgroup for the whole
+// code its 1 MB of W_z came through one CU (30 us for 256 values; 16 us by four).
 __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int kmax, int tile, const int* seg_base,
                                                     const int* seg_padded, int w0, int mg0, const float* W0z,
                                                     int ws, int mgs, const float* Wsz, int L, float* gz, int lat0,
@@ -614,7 +634,7 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
   __shared__ float S0[512];
   __shared__ float Ss[512];
   __shared__ float ph[2][2][512];
-  __shared__ float pq[4][256];
+  __shared__ float pq[4][64];
   const int l = lat0 + blockIdx.x;
   const int t0 = seg_base[l] / tile, nt = seg_padded[l] / tile;
   const int nheads = (nt + kFold - 1) / kFold;
@@ -623,10 +643,10 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
     const int h1 = half ? nheads : nheads / 2;
     int h = half ? nheads / 2 : 0;
     float a = 0.f, b = 0.f;
-    for (; h + 4 <= h1; h += 4) {
-      float va[4][2], vb[4][2];            // four run heads (up to two row groups each) in flight
+    for (; h + 8 <= h1; h += 8) {
+      float va[8][2], vb[8][2];            // eight run heads (up to two row groups each) in flight
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < 8; ++u) {
         const float* pt = partial + (size_t)(t0 + (h + u) * kFold) * 4 * kmax;
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
@@ -635,7 +655,7 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
         }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < 8; ++u) {
         for (int g = 0; g < mg0; ++g) a += va[u][g];
         if (Wsz)
           for (int g = 0; g < mgs; ++g) b += vb[u][g];
@@ -656,35 +676,35 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
     Ss[threadIdx.x] = ph[1][0][threadIdx.x] + ph[1][1][threadIdx.x];
   }
   __syncthreads();
-  const int q = threadIdx.x >> 8, jl = threadIdx.x & 255;
-  const int rows = w0 + (Wsz ? ws : 0);
-  const int r0 = q * rows / 4, r1 = (q + 1) * rows / 4;
-  for (int j0 = 0; j0 < L; j0 += 256) {
-    const int j = j0 + jl;
+  const int q = threadIdx.x >> 6, jl = threadIdx.x & 63, j = blockIdx.y * 64 + jl;
+  if (q < 4) {
+    const int rows = w0 + (Wsz ? ws : 0);
+    const int r1 = (q + 1) * rows / 4;
+    int r = q * rows / 4;
     float acc = 0.f;
     if (j < L) {
-      int r = r0;
-      for (; r + 8 <= r1; r += 8) {
-        float w[8], x[8];
+      for (; r + 32 <= r1; r += 32) {
+        float w[32];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 32; ++u) {
           const int rr = r + u;
           w[u] = rr < w0 ? W0z[(size_t)rr * L + j] : Wsz[(size_t)(rr - w0) * L + j];
-          x[u] = rr < w0 ? S0[rr] : Ss[rr - w0];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc = fmaf(w[u], x[u], acc);
+        for (int u = 0; u < 32; ++u) {
+          const int rr = r + u;
+          acc = fmaf(w[u], rr < w0 ? S0[rr] : Ss[rr - w0], acc);
+        }
       }
       for (; r < r1; ++r)
         acc = fmaf(r < w0 ? W0z[(size_t)r * L + j] : Wsz[(size_t)(r - w0) * L + j], r < w0 ? S0[r] : Ss[r - w0], acc);
     }
     pq[q][jl] = acc;
-    __syncthreads();
-    if (q == 0 && j < L) {
-      const float v = ((pq[0][jl] + pq[1][jl]) + pq[2][jl]) + pq[3][jl];
-      gz[(size_t)l * L + j] = accumulate ? gz[(size_t)l * L + j] + v : v;
-    }
-    __syncthreads();
+  }
+  __syncthreads();
+  if (q == 0 && j < L) {
+    const float v = ((pq[0][jl] + pq[1][jl]) + pq[2][jl]) + pq[3][jl];
+    gz[(size_t)l * L + j] = accumulate ? gz[(size_t)l * L + j] + v : v;
   }
 }
 
@@ -740,6 +760,29 @@ __global__ __launch_bounds__(256) void k_advance_new(RayPool pl, const ImgDesc* 
 // and max'(0) = 0; a hinge term whose weight S* or 1 - S* is zero adds
 // nothing.  Gradient outputs may be null (not written); normals are read
 // only when w_n != 0.
+// V pixels per thread and step: 4 with 16-byte accesses where every map starts
+// and every image's map ends on a 16-byte boundary, else 1.  The loss of an
+// image is one workgroup's sum (blockIdx.y = 0), so its order is fixed; of an
+// image of more than kLossRun pixels the gradients are written by further
+// workgroups of kLossRun pixels each.  Four 256^2 images with normals: 61 us by
+// one pixel at a time, 45 us by four, 16 us with the gradients apart.
+constexpr int kLossRun = 4096;
+
+template <int V>
+__device__ __forceinline__ void ld_map(const float* p, size_t i, float (&v)[V]) {
+  if constexpr (V == 4) {
+    const float4 x = *(const float4*)(p + i);
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+  } else {
+    v[0] = p[i];
+  }
+}
+template <int V>
+__device__ __forceinline__ void st_map(float* p, size_t i, const float (&v)[V]) {
+  if constexpr (V == 4) *(float4*)(p + i) = make_float4(v[0], v[1], v[2], v[3]);
+  else p[i] = v[0];
+}
+template <int V>
 __global__ __launch_bounds__(1024) void k_render_loss(const float* depth, const float* normal, const float* sil,
                                                       const float* depth_t, const float* normal_t,
                                                       const float* sil_t, int hw, float w_d, float w_s, float w_n,
@@ -749,25 +792,61 @@ __global__ __launch_bounds__(1024) void k_render_loss(const float* depth, const 
   const float inv = 1.f / (float)hw;
   const float cd = w_d * inv, cs = w_s * inv, cn = w_n * inv;
   const bool nrm = w_n != 0.f;
+  const bool sum = blockIdx.y == 0, grad = gridDim.y == 1 || !sum;
+  const int p0 = sum ? 0 : (blockIdx.y - 1) * kLossRun, p1 = sum ? hw : min(p0 + kLossRun, hw);
   float acc = 0.f;
-  for (int p = threadIdx.x; p < hw; p += 1024) {
+  for (int p = p0 + V * threadIdx.x; p < p1; p += V * 1024) {
     const size_t i = base + p;
-    const float S = sil[i], St = sil_t[i];
-    const bool fg = S < 0.f && St > 0.5f;
-    const float dd = fg ? depth[i] - depth_t[i] : 0.f;
-    float l = cd * fabsf(dd);
-    l += cs * ((St > 0.f ? St * fmaxf(S, 0.f) : 0.f) + (St < 1.f ? (1.f - St) * fmaxf(-S, 0.f) : 0.f));
-    float nt[3] = {0.f, 0.f, 0.f};
-    if (nrm && fg) {
-      for (int k = 0; k < 3; ++k) nt[k] = normal_t[3 * i + k];
-      l -= cn * (normal[3 * i] * nt[0] + normal[3 * i + 1] * nt[1] + normal[3 * i + 2] * nt[2]);
+    float S[V], St[V], d[V], dt[V], gd[V], gs[V], ls[V];
+    float nr[3][V], nt[3][V];           // 3 V consecutive floats each
+    ld_map<V>(sil, i, S);
+    ld_map<V>(sil_t, i, St);
+    ld_map<V>(depth, i, d);
+    ld_map<V>(depth_t, i, dt);
+    if (nrm) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        ld_map<V>(normal, 3 * i + V * k, nr[k]);
+        ld_map<V>(normal_t, 3 * i + V * k, nt[k]);
+      }
     }
-    if (g_depth) g_depth[i] = cd * (dd > 0.f ? 1.f : (dd < 0.f ? -1.f : 0.f));
-    if (g_sil) g_sil[i] = cs * (St * (S > 0.f ? 1.f : 0.f) - (1.f - St) * (S < 0.f ? 1.f : 0.f));
-    if (g_normal)
-      for (int k = 0; k < 3; ++k) g_normal[3 * i + k] = -cn * nt[k];
-    acc += l;
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const bool fg = S[u] < 0.f && St[u] > 0.5f;
+      const float dd = fg ? d[u] - dt[u] : 0.f;
+      float l = cd * fabsf(dd);
+      l += cs * ((St[u] > 0.f ? St[u] * fmaxf(S[u], 0.f) : 0.f) + (St[u] < 1.f ? (1.f - St[u]) * fmaxf(-S[u], 0.f) : 0.f));
+      if (nrm) {
+        float dot = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          float& n = nt[(3 * u + k) / V][(3 * u + k) % V];
+          if (!fg) n = 0.f;
+          const float x = nr[(3 * u + k) / V][(3 * u + k) % V] * n;
+          dot = k == 0 ? x : dot + x;
+        }
+        if (fg) l -= cn * dot;
+      }
+      gd[u] = cd * (dd > 0.f ? 1.f : (dd < 0.f ? -1.f : 0.f));
+      gs[u] = cs * (St[u] * (S[u] > 0.f ? 1.f : 0.f) - (1.f - St[u]) * (S[u] < 0.f ? 1.f : 0.f));
+      ls[u] = l;
+    }
+    if constexpr (V == 4) acc += (ls[0] + ls[1]) + (ls[2] + ls[3]);
+    else acc += ls[0];
+    if (!grad) continue;
+    if (g_depth) st_map<V>(g_depth, i, gd);
+    if (g_sil) st_map<V>(g_sil, i, gs);
+    if (g_normal) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        float gn[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) gn[u] = nrm ? -cn * nt[k][u] : -cn * 0.f;
+        st_map<V>(g_normal, 3 * i + V * k, gn);
+      }
+    }
   }
+  if (!sum) return;
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int s = 512; s > 0; s >>= 1) {
@@ -1222,17 +1301,20 @@ void launch_hit_gv(const RayPool& pl, const ImgDesc* imgs, const float4* samples
 
 void launch_cam_reduce(const RayPool& pl, const ImgDesc* imgs, const int* img_view, int n_img, int n_views,
                        const float4* samples, const int4* sample_cam, const float* gp_part, const int* n_samples,
-                       const float* g_sil, float* g_cam, hipStream_t s) {
-  hipLaunchKernelGGL(k_cam_reduce, dim3(n_views), dim3(256), 0, s, pl, imgs, img_view, n_img, samples, sample_cam,
-                     gp_part, n_samples, g_sil, g_cam);
+                       const float* g_sil, float* scratch, size_t scratch_floats, float* g_cam, hipStream_t s) {
+  // as many workgroups per view as the scratch holds sums for; one writes g_cam itself
+  const int B = (int)std::max<size_t>(1, std::min<size_t>(64, scratch_floats / (12 * (size_t)n_views)));
+  hipLaunchKernelGGL(k_cam_reduce, dim3(B, n_views), dim3(256), 0, s, pl, imgs, img_view, n_img, samples, sample_cam,
+                     gp_part, n_samples, g_sil, B > 1 ? scratch : g_cam);
+  if (B > 1) hipLaunchKernelGGL(k_cam_sum, dim3(n_views), dim3(64), 0, s, scratch, B, g_cam);
 }
 void launch_gz_reduce(float* partial, int kmax, int tile, int max_tiles, const int* seg_base,
                       const int* seg_padded, int n_lat, int w0, int mg0, const float* W0z, int ws, int mgs,
                       const float* Wsz, int L, float* gz, hipStream_t s, int lat0, int accumulate) {
-  hipLaunchKernelGGL(k_gz_fold, dim3(nblk(max_tiles, kFold), n_lat), dim3(512), 0, s, partial, kmax, tile, seg_base,
-                     seg_padded, lat0);
-  hipLaunchKernelGGL(k_gz_reduce, dim3(n_lat), dim3(1024), 0, s, partial, kmax, tile, seg_base, seg_padded, w0, mg0,
-                     W0z, ws, mgs, Wsz, L, gz, lat0, accumulate);
+  hipLaunchKernelGGL(k_gz_fold, dim3(nblk(max_tiles, kFold), n_lat, mg0 + (Wsz ? mgs : 0)), dim3(512), 0, s, partial,
+                     kmax, tile, seg_base, seg_padded, lat0, mg0);
+  hipLaunchKernelGGL(k_gz_reduce, dim3(n_lat, nblk(L, 64)), dim3(1024), 0, s, partial, kmax, tile, seg_base,
+                     seg_padded, w0, mg0, W0z, ws, mgs, Wsz, L, gz, lat0, accumulate);
 }
 void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
                     const int* hdr, int grid, hipStream_t s) {
@@ -1241,8 +1323,22 @@ void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* coun
 void launch_render_loss(const float* depth, const float* normal, const float* sil, const float* depth_t,
                         const float* normal_t, const float* sil_t, int n_img, int hw, float w_d, float w_s, float w_n,
                         float* loss, float* g_depth, float* g_normal, float* g_sil, hipStream_t s) {
-  hipLaunchKernelGGL(k_render_loss, dim3(n_img), dim3(1024), 0, s, depth, normal, sil, depth_t, normal_t, sil_t, hw,
-                     w_d, w_s, w_n, loss, g_depth, g_normal, g_sil);
+  uintptr_t any = 0;
+  for (const void* p : {(const void*)depth, (const void*)sil, (const void*)depth_t, (const void*)sil_t,
+                        (const void*)g_depth, (const void*)g_normal, (const void*)g_sil})
+    any |= (uintptr_t)p;
+  if (w_n != 0.f) any |= (uintptr_t)normal | (uintptr_t)normal_t;
+  bool apart = hw > kLossRun && (g_depth || g_normal || g_sil);
+  for (const float* g : {g_depth, g_normal, g_sil})       // a gradient in its map's place: each pixel read first
+    for (const float* p : {depth, normal, sil, depth_t, normal_t, sil_t})
+      if (g && g == p) apart = false;
+  const dim3 grid(n_img, apart ? 1 + nblk(hw, kLossRun) : 1);
+  if (hw % 4 == 0 && any % 16 == 0)
+    hipLaunchKernelGGL(k_render_loss<4>, grid, dim3(1024), 0, s, depth, normal, sil, depth_t, normal_t, sil_t, hw,
+                       w_d, w_s, w_n, loss, g_depth, g_normal, g_sil);
+  else
+    hipLaunchKernelGGL(k_render_loss<1>, grid, dim3(1024), 0, s, depth, normal, sil, depth_t, normal_t, sil_t, hw,
+                       w_d, w_s, w_n, loss, g_depth, g_normal, g_sil);
 }
 void launch_sum_ordered(const float* a, int n, float* out, hipStream_t s) {
   hipLaunchKernelGGL(k_sum_ordered, dim3(1), dim3(64), 0, s, a, n, out);

@@ -190,3 +190,47 @@ def test_tiles_of_one_latent_and_of_several(name, prec):
     a = api.dist_sdf_eval(ctx, P, one, Z[:1].contiguous(), prec)
     b = api.dist_sdf_eval(ctx, P, two, Z, prec)
     assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(a.nan_to_num(), b.nan_to_num())
+
+
+@pytest.mark.parametrize("shift", [0, 1], ids=["aligned", "shifted"])
+@pytest.mark.parametrize("H,W", [(1, 3), (64, 64), (63, 65), (64, 65), (67, 71)])
+def test_loss_of_odd_sizes_and_unaligned_maps(H, W, shift):
+    """Maps whose sizes and addresses call for one or four pixels per access, of up to and over one
+    4096-pixel run, and gradients written over the maps they come from.  A loss adds at most
+    ceil(4757 / 1024) + 10 terms in a chain after about 8 roundings of each: 23 x 2^-24 < 2e-6 of the
+    sum of absolute terms (the normals' at most w_n)."""
+    from types import SimpleNamespace
+    from oracle import dist_oracle as O
+    from paper_1911_13225_amd import api, _native as N
+    n, w = 2, (10.0, 1.0, 0.5)
+    rng = np.random.default_rng(100 * H + W)
+    maps = [rng.uniform(0.5, 2, (n, H, W)), rng.normal(size=(n, H, W, 3)), rng.normal(size=(n, H, W)),
+            rng.uniform(0.5, 2, (n, H, W)), rng.normal(size=(n, H, W, 3)), rng.choice([0.0, 0.3, 1.0], (n, H, W))]
+    for k in (1, 4):
+        maps[k] /= np.linalg.norm(maps[k], axis=-1, keepdims=True)
+    maps = [m.astype(np.float32) for m in maps]
+
+    def dev(a):
+        t = torch.empty(a.size + shift, device="cuda")[shift:].view(a.shape)
+        t.copy_(torch.tensor(a))
+        return t
+
+    d, nr, s, dt, nt, st = [dev(a) for a in maps]
+    loss, gd, gn, gs = api.dist_render_loss(d, nr, s, dt, nt, st, *w)
+    for i in range(n):
+        m = [a[i].astype(np.float64) for a in maps]
+        r = SimpleNamespace(H=H, W=W, depth=m[0], normal=m[1], sil=m[2])
+        L, g_d, g_n, g_s = O.loss_and_grads(r, *m[3:], w_d=w[0], w_s=w[1], w_n=w[2])
+        L0 = O.loss_and_grads(r, *m[3:], w_d=w[0], w_s=w[1], w_n=0.0)[0]
+        print(H, W, shift, i, float(loss[i]), L, flush=True)
+        assert abs(float(loss[i]) - L) <= 2e-6 * (L0 + w[2])
+        for got, want in ((gd, g_d), (gn, g_n), (gs, g_s)):
+            np.testing.assert_allclose(got[i].cpu().numpy(), want, rtol=1e-6, atol=0)
+    # the loss alone, and the gradients in the place of their maps
+    assert torch.equal(loss, api.dist_render_loss(d, nr, s, dt, nt, st, *w, want_grad=False)[0])
+    loss2 = torch.empty_like(loss)
+    p = api._ptr
+    api.check(N.load().dist_render_loss(n, H, W, p(d), p(nr), p(s), p(dt), p(nt), p(st), *w, p(loss2), p(d), p(nr),
+                                        p(s), api._stream()))
+    torch.cuda.synchronize()
+    assert torch.equal(loss, loss2) and torch.equal(d, gd) and torch.equal(nr, gn) and torch.equal(s, gs)
