@@ -192,6 +192,8 @@ __device__ __forceinline__ void cap_put(float* base, size_t off, float v) {
   else ((bf16*)base)[off] = (bf16)v;
 }
 
+__device__ __forceinline__ float4 ld4(const float* p) { return *(const float4*)p; }
+
 // Capture of a whole tile from LDS, after the barrier that ends a layer: the
 // tile's M rows of the layer's first W features, from one plane of the
 // activation tile (split bf16: the hi chunks, or the lo chunks where an
@@ -246,11 +248,36 @@ __device__ __forceinline__ void cap_tile(const Sm<P>& s, int plane, float* base,
   }
 }
 
+// Delta of the last hidden layer, gm w_last [h > 0], in the blocked layout of
+// the capture: h is in the tile's lo chunks (split bf16, after EP_LAST_ADJ), so
+// the values are gathered as in cap_tile and written as 16-byte runs of rows
+// (60,007 samples of an 8 x 512 decoder: 1031 us for the whole recompute with
+// h read back from memory and Delta written 2 bytes a thread, now 934).
+__device__ __forceinline__ void cap_last_delta(const Sm<2>& s, const float* wlast, float* base, int W) {
+  constexpr int G = Cfg<2>::M / 8;
+  for (int it = threadIdx.x; it < (W / 4) * G; it += blockDim.x) {
+    const int a = it % G, n = 4 * (it / G);
+    const float4 w4 = ld4(wlast + n);
+    const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+    bf16 d[4][8] __attribute__((aligned(16)));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint2 r = *(const uint2*)(s.chunk(8 * a + i, 2 * (n >> 3) + 1) + 2 * (n & 7));
+      const float gm = s.gm[8 * a + i];
+      const float h[4] = {__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u), __uint_as_float(r.y << 16),
+                          __uint_as_float(r.y & 0xffff0000u)};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e][i] = (bf16)(h[e] > 0.f ? gm * w[e] : 0.f);
+    }
+    bf16* dst = (bf16*)base + (size_t)n * kCapBlock + 8 * a;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *(uint4*)(dst + e * (size_t)kCapBlock) = *(const uint4*)d[e];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Layer 0: h0 = relu(W0_p p + (b0 + W0_z z)), float32 VALU, written to LDS.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float4 ld4(const float* p) { return *(const float4*)p; }
-
 // Each thread owns one chunk of EPC output features (its W0_p columns stay in
 // registers) and walks the rows of the tile; N0 / EPC divides NT.
 // With MASK the ReLU bits of layer 0 are stored like those of the other
@@ -1922,10 +1949,15 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     if (theta) {
       // Delta of the last hidden layer: gm * w_last * [h > 0]
       const int ll = net.nl - 2, W = net.wpad[ll];
-      for (int i = tid; i < M * W; i += kAdjWaves * 64) {
-        const int n = i / M, m = i - n * M;          // consecutive threads: consecutive rows of a feature
-        const size_t o = (size_t)ll * net.kmax * rstride + blk0 + (size_t)n * kCapBlock + m;
-        cap_put<P>(a.dbuf, o, cap_get<P>(a.hbuf, o) > 0.f ? s.gm[m] * net.wlast[n] : 0.f);
+      const size_t o0 = (size_t)ll * net.kmax * rstride + blk0;
+      if constexpr (P == 2) {
+        cap_last_delta(s, net.wlast, cap_ptr<P>(a.dbuf, o0), W);
+      } else {
+        for (int i = tid; i < M * W; i += kAdjWaves * 64) {
+          const int n = i / M, m = i - n * M;          // consecutive threads: consecutive rows of a feature
+          const size_t o = o0 + (size_t)n * kCapBlock + m;
+          cap_put<P>(a.dbuf, o, cap_get<P>(a.hbuf, o) > 0.f ? s.gm[m] * net.wlast[n] : 0.f);
+        }
       }
     }
     float* part = a.partial + (size_t)tile * 4 * net.kmax;
