@@ -123,6 +123,20 @@ void launch_color_samples(const RayPool& pl, const ImgDesc* imgs, const int* img
                           int n_img, int hw, int n_lat, int tile, const float* g_rgb, int* bsum, int* boff,
                           int* seg_base, int* seg_total, int* seg_padded, int* n_samples, float4* samples,
                           float4* cseed, int* sample_lat, hipStream_t s);
+// What a serving tick reads from and writes to pinned host memory, in 4-byte
+// words: the header and the entries it counts, and the counts the scheduler
+// reads.  The tick's own kernels move them, which spares two copies and the
+// gaps around them (10 us a tick).
+struct TickIo {
+  const int* h_hdr;
+  int* hdr;
+  int hdr_words, entry_words, cap_entries;
+  const int* stat;
+  int* h_stat;
+  int stat_words;
+};
+void launch_tick_begin(const TickIo& io, int* zero, int n_zero, hipStream_t s);
+void launch_tick_end(const TickIo& io, hipStream_t s);
 // The rays that start this tick (split children and (re)started images) join the list.
 void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
                     const int* hdr, int grid, hipStream_t s);

@@ -709,6 +709,21 @@ __global__ __launch_bounds__(1024) void k_gz_reduce(const float* partial, int km
 }
 
 // ---------------------------------------------------------------------------
+// Serving: a tick's header and table come from, and its counts go to, pinned
+// host memory by kernels of the tick itself (see TickIo).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_tick_begin(TickIo io, int* zero, int n_zero) {
+  const int i0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+  for (int i = i0; i < n_zero; i += step) zero[i] = 0;
+  const int words = io.hdr_words + io.entry_words * min(io.h_hdr[0], io.cap_entries);
+  for (int i = i0; i < words; i += step) io.hdr[i] = io.h_hdr[i];
+}
+
+__global__ __launch_bounds__(256) void k_tick_end(TickIo io) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < io.stat_words; i += gridDim.x * 256) io.h_stat[i] = io.stat[i];
+}
+
+// ---------------------------------------------------------------------------
 // Serving: the rays that start this tick, the children of images that split
 // and the coarsest rays of newly (re)started images, join the pooled active
 // list behind the rays that the last march left active.
@@ -1319,6 +1334,12 @@ void launch_gz_reduce(float* partial, int kmax, int tile, int max_tiles, const i
 void launch_advance(const RayPool& pl, const ImgDesc* imgs, int* list, int* count, const AdvEntry* table,
                     const int* hdr, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_advance_new, dim3(grid), dim3(256), 0, s, pl, imgs, list, count, table, hdr);
+}
+void launch_tick_begin(const TickIo& io, int* zero, int n_zero, hipStream_t s) {
+  hipLaunchKernelGGL(k_tick_begin, dim3(nblk(n_zero, 256)), dim3(256), 0, s, io, zero, n_zero);
+}
+void launch_tick_end(const TickIo& io, hipStream_t s) {
+  hipLaunchKernelGGL(k_tick_end, dim3(nblk(io.stat_words, 256)), dim3(256), 0, s, io);
 }
 void launch_render_loss(const float* depth, const float* normal, const float* sil, const float* depth_t,
                         const float* normal_t, const float* sil_t, int n_img, int hw, float w_d, float w_s, float w_n,

@@ -2,15 +2,18 @@
 // requests over one pooled sphere tracer.
 //
 // One persistent ray pool holds the rays of every admitted request.  Each
-// tick replays a captured hipGraph on the server stream:
-//     clear counters -> advance (coarse-to-fine splits and newly started images
-//     join the active list) -> march (three steps of every active ray of every
-//     request with the bf16 decoder; the rays left active form the next list)
+// tick launches on the server stream:
+//     begin (clear counters, fetch the tick's table) -> advance (coarse-to-fine
+//     splits and newly started images join the active list) -> march (three
+//     steps of every active ray of every request with the bf16 decoder; the rays
+//     left active form the next list) -> end (counts to the host)
 // so requests of different resolutions share every decoder launch, and a
 // request that arrives while others are marching joins at the next tick.  Three
 // steps are what lies between two splits: a tick of one step spent more time
 // on its copies, launches and host synchronisation (120 us) than on its march
-// (89 us), and 158 of them served the nine requests of a burst.
+// (89 us), and 158 of them served the nine requests of a burst.  The host waits
+// for every tick's counts, so its four kernels are launched one by one: replayed
+// as a graph they began 13 us later (54 ticks of a burst: 24.0 against 23.3 ms).
 // Between ticks the scheduler thread reads the per-image active counts,
 // finalises finished requests (maps, normals), and for latent-optimisation
 // requests computes the loss, the paper's approximate gradient (adjoint) and
@@ -21,7 +24,7 @@
 // waits in the queue until resources free up.  The queue, tickets, admission
 // bookkeeping, the coarse-to-fine tick table and the completion / failure /
 // cancellation paths are the device-independent core in sched_core.h; this
-// file is its HIP backend (pool, captured tick, per-request buffers, outputs,
+// file is its HIP backend (pool, tick, per-request buffers, outputs,
 // loss, gradient and optimiser step).
 #include <cstring>
 #include <deque>
@@ -81,7 +84,7 @@ struct Server : sched::Backend {
   int* h_active = nullptr;
   ImgDesc* h_desc = nullptr;
   float* h_loss = nullptr;
-  hipGraphExec_t exec[2] = {nullptr, nullptr};
+  TickIo io{};
   int parity = 0;
   int adv_grid = 1024;
   // request buffer cache (size -> blocks), charged against the budget
@@ -139,7 +142,7 @@ static void buf_put(Server* s, char* p, size_t bytes) {
 }
 
 // ---------------------------------------------------------------------------
-// pool set-up and the captured tick
+// pool set-up and the tick
 // ---------------------------------------------------------------------------
 template <class T>
 static T* carve(char*& p, size_t n) {
@@ -190,12 +193,13 @@ static size_t pool_layout(Server* s, char* base) {
   return (size_t)(p - base) + 256;
 }
 
-static int capture_tick(Server* s, int par) {
+// The kernels of a tick: counters cleared and the table fetched, the rays that
+// start, three marching steps, the counts handed to the host.
+static void launch_tick(Server* s) {
   dist_ctx* ctx = s->ctx;
-  const int cur = par, nxt = par ^ 1;
-  HIPCHK_S(hipStreamBeginCapture(s->st, hipStreamCaptureModeThreadLocal));
+  const int cur = s->parity, nxt = cur ^ 1;
   // active rays per image, claims and the next list's length
-  launch_fill_i32(nxt ? s->img_active : s->count[0], 0, s->cap_imgs + 2, s->st);
+  launch_tick_begin(s->io, nxt ? s->img_active : s->count[0], s->cap_imgs + 2, s->st);
   launch_advance(s->pool, s->imgs, s->lists[cur], s->count[cur], s->table, s->hdr, s->adv_grid, s->st);
   MarchArgs ma{};
   ma.net = ctx->net[kPrecBF16];
@@ -214,11 +218,7 @@ static int capture_tick(Server* s, int par) {
   ma.next_count = s->count[nxt];
   ma.img_active = s->img_active;
   launch_march_pool(ma, ctx->n_cu, s->st);
-  hipGraph_t g = nullptr;
-  HIPCHK_S(hipStreamEndCapture(s->st, &g));
-  HIPCHK_S(hipGraphInstantiate(&s->exec[par], g, nullptr, nullptr, 0));
-  (void)hipGraphDestroy(g);
-  return DIST_OK;
+  launch_tick_end(s->io, s->st);
 }
 
 static int pool_init(Server* s) {
@@ -245,10 +245,11 @@ static int pool_init(Server* s) {
   HIPCHK_S(hipHostMalloc((void**)&s->h_desc, sizeof(ImgDesc) * s->cap_imgs));
   HIPCHK_S(hipHostMalloc((void**)&s->h_loss, sizeof(float) * s->cap_lat));
   HIPCHK_S(hipStreamSynchronize(s->st));
-  for (int par = 0; par < 2; ++par) {
-    rc = capture_tick(s, par);
-    if (rc) return rc;
-  }
+  void* hp[2];
+  HIPCHK_S(hipHostGetDevicePointer(&hp[0], s->h_hdr, 0));
+  HIPCHK_S(hipHostGetDevicePointer(&hp[1], s->h_q, 0));
+  s->io = TickIo{(const int*)hp[0], s->hdr, (int)(kHdrBytes / 4), (int)(sizeof(AdvEntry) / 4), s->cap_imgs,
+                 (const int*)s->qcount, (int*)hp[1], (int)(stat_bytes(s->cap_imgs) / 4)};
   return DIST_OK;
 }
 
@@ -440,7 +441,7 @@ void Server::settle(sched::Job* j) {
   if (r->req.kind == DIST_REQ_ZOPT && r->lat >= 0 && r->iter > 0) r->final_loss = h_loss[r->lat];
 }
 
-// One tick: the table of images that start rays, the captured graph (clear
+// One tick: the table of images that start rays, the tick's kernels (clear
 // counters, advance, march), then the per-image active
 // and query counts back on the host.
 int Server::tick(const std::vector<sched::TickEntry>& tab, int n_new) {
@@ -451,10 +452,9 @@ int Server::tick(const std::vector<sched::TickEntry>& tab, int n_new) {
   }
   h_hdr[0] = n_tab;
   h_hdr[1] = n_new;
-  (void)hipMemcpyAsync(hdr, h_hdr, kHdrBytes + sizeof(AdvEntry) * n_tab, hipMemcpyHostToDevice, st);
-  hipError_t e = hipGraphLaunch(exec[parity], st);
+  launch_tick(this);
+  hipError_t e = hipGetLastError();
   parity ^= 1;
-  (void)hipMemcpyAsync(h_q, qcount, stat_bytes(cap_imgs), hipMemcpyDeviceToHost, st);
   hipError_t e2 = hipStreamSynchronize(st);
   return (e != hipSuccess || e2 != hipSuccess) ? DIST_EHIP : DIST_OK;
 }
@@ -481,8 +481,6 @@ void serve_shutdown(dist_ctx* ctx) {
   s->core->shutdown();
   (void)hipStreamSynchronize(s->st);
   s->core.reset();
-  for (int p = 0; p < 2; ++p)
-    if (s->exec[p]) (void)hipGraphExecDestroy(s->exec[p]);
   for (auto& kv : s->cache) ctx_free(ctx, kv.second, kv.first);
   if (s->mem) ctx_free(ctx, s->mem, s->mem_bytes);
   (void)hipHostFree(s->h_hdr);
