@@ -13,8 +13,9 @@
 //     then holds 4 consecutive output features of one ray, which the
 //     epilogue (bias, ReLU, rounding) writes back as one 8/16-byte chunk.
 //   * Layer 0 and the point columns of the skip layer are 3-wide products done
-//     in float32 on the vector ALUs; the latent part of both is folded into a
-//     per-latent bias once per call (z is constant for an image).
+//     in float32, on the matrix cores in tiles of one latent and on the vector
+//     ALUs in others (the same chain of roundings); the latent part of both is
+//     folded into a per-latent bias once per call (z is constant for an image).
 //   * The 1-wide output layer is a float32 dot product reduced across waves
 //     in a fixed order, then f = 0.5 (|p| - 0.5) + 0.05 tanh(m).
 #include "dist_internal.h"
