@@ -1792,7 +1792,7 @@ __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, lon
   const int tid = threadIdx.x;
   // stencil queries may keep their ReLU masks for the backward (the host
   // only asks for it when every stencil index fits an int)
-  const bool keep = P != kPrecBF16 && M > 16 && a.mode == 1 && a.mask_out != nullptr;
+  const bool keep = UNI && P != kPrecBF16 && M > 16 && a.mode == 1 && a.mask_out != nullptr;
   const int ntmax = a.net.kmax / 32;
   const MaskRef mk{a.mask_out, (a.net.nl - 1) * ntmax, ntmax, true};
   int lt = 0;
@@ -1802,7 +1802,7 @@ __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, lon
     int row = -1;
     if (tid < k) {
       row = (int)min(idx, (long long)INT_MAX);
-      if (a.mode == 0) {
+      if (!UNI || a.mode == 0) {
         p = make_float4(a.pts[3 * idx], a.pts[3 * idx + 1], a.pts[3 * idx + 2], 0.f);
         lt = min(max(a.lat[idx], 0), a.n_lat - 1);
       } else {
@@ -1845,12 +1845,12 @@ __device__ __forceinline__ void eval_tile(const EvalArgs& a, const Sm<P>& s, lon
 // UNI: tiles of one latent are looked for (one latent in all, or the stencil of
 // hits, which come image by image).  Points of several latents come in any
 // order, and their kernel is spared the second form of layer 0 (small decoder,
-// 524,288 points of three latents: 102 against 108 us).
+// 524,288 points of three latents: 102 against 108 us) and the stencil.
 template <int P, bool UNI>
 __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kFwdWaves<P> / 4, kFwdWaves<P> / 4))) void k_eval(EvalArgs a) {
   constexpr int M = Cfg<P>::M;
   Sm<P> s(dyn_smem, a.net.kmax);
-  const long long count = a.mode == 0 ? a.n : 6ll * (long long)(*a.hit_count);
+  const long long count = !UNI || a.mode == 0 ? a.n : 6ll * (long long)(*a.hit_count);
   const long long round = (long long)M * gridDim.x, full = count / round * round;
   for (long long base = (long long)blockIdx.x * M; base < full; base += round) eval_tile<P, M, UNI>(a, s, base, M);
   long long base, last;
@@ -1860,7 +1860,7 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
   while (base < last) {
     const int left = (int)min(last - base, (long long)M);
     int m = next_tile<P>(left);
-    if (m == 16 && a.mode == 1) m = 32;               // the masks of a stencil query need whole words
+    if (m == 16 && UNI && a.mode == 1) m = 32;        // the masks of a stencil query need whole words
     const int k = min(left, m);
     if (P == kPrecF32 && m == 16) eval_tile<P, P == kPrecF32 ? 16 : 32, UNI>(a, s, base, k);
     else if (m == 32) eval_tile<P, 32, UNI>(a, s, base, k);
