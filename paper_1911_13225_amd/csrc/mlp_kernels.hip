@@ -1428,19 +1428,20 @@ __device__ __forceinline__ int next_tile(int left) {
 }
 
 // Rows [first, last) of `count` (what full rounds of full tiles leave) that
-// this workgroup owns.  The rows are dealt
-// out in runs of the smallest tile, so that every workgroup has the same
-// number to one run; where the share leaves a rest that takes a full tile
-// anyway, in full tiles, so that some workgroups have none of the last round
-// and leave the others their bandwidth (bf16, 20,011 points: 79 us against
-// 83 us with 79 rows to every CU).
+// this workgroup owns.  The rows are dealt out in runs of the smallest tile, so
+// that every workgroup has the same number to one run; where the largest share
+// ends in a full tile anyway, in full tiles, so that some workgroups have none
+// of the last round and leave the others their bandwidth (bf16, 20,011 points:
+// 79 us against 83 us with 79 rows to every CU).  In 32 bits: fewer rows than
+// one round of full tiles, and 64-bit divisions took a microsecond of a call
+// that has no other tile.
 template <int P>
-__device__ __forceinline__ void row_share(long long count, long long& first, long long& last) {
-  constexpr int M = Cfg<P>::M;
-  const long long G = gridDim.x, runs = (count + kGranule<P> - 1) / kGranule<P>;
-  const int rest = (int)((runs + G - 1) / G * kGranule<P> % M);
-  const int g = rest && next_tile<P>(rest) == M ? M : kGranule<P>;
-  const long long t = (count + g - 1) / g;
+__device__ __forceinline__ void row_share(unsigned count, unsigned& first, unsigned& last) {
+  constexpr unsigned M = Cfg<P>::M;
+  const unsigned G = gridDim.x, runs = (count + kGranule<P> - 1) / kGranule<P>;
+  const unsigned rest = (runs + G - 1) / G * kGranule<P> % M;
+  const unsigned g = rest == 0 || next_tile<P>((int)rest) == (int)M ? M : kGranule<P>;
+  const unsigned t = (count + g - 1) / g;
   first = t * blockIdx.x / G * g;
   last = min(count, t * (blockIdx.x + 1) / G * g);
 }
@@ -1851,12 +1852,14 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
   constexpr int M = Cfg<P>::M;
   Sm<P> s(dyn_smem, a.net.kmax);
   const long long count = !UNI || a.mode == 0 ? a.n : 6ll * (long long)(*a.hit_count);
-  const long long round = (long long)M * gridDim.x, full = count / round * round;
+  const long long round = (long long)M * gridDim.x;
+  const long long full = count < round ? 0 : count <= INT_MAX ? (unsigned)count / (unsigned)round * round
+                                                              : count / round * round;
   for (long long base = (long long)blockIdx.x * M; base < full; base += round) eval_tile<P, M, UNI>(a, s, base, M);
-  long long base, last;
-  row_share<P>(count - full, base, last);
-  base += full;
-  last += full;
+  unsigned first, end;
+  row_share<P>((unsigned)(count - full), first, end);
+  long long base = full + first;
+  const long long last = full + end;
   while (base < last) {
     const int left = (int)min(last - base, (long long)M);
     int m = next_tile<P>(left);
