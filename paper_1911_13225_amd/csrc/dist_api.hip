@@ -96,6 +96,9 @@ int ctx_alloc(dist_ctx* ctx, void** p, size_t bytes) {
   if (e != hipSuccess) {
     std::lock_guard<std::mutex> lk(ctx->mem_mu);
     ctx->used -= bytes;
+    // the failure is reported here, and callers may go on without the memory:
+    // the runtime's own record of it would fail the next check of a launch
+    (void)hipGetLastError();
     return dist_set_error(DIST_EHIP, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
   }
   return DIST_OK;
