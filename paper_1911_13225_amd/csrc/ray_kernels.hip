@@ -596,28 +596,30 @@ __global__ __launch_bounds__(64) void k_cam_sum(const float* part, int B, float*
 constexpr int kFold = 64;
 
 // blockIdx.z: the column sums of one row group of layer 0 or of the skip layer
-// (the groups that the kernel did not write are left out).
+// (the groups that the kernel did not write are left out).  A latent's runs are
+// dealt to gridDim.x workgroups (see launch_gz_reduce).
 __global__ __launch_bounds__(512) void k_gz_fold(float* partial, int kmax, int tile, const int* seg_base,
                                                  const int* seg_padded, int lat0, int mg0) {
   const int l = lat0 + blockIdx.y;
   const int t0 = seg_base[l] / tile, nt = seg_padded[l] / tile;
-  const int c0 = blockIdx.x * kFold;
   const int i = threadIdx.x;
-  if (c0 >= nt || i >= kmax) return;
-  const int c1 = min(c0 + kFold, nt);
+  if (i >= kmax) return;
   const int width = 4 * kmax, z = blockIdx.z;
-  float* p = partial + (size_t)(t0 + c0) * width + (z < mg0 ? z : 2 + z - mg0) * kmax + i;
-  float a = 0.f;
-  int t = 0;
-  for (; t + 16 <= c1 - c0; t += 16) {
-    float v[16];
+  for (int c0 = blockIdx.x * kFold; c0 < nt; c0 += gridDim.x * kFold) {
+    const int c1 = min(c0 + kFold, nt);
+    float* p = partial + (size_t)(t0 + c0) * width + (z < mg0 ? z : 2 + z - mg0) * kmax + i;
+    float a = 0.f;
+    int t = 0;
+    for (; t + 16 <= c1 - c0; t += 16) {
+      float v[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = p[(size_t)(t + u) * width];
+      for (int u = 0; u < 16; ++u) v[u] = p[(size_t)(t + u) * width];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) a += v[u];
+      for (int u = 0; u < 16; ++u) a += v[u];
+    }
+    for (; t < c1 - c0; ++t) a += p[(size_t)t * width];
+    *p = a;
   }
-  for (; t < c1 - c0; ++t) a += p[(size_t)t * width];
-  *p = a;
 }
 
 // One workgroup per latent and 64 values of its gradient (blockIdx.y).  The
@@ -1326,8 +1328,14 @@ void launch_cam_reduce(const RayPool& pl, const ImgDesc* imgs, const int* img_vi
 void launch_gz_reduce(float* partial, int kmax, int tile, int max_tiles, const int* seg_base,
                       const int* seg_padded, int n_lat, int w0, int mg0, const float* W0z, int ws, int mgs,
                       const float* Wsz, int L, float* gz, hipStream_t s, int lat0, int accumulate) {
-  hipLaunchKernelGGL(k_gz_fold, dim3(nblk(max_tiles, kFold), n_lat, mg0 + (Wsz ? mgs : 0)), dim3(512), 0, s, partial,
-                     kmax, tile, seg_base, seg_padded, lat0, mg0);
+  // A latent may own every run of the list, but all of them together own one
+  // list: workgroups for every run of every latent are nearly all empty where
+  // the latents are many (200,000 samples of 60,000 latents: 117 M workgroups,
+  // 30 of 61 ms).  kFoldWgs in all, each over several runs if need be.
+  constexpr unsigned kFoldWgs = 16384;
+  const unsigned per_lat = std::min(nblk(max_tiles, kFold), std::max(1u, kFoldWgs / n_lat));
+  hipLaunchKernelGGL(k_gz_fold, dim3(per_lat, n_lat, mg0 + (Wsz ? mgs : 0)), dim3(512), 0, s, partial, kmax, tile,
+                     seg_base, seg_padded, lat0, mg0);
   hipLaunchKernelGGL(k_gz_reduce, dim3(n_lat, nblk(L, 64)), dim3(1024), 0, s, partial, kmax, tile, seg_base,
                      seg_padded, w0, mg0, W0z, ws, mgs, Wsz, L, gz, lat0, accumulate);
 }
