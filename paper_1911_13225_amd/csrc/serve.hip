@@ -452,6 +452,10 @@ int Server::tick(const std::vector<sched::TickEntry>& tab, int n_new) {
   }
   h_hdr[0] = n_tab;
   h_hdr[1] = n_new;
+  // the record of the last error is the thread's, and the calls that admit and
+  // complete single requests leave theirs in it: only this tick's launches end
+  // every running request
+  (void)hipGetLastError();
   launch_tick(this);
   hipError_t e = hipGetLastError();
   parity ^= 1;
