@@ -96,6 +96,10 @@ struct TickEntry {
   int img, lvl, step, split, begin, count;
 };
 
+// Marching steps of one tick: what lies between two coarse-to-fine splits, so
+// that the splits fall between ticks and a coarse ray lives for one tick.
+constexpr int kStepsPerTick = 3;
+
 struct Backend {
   virtual ~Backend() = default;
   // device buffers of a job beyond its pooled slots (charged against the
@@ -105,11 +109,9 @@ struct Backend {
   // the job holds its ray slots, image slots and latent: descriptors,
   // latent code, optimiser state, first render
   virtual void begin(Job* j) = 0;
-  // marching steps of one tick: 1 or 3 (the coarse-to-fine splits, every third
-  // step, fall between ticks)
-  virtual int steps_per_tick() const { return 1; }
-  // one tick: start the table's rays, march every pooled active ray, and
-  // make active(img) / queries(img) current; DIST_OK or an error code
+  // one tick: start the table's rays, march every pooled active ray by up to
+  // kStepsPerTick steps, and make active(img) / queries(img) current; DIST_OK or
+  // an error code
   virtual int tick(const std::vector<TickEntry>& table, int n_new) = 0;
   virtual int active(int img) const = 0;
   virtual int64_t queries(int img) const = 0;
@@ -304,7 +306,7 @@ class Core {
       // progress and completion
       std::vector<Job*> keep;
       for (Job* j : running_) {
-        j->step += be_->steps_per_tick();
+        j->step += kStepsPerTick;
         bool all = true;
         for (int v = 0; v < j->n_views; ++v) {
           if (!j->img_done[v]) {

@@ -94,7 +94,6 @@ struct Server : sched::Backend {
   bool acquire(sched::Job* j) override;
   void release(sched::Job* j) override;
   void begin(sched::Job* j) override;
-  int steps_per_tick() const override { return 3; }
   int tick(const std::vector<sched::TickEntry>& table, int n_new) override;
   int active(int img) const override { return h_active[img]; }
   int64_t queries(int img) const override { return (int64_t)h_q[img]; }
@@ -210,7 +209,7 @@ static void launch_tick(Server* s) {
   ma.list = s->lists[cur];
   ma.count = s->count[cur];
   ma.claim = s->claim;
-  ma.n_end = s->steps_per_tick();
+  ma.n_end = sched::kStepsPerTick;
   ma.alpha = 1.5f;
   ma.qcount = s->qcount;          // queries counted where they are made
   ma.ecount = s->ecount;          // and non-finite ones
