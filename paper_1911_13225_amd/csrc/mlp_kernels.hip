@@ -2190,7 +2190,7 @@ void launch_theta_rows(int precision, const float4* pts, const int* lat, const f
 // 8 slices of any length, where one launch per layer needed slices of 2,048
 // rows.  A partial holds every weight in float32, so fewer slices also mean
 // fewer partials to write and to add up (7.3 MB each).  60,007 samples, bf16:
-// contraction 533 -> 355 us (620 TFLOP/s), adding up the partials 138 -> 14 us.
+// contraction 533 -> 354 us (620 TFLOP/s), adding up the partials 138 -> 14 us.
 // input feature k: its rows of block 0 and the block stride (elements)
 __device__ __forceinline__ const char* dw_feature(const DwX& x, int k, int es, int& bstride) {
   const void* b = x.p[0];
@@ -2237,6 +2237,10 @@ __device__ __forceinline__ void dw_put(const DwArgs& a, bool acc, float* P, int 
 // column also sum the staged Delta rows: the bias column (k_in) of the
 // partial.  Features past n_out or kcols are clamped to the last one and
 // their outputs dropped.
+//   The float32 sums run over kDwRunBlocks blocks (1,920 rows) at a time and
+// those are added up, however long the slice (up to 8,192 rows): a longer sum
+// loses small terms behind a large one.
+constexpr int kDwRunBlocks = 30;
 __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwBatch batch) {
   bf16* lds = (bf16*)dyn_smem;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63, ln = lane & 31, g = lane >> 5;
@@ -2261,10 +2265,12 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwBatch batch) {
   }
   const bool bias = k0 == 0 && a.bias;
   float bs[4] = {0.f, 0.f, 0.f, 0.f};
-  // three register sets: the loads of blocks b + 2 and b + 3 are in flight
-  // while block b is multiplied from LDS and block b + 1 is staged (HBM
-  // latency under load needs about that many bytes in flight per CU)
-  constexpr int NS = 3;
+  // two register sets: the loads of block b + 2 are in flight while block b is
+  // multiplied from LDS and block b + 1 is staged.  A third set would be 2%
+  // faster, but the totals take its registers (with both, 53 registers spill:
+  // 60,007 samples 346 us with three sets and no totals, 392 with three and
+  // totals, 354 with two and totals)
+  constexpr int NS = 2;
   bf16x8 ra[NS][4], rx[NS][4];
   auto gload = [&](int set, int blk) {
 #pragma unroll
@@ -2288,11 +2294,28 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwBatch batch) {
         for (int e = 0; e < 8; ++e) bs[i] += (float)ra[set][i][e];
     }
   };
-  f32x16 acc[2][2];
+  f32x16 acc[2][2], tot[2][2];
+  float bt[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < 2; ++j) acc[i][j] = tot[i][j] = f32x16{};
+  // the sums so far join the total, and new ones begin
+  auto sub_total = [&]() {
+    mfma_drain();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        tot[i][j] += acc[i][j];
+        acc[i][j] = f32x16{};
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bt[i] += bs[i];
+      bs[i] = 0.f;
+    }
+  };
   const int wn = wave & 1, wk = wave >> 1;
   auto mma = [&](int buf) {
     const bf16* A = lds + (size_t)buf * 2 * 128 * kDwLd;
@@ -2330,14 +2353,19 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwBatch batch) {
   stage(0, 0);
   __syncthreads();
   int blk = 0;
-  for (; blk + 6 <= nblk; blk += 6) {
+  for (int run = 0; blk + 6 <= nblk; blk += 6) {
 #pragma unroll
     for (int u = 0; u < 6; ++u) step(blk + u, u % NS, u & 1);
+    run += 6;
+    if (run + 6 > kDwRunBlocks) {
+      sub_total();
+      run = 0;
+    }
   }
 #pragma unroll
   for (int u = 0; u < 6; ++u)                     // the last nblk % 6 blocks (register sets indexed statically)
     if (blk + u < nblk) step(blk + u, u % NS, u & 1);
-  mfma_drain();
+  sub_total();
   float* P = a.P + (size_t)slice * a.n_out * a.ldp;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -2348,12 +2376,12 @@ __global__ __launch_bounds__(256, 2) void k_dw_bf16(DwBatch batch) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = n0 + 64 * wn + 32 * i + 8 * q + 4 * g + e, k = k0 + 64 * wk + 32 * j + ln;
-          if (n < a.n_out && k < a.kcols) dw_put(a, batch.acc, P, n, k, acc[i][j][4 * q + e]);
+          if (n < a.n_out && k < a.kcols) dw_put(a, batch.acc, P, n, k, tot[i][j][4 * q + e]);
         }
   if (bias) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float x = bs[i];
+      float x = bt[i];
       x += __shfl_xor(x, 1);
       x += __shfl_xor(x, 2);
       x += __shfl_xor(x, 4);
