@@ -232,16 +232,21 @@ int dist_render_bwd_camera(dist_ctx* ctx, const dist_saved* saved,
  * residual term (d = t + f at the last query), the silhouette through the
  * minimum-|f| query (dS/dz = sign f df/dz).  A child ray of the coarse-to-fine
  * split passes its dt to its parent unless the clamp into its own unit-sphere
- * interval bound.  Computed in reverse over the marching steps: at each step
- * the decoder is re-evaluated at every ray's point of that step (the
- * recompute of App. B.2) and back-propagated, costing about two decoder
- * passes per march query.
+ * interval bound.  The decoder is re-evaluated at every ray's point of every
+ * step (the recompute of App. B.2) and back-propagated, costing about two
+ * decoder passes per march query; only the scalar adjoint of t runs in reverse
+ * over the marching steps, so several steps share a launch.  The memory for
+ * that (up to 512 MB or one step, if that is more) is one block per context,
+ * taken if there is room for it and given back when another allocation of the
+ * context finds none; without it, and under graph capture, fewer steps share a
+ * launch and the result is the same.
  *   saved    from dist_render_fwd with keep_history = 1 (DIST_EINVAL
  *            otherwise)
  *   g_depth, g_sil  device [n_images][H][W] (either may be NULL = zero)
  *   g_z      device [n_latents, latent_dim]; overwritten
- * Normal terms are not part of this gradient.  The reduction order is fixed,
- * so results are bitwise reproducible. */
+ * Normal terms are not part of this gradient.  The reduction order is fixed and
+ * depends neither on the memory at hand nor on the images of other latents, so
+ * results are bitwise reproducible. */
 int dist_render_bwd_unrolled(dist_ctx* ctx, const dist_saved* saved,
                              const float* g_depth, const float* g_sil,
                              float* g_z, void* stream);
@@ -450,8 +455,9 @@ int dist_poll(dist_ctx* ctx, uint64_t ticket, dist_result* res, int64_t timeout_
  * number of launches and their summed duration since timing was enabled.
  * kernel: 0 = march (one launch per coarse-to-fine level), 1 = plain decoder queries
  * (normals, dist_sdf_eval), 2 = adjoint (backward recompute + VJP),
- * 3 = VJP of the normal-stencil samples from the ReLU masks the forward
- * saved (no recompute), 4 = weight-gradient contraction over the captured
+ * 3 = VJP of samples from saved ReLU masks, without the recompute (normal
+ * stencils; unrolled steps that share a launch without the memory block),
+ * 4 = weight-gradient contraction over the captured
  * rows (one launch per chunk, all layers; rows are not counted). */
 typedef struct {
   int64_t launches;

@@ -76,14 +76,29 @@ struct GroupSpace {
   void* temp = nullptr;
 };
 
-// Rows of a group of steps of the unrolled gradient: delta at layer 0 and the
-// skip layer, and the row factor.
-struct UlRows {
+// Plan of the gradient through the unrolled march (see UlLevel in
+// ray_kernels.h): per ray, segment, step and chunk, and the column sums.
+struct UlTab {
   char* mem = nullptr;
   size_t bytes = 0;
-  long long cap = 0;
-  float* delta = nullptr;
-  float* gm = nullptr;
+  uint8_t* top = nullptr;
+  int *off = nullptr, *seg_rays = nullptr, *seg_base = nullptr;
+  int *step_tiles = nullptr, *step_base = nullptr;
+  int4* chunk = nullptr;
+  int *img_slot = nullptr, *slot_lat = nullptr;
+  double* sums = nullptr;
+};
+
+// Buffers of a chunk of steps of that gradient.  One block per context, shared
+// by its calls (ordered by the event `done`), and given back whenever another
+// allocation of the context finds no memory (ctx_alloc): without it the calls
+// take shorter chunks, in the buffers of a single step.
+struct UlShared {
+  std::mutex mu;                   // held while a call launches work on the block
+  char* mem = nullptr;
+  size_t bytes = 0;
+  hipEvent_t done = nullptr;
+  bool used = false;               // done has been recorded
 };
 
 struct UnrollSpace {
@@ -117,7 +132,7 @@ struct Workspace {
   NrmSave* ns = nullptr;
   CamSpace* cs = nullptr;
   UnrollSpace* us = nullptr;
-  UlRows* ur = nullptr;
+  UlTab* ut = nullptr;
   // pinned staging of the per-call descriptors
   char* h_stage = nullptr;
   hipEvent_t staged = nullptr;
@@ -165,6 +180,7 @@ struct dist_ctx {
   std::vector<int> out_dims, in_dims, wpad, kpad;
   size_t budget = 0, used = 0;
   std::mutex mem_mu;
+  UlShared ul;
   std::vector<std::pair<void*, size_t>> owned;
   std::vector<float*> Wf, bf;            // float32 master copies [out][in], [out]
   std::vector<float*> bias_pad;          // padded hidden biases

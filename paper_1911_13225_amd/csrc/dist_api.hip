@@ -83,7 +83,7 @@ extern "C" const char* dist_version(void) { return "dist-mi355x 0.1 (gfx950)"; }
 // ---------------------------------------------------------------------------
 static int pad_width(int w) { return w <= 128 ? 128 : (w <= 256 ? 256 : 512); }
 
-int ctx_alloc(dist_ctx* ctx, void** p, size_t bytes) {
+static int alloc_once(dist_ctx* ctx, void** p, size_t bytes) {
   bytes = (bytes + 255) & ~(size_t)255;
   {
     std::lock_guard<std::mutex> lk(ctx->mem_mu);
@@ -102,6 +102,26 @@ int ctx_alloc(dist_ctx* ctx, void** p, size_t bytes) {
     return dist_set_error(DIST_EHIP, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
   }
   return DIST_OK;
+}
+
+// Give the shared block of the unrolled gradient back (its lock is held).
+static void ul_release(dist_ctx* ctx) {
+  UlShared& u = ctx->ul;
+  if (u.used) (void)hipEventSynchronize(u.done);
+  ctx_free(ctx, u.mem, u.bytes);
+  u.mem = nullptr;
+  u.bytes = 0;
+}
+
+int ctx_alloc(dist_ctx* ctx, void** p, size_t bytes) {
+  const int rc = alloc_once(ctx, p, bytes);
+  if (rc == DIST_OK) return rc;
+  {
+    std::unique_lock<std::mutex> lk(ctx->ul.mu, std::try_to_lock);   // (a call that launches on it keeps it)
+    if (!lk || !ctx->ul.mem) return rc;
+    ul_release(ctx);
+  }
+  return alloc_once(ctx, p, bytes);
 }
 
 void ctx_free(dist_ctx* ctx, void* p, size_t bytes) {
@@ -330,6 +350,8 @@ extern "C" int dist_destroy(dist_ctx* ctx) {
     ctx_free(ctx, ctx->theta->mem, ctx->theta->bytes);
     delete ctx->theta;
   }
+  ul_release(ctx);
+  if (ctx->ul.done) (void)hipEventDestroy(ctx->ul.done);
   for (auto& o : ctx->owned) ctx_free(ctx, o.first, o.second);
   delete ctx;
   return DIST_OK;
@@ -532,9 +554,9 @@ static void ws_destroy(dist_ctx* ctx, Workspace* w) {
     ctx_free(ctx, w->gs->mem, w->gs->bytes);
     delete w->gs;
   }
-  if (w->ur) {
-    ctx_free(ctx, w->ur->mem, w->ur->bytes);
-    delete w->ur;
+  if (w->ut) {
+    ctx_free(ctx, w->ut->mem, w->ut->bytes);
+    delete w->ut;
   }
   delete w;
 }
@@ -659,23 +681,44 @@ static int us_get(dist_ctx* ctx, Workspace* w, long long cap_lam, int steps) {
   return DIST_OK;
 }
 
-// Rows of cap samples, dw delta floats each, of a group of unrolled steps.
-static int ur_get(dist_ctx* ctx, Workspace* w, long long cap, int dw) {
-  if (w->ur && w->ur->cap >= cap) return DIST_OK;
-  if (w->ur) {
-    ctx_free(ctx, w->ur->mem, w->ur->bytes);
-    delete w->ur;
-    w->ur = nullptr;
+// Plan of the unrolled gradient of n_img images of hw rays at up to S steps of a
+// level, n_slot distinct latents: some 2 bytes per ray and 32 KB per latent (kmax 512).
+static int ut_get(dist_ctx* ctx, Workspace* w, int n_img, int hw, int S, int n_slot) {
+  const size_t blocks = (size_t)n_img * ((hw + 255) / 256);
+  UlTab t;
+  Carver c;
+  auto layout = [&] {
+    t.top = c.take<uint8_t>((size_t)n_img * hw);
+    t.off = c.take<int>((size_t)S * blocks);
+    t.seg_rays = c.take<int>((size_t)S * n_slot);
+    t.seg_base = c.take<int>((size_t)S * n_slot);
+    t.step_tiles = c.take<int>(S);
+    t.step_base = c.take<int>(S);
+    t.chunk = c.take<int4>(S);
+    t.img_slot = c.take<int>(n_img);
+    t.slot_lat = c.take<int>(n_slot);
+    t.sums = c.take<double>((size_t)n_slot * kUlChains * 2 * ctx->kmax);
+  };
+  layout();
+  const size_t need = c.off + 256;
+  if (!w->ut || w->ut->bytes < need) {
+    if (w->ut) {
+      ctx_free(ctx, w->ut->mem, w->ut->bytes);
+      delete w->ut;
+      w->ut = nullptr;
+    }
+    void* p = nullptr;
+    int rc = ctx_alloc(ctx, &p, need);
+    if (rc != DIST_OK) return rc;
+    w->ut = new UlTab();
+    w->ut->mem = (char*)p;
+    w->ut->bytes = need;
   }
-  UlRows* u = new UlRows();
-  u->cap = cap;
-  const size_t db = (size_t)cap * dw * sizeof(float);
-  u->bytes = db + (size_t)cap * sizeof(float) + 256;
-  int rc = ctx_alloc(ctx, (void**)&u->mem, u->bytes);
-  if (rc != DIST_OK) { delete u; return rc; }
-  u->delta = (float*)u->mem;
-  u->gm = (float*)(u->mem + db);
-  w->ur = u;
+  t.mem = c.base = w->ut->mem;
+  t.bytes = w->ut->bytes;
+  c.off = 0;
+  layout();
+  *w->ut = t;
   return DIST_OK;
 }
 
@@ -1436,11 +1479,70 @@ extern "C" int dist_render_bwd_camera(dist_ctx* ctx, const dist_saved* saved, co
   return DIST_OK;
 }
 
-// Samples a group of unrolled steps may hold (4 KB of delta rows each for the
-// DeepSDF decoder), and the fewest steps it is made for: from 512 K pixels on a
-// step fills the chip by itself (eight images of 256^2: 16.3 ms step by step).
-static constexpr long long kUlGroupSamples = 1 << 19;
-static constexpr int kUlMinSteps = 2;
+// Where the unrolled gradient's samples, partials and, per sample of a chunk of
+// several steps, 1 - tanh^2 and either a row of delta or the masks go.
+struct UlBuf {
+  float4* samples;
+  int* sample_lat;
+  float *gp, *partial;
+  unsigned* mask_ws;               // per workgroup
+  float *dtanh, *delta;
+  unsigned* mask;
+};
+// The shared block's samples of a chunk of several steps keep rows of delta
+// (4.3 KB per sample in all for the DeepSDF decoder: 118,000 samples), and the
+// column sums are made from them.  Masks and a second VJP, as in the buffers of
+// a step, take an eighth of the memory and longer: two images of 96^2, bfloat16
+// 1.28 against 1.19 ms, float32 5.8 against 4.1 ms.
+static constexpr size_t kUlBytes = (size_t)512 << 20;
+// A step of so many multiply-adds of one VJP is a chunk of its own (1,024 tiles
+// of the DeepSDF decoder, four rounds of the chip): a second VJP of its tiles
+// would take longer than the launches around a chunk and a partly filled round.
+static constexpr double kUlBigMacs = 1024.0 * 7 * 512 * 512;
+
+// The context's shared block, carved for `cap` samples and `chunk` rows of delta
+// of dw floats; the lock stays held.  False if there is no memory for it, or if
+// the stream is being captured (a graph outlives the call, the block need not).
+static bool ul_shared(dist_ctx* ctx, hipStream_t st, std::unique_lock<std::mutex>& lk, size_t cap, size_t chunk,
+                      int tile, size_t mask_ws, size_t dw, UlBuf& u) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (cs != hipStreamCaptureStatusNone) return false;
+  UlShared& s = ctx->ul;
+  lk = std::unique_lock<std::mutex>(s.mu);
+  Carver c;
+  auto layout = [&] {
+    u.samples = c.take<float4>(cap);
+    u.sample_lat = c.take<int>(cap);
+    u.gp = c.take<float>(cap * 3 * kGpSlots);
+    u.partial = c.take<float>((cap / tile + 1) * 4 * ctx->kmax);
+    u.mask_ws = c.take<unsigned>(mask_ws);
+    u.dtanh = c.take<float>(chunk);
+    u.delta = c.take<float>(chunk * dw);
+  };
+  layout();
+  const size_t need = c.off + 256;
+  bool ok = s.done || hipEventCreateWithFlags(&s.done, hipEventDisableTiming) == hipSuccess;
+  if (ok && s.bytes < need) {
+    ul_release(ctx);
+    ok = alloc_once(ctx, (void**)&s.mem, need) == DIST_OK;
+    if (ok) s.bytes = need;
+    else s.mem = nullptr;
+  }
+  ok = ok && (!s.used || hipStreamWaitEvent(st, s.done, 0) == hipSuccess);
+  if (!ok) {
+    lk.unlock();
+    (void)hipGetLastError();
+    return false;
+  }
+  c.base = s.mem;
+  c.off = 0;
+  layout();
+  return true;
+}
 
 extern "C" int dist_render_bwd_unrolled(dist_ctx* ctx, const dist_saved* saved, const float* g_depth,
                                         const float* g_sil, float* g_z, void* stream) {
@@ -1453,98 +1555,123 @@ extern "C" int dist_render_bwd_unrolled(dist_ctx* ctx, const dist_saved* saved, 
   const int tile = adj_tile_rows(prec);
   const int n_img = saved->n_img, hw = saved->hw, n_lat = saved->n_lat;
   const int Lv = saved->prm.c2f_levels, steps = saved->prm.max_steps;
-  // one sample per ray of the step's level at most, padded per latent
-  const long long rays = (long long)n_img * hw, pad = (long long)n_lat * tile;
-  long long cap = rays + pad;
+  const int S0 = steps - 3 * Lv, S = std::max(S0, Lv > 0 ? 3 : 0);
+  int n_slot = 1;                              // distinct latents of the images
+  for (int i = 1; i < n_img; ++i)
+    n_slot += saved->img_latent[saved->order[i]] != saved->img_latent[saved->order[i - 1]];
+  // the buffers of one step: a sample per ray of it at most, padded per latent
+  const long long cap = (long long)n_img * hw + (long long)n_lat * tile;
   if (cap > (1LL << 31) - 1) return dist_set_error(DIST_EINVAL, "too many gradient samples");
   const int bpi = (hw + 255) / 256;
-  const int w0 = ctx->wpad[0];
-  const int ws = ctx->skip >= 0 ? ctx->wpad[ctx->skip] : 0;
-  // several steps at once, as many as the group's rows allow; without the
-  // memory for them (the context's budget), or for images so large that a step
-  // fills the chip by itself, step by step
-  int per = (int)std::min<long long>(kUlGroupSamples / rays, steps - 3 * Lv);
-  bool group = per >= kUlMinSteps;
   const size_t mw = adj_mask_words(prec, ctx->net[prec]);
-  int rc = DIST_OK;
-  if (group) {
-    const long long gcap = per * rays + pad;
-    rc = bw_get(ctx, w, (int)gcap, n_img * bpi, n_lat, tile, mw * mlp_grid(ctx, gcap, prec));
-    if (!rc) rc = cs_get(ctx, w, gcap);
-    if (!rc) rc = ur_get(ctx, w, gcap, w0 + ws);
-    if (!rc) {
-      cap = gcap;
-    } else {
-      // give back what the group was to use and take what a step needs
-      group = false;
-      if (w->bw) { ctx_free(ctx, w->bw->mem, w->bw->bytes); delete w->bw; w->bw = nullptr; }
-      if (w->cs) { ctx_free(ctx, w->cs->mem, w->cs->bytes); delete w->cs; w->cs = nullptr; }
-    }
-  }
-  if (!group) {
-    rc = bw_get(ctx, w, (int)cap, n_img * bpi, n_lat, tile, mw * mlp_grid(ctx, cap, prec));
-    if (!rc) rc = cs_get(ctx, w, cap);
-    if (rc) return rc;
-  }
-  const int grid = mlp_grid(ctx, cap, prec);
+  int rc = bw_get(ctx, w, (int)cap, n_img * bpi, n_lat, tile, mw * mlp_grid(ctx, cap, prec));
+  if (!rc) rc = cs_get(ctx, w, cap);
+  if (!rc) rc = ut_get(ctx, w, n_img, hw, S, n_slot);
+  if (rc) return rc;
   BwdSpace* b = w->bw;
   UnrollSpace* u = w->us;
+  const UlTab& t = *w->ut;
+  // a step has at most t1 tiles at level 0; a chunk of several takes as many as
+  // the shared block holds
+  auto step_tiles = [&](int lv) { return ((long long)n_img * (hw >> (2 * lv)) + (long long)n_slot * (tile - 1)) / tile; };
+  const long long t1 = step_tiles(0);
+  const size_t mwords = (size_t)(ctx->nl - 1) * (ctx->net[prec].kmax / 32);
+  const size_t row_bytes = sizeof(float4) + sizeof(int) + 3 * kGpSlots * sizeof(float) + 4 * ctx->kmax * sizeof(float) / tile;
+  const int w0 = ctx->wpad[0];
+  const int ws = ctx->skip >= 0 ? ctx->wpad[ctx->skip] : 0;
+  long long chunk = std::min<long long>(kUlBytes / (row_bytes + 4 * (w0 + ws + 1)) / tile, S0 * t1);
+  UlBuf buf{};
+  std::unique_lock<std::mutex> lk;
+  const bool shared = ul_shared(ctx, st, lk, (size_t)std::max(chunk, t1) * tile, (size_t)chunk * tile, tile,
+                                mw * ctx->n_cu, w0 + ws, buf);
+  if (!shared) {
+    // the buffers of a step; the masks take the column sums of the second sample
+    // list, which this call has no other use for
+    const size_t p2 = (size_t)(b->cap_samples / tile + 1) * 4 * kMaxWidth * sizeof(float);
+    const long long rows = std::min<long long>(b->cap_samples, w->cs->cap_samples);
+    chunk = std::min<long long>(p2 / (tile * (4 * mwords + 4)), rows / tile);
+    buf = UlBuf{b->samples, b->sample_lat, w->cs->gp, b->partial, b->mask_ws, nullptr, nullptr, (unsigned*)b->partial2};
+    buf.dtanh = (float*)(buf.mask + (size_t)chunk * tile * mwords);
+  }
+  const int max_grid = shared ? ctx->n_cu : (int)std::min<size_t>(ctx->n_cu, b->mask_words / mw);
+  double macs = 0.0;
+  for (int l = 1; l <= ctx->nl - 2; ++l) macs += (double)ctx->wpad[l] * ctx->kpad[l];
+  const UlChunks ck{(int)std::min<long long>((long long)(kUlBigMacs / macs), (chunk + 1) / 2), (int)chunk};
   const int spi = slots_per_image(hw, Lv);
-  hipLaunchKernelGGL(k_fill_f32, dim3(64), dim3(256), 0, st, g_z, (long long)n_lat * ctx->L);
-  launch_ul_init(w->pool, w->imgs, n_img, spi, g_depth, u->lam, st);
+  launch_ul_init(w->pool, w->imgs, n_img, spi, g_depth, u->lam, t.sums, (long long)n_slot * kUlChains * 2 * ctx->kmax, st);
+  launch_ul_slots(w->img_order, w->img_latent, n_img, t.img_slot, t.slot_lat, st);
   AdjArgs aa{};
   aa.net = ctx->net[prec];
   aa.bias0_lat = w->bias0_lat;
   aa.biasS_lat = w->biasS_lat;
-  aa.samples = b->samples;
-  aa.sample_lat = b->sample_lat;
-  aa.n_samples = b->n_samples;
-  aa.mask_ws = b->mask_ws;
-  aa.partial = b->partial;
-  aa.gp_part = w->cs->gp;
-  if (group) {
-    aa.delta_out = w->ur->delta;
-    aa.gm_out = w->ur->gm;
-  }
-  auto reduce = [&](int mg0, int mgs) {
-    launch_gz_reduce(b->partial, ctx->kmax, tile, (int)(cap / tile) + 1, b->seg_base, b->seg_padded, n_lat, w0, mg0,
-                     ctx->w0z, ws, mgs, ctx->skip >= 0 ? ctx->wsz : nullptr, ctx->L, g_z, st, 0, 1);
-  };
-  auto steps_of = [&](int lv, int s0, int s1) {
-    return UlGroup{s0, s1, lv, g_depth, g_sil, u->t_hist, (size_t)w->pool.cap, u->lam};
-  };
-  // in reverse over the levels; after the split that follows a level's last
+  aa.samples = buf.samples;
+  aa.sample_lat = buf.sample_lat;
+  aa.mask_ws = buf.mask_ws;
+  aa.partial = buf.partial;
+  aa.gp_part = buf.gp;
+  aa.smask = aa.mask_out = buf.mask;
+  aa.sdtanh = aa.dtanh_out = buf.dtanh;
+  aa.delta_out = buf.delta;
+  const UlSums sum{buf.partial, ctx->kmax, w0, groups_s0(ctx, adjoint_waves()), ws, groups_skip(ctx, adjoint_waves()),
+                   t.sums};
+  // in reverse over the levels; through the split that follows a level's last
   // step, the children's adjoints flow to their parents
   for (int lv = 0; lv <= Lv; ++lv) {
-    const int first = 3 * (Lv - lv), last = lv == 0 ? steps - 1 : first + 2;     // the level's steps
     const int nr = hw >> (2 * lv);
-    if (lv > 0) launch_ul_split(w->pool, w->imgs, w->img_order, n_img, nr, lv, u->lam, st);
-    for (int s1 = last; s1 >= first; s1 -= group ? per : 1) {
-      if (group) {
-        const UlGroup in = steps_of(lv, std::max(first, s1 - per + 1), s1);
-        launch_ulg_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, nr, n_lat, tile, in, b->bsum, b->boff,
-                           b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, b->sample_lat, st);
-      } else {
-        const UlIn in{s1, lv, g_depth, g_sil, u->t_hist + (size_t)s1 * w->pool.cap, u->lam};
-        launch_ul_samples(w->pool, w->imgs, w->img_order, w->img_latent, n_img, nr, n_lat, tile, in, b->bsum, b->boff,
-                          b->seg_base, b->seg_total, b->seg_padded, b->n_samples, b->samples, b->sample_lat,
-                          w->cs->sample_cam, st);
-      }
+    UlLevel L{};
+    L.lvl = lv;
+    L.first = 3 * (Lv - lv);
+    L.S = lv == 0 ? S0 : 3;
+    L.n_img = n_img;
+    L.blk = (nr + 255) / 256;
+    L.n_slot = n_slot;
+    L.g_depth = g_depth;
+    L.g_sil = g_sil;
+    L.t_hist = u->t_hist;
+    L.t_stride = (size_t)w->pool.cap;
+    L.lam = u->lam;
+    L.img_slot = t.img_slot;
+    L.slot_lat = t.slot_lat;
+    L.top = t.top;
+    L.off = t.off;
+    L.seg_rays = t.seg_rays;
+    L.seg_base = t.seg_base;
+    L.step_tiles = t.step_tiles;
+    L.step_base = t.step_base;
+    L.chunk = t.chunk;
+    const long long tl = step_tiles(lv);
+    const int rounds = ul_rounds(L.S, tl, ck);
+    const int grid = (int)std::min<long long>(std::max(tl, std::min(chunk, tl * L.S)), max_grid);
+    launch_ul_plan(w->pool, w->imgs, w->img_order, L, tile, ck, rounds, st);
+    for (int c = 0; c <= rounds; ++c) {
+      launch_ul_step(w->pool, w->imgs, w->img_order, L, c < rounds ? t.chunk + c : nullptr,
+                     c > 0 ? t.chunk + c - 1 : nullptr, tile, buf.samples, buf.sample_lat, b->n_samples, sum, st);
+      if (c == rounds) break;
+      aa.chunk = t.chunk + c;
+      aa.n_samples = b->n_samples;
       {
-        TimedLaunch tl(ctx, 2, st, b->n_samples, 1);
+        TimedLaunch time(ctx, 2, st, aa.n_samples, 1);
         launch_adjoint(prec, aa, grid, st);
       }
-      if (group) {
-        const UlGroup in = steps_of(lv, std::max(first, s1 - per + 1), s1);
-        launch_ulg_lambda(w->pool, w->imgs, w->img_order, n_img, nr, in, b->boff, b->samples, w->cs->gp, w->ur->gm,
-                          st);
-        launch_ul_colsum(w->ur->delta, w->ur->gm, b->n_samples, (int)cap, w0, ws, ctx->kmax, b->partial, st);
-        reduce(1, 1);
+      launch_ul_lambda(w->pool, w->imgs, w->img_order, L, aa.chunk, tile, buf.samples, buf.gp, st);
+      if (chunk <= 2 || L.S == 1) continue;
+      // a chunk of several steps: its column sums, now that the seeds are known
+      if (buf.delta) {
+        launch_ul_colsum(aa.chunk, (int)chunk, buf.delta, buf.samples, buf.dtanh, buf.partial, ctx->kmax, w0, sum.mg0,
+                         ws, sum.mgs, st);
       } else {
-        reduce(groups_s0(ctx, adjoint_waves()), groups_skip(ctx, adjoint_waves()));
-        launch_ul_lambda(w->pool, b->samples, w->cs->sample_cam, w->cs->gp, b->n_samples, (int)cap, u->lam, st);
+        aa.n_samples = b->n_samples + 1;
+        TimedLaunch time(ctx, 3, st, aa.n_samples, 1);
+        launch_vjp_again(prec, aa, grid, st);
       }
     }
+  }
+  launch_ul_total(t.slot_lat, n_slot, n_lat, tile, t.sums, ctx->kmax, buf.partial, b->seg_base, b->seg_padded, st);
+  launch_gz_reduce(buf.partial, ctx->kmax, tile, 1, b->seg_base, b->seg_padded, n_lat, w0, 1, ctx->w0z, ws, 1,
+                   ctx->skip >= 0 ? ctx->wsz : nullptr, ctx->L, g_z, st);
+  if (shared) {
+    HIPCHK(hipEventRecord(ctx->ul.done, st));
+    ctx->ul.used = true;
   }
   HIPCHK(hipGetLastError());
   return DIST_OK;

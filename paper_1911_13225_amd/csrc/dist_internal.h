@@ -159,7 +159,8 @@ struct AdjArgs {
   int cap_rows;                    // rows of the capture chunk (element l kmax cap_rows + (row / 64 kmax + n) 64 + row % 64)
   // VJP from saved masks (k_vjp_saved): samples [n_begin[0], n_samples[0]),
   // each with its stencil index in sample_idx; masks and 1 - tanh^2 as
-  // written by the forward's stencil queries
+  // written by the forward's stencil queries (n_begin null: from 0; sample_idx
+  // null: a sample's index is its own)
   const int* n_begin;
   const int* sample_idx;
   const unsigned* smask;
@@ -169,11 +170,16 @@ struct AdjArgs {
   // [sample][kGpSlots][3] (the spatial gradient of m, weighted by the row's
   // factor; slots beyond a layer's wave count hold zeros)
   float* gp_part;
-  // k_adjoint, optional, in place of the column sums: every row's delta at
-  // layer 0 and at the skip layer, [sample][wpad 0 + wpad skip], and its factor
-  // gm, for column sums weighted later (k_ul_colsum)
+  // gradient through the unrolled march (optional): the samples are a chunk of
+  // marching steps (see UlLevel), chunk->w set if they are several.  Then the
+  // seeds are 1, and instead of making column sums k_adjoint keeps 1 - tanh^2
+  // and either the masks of the samples (in the layout of smask and sdtanh) or,
+  // with delta_out, their rows of delta at layer 0 and at the skip layer
+  // [sample][wpad 0 + wpad skip].  gp_part is in any case that of unit seeds.
+  const int4* chunk;
+  unsigned* mask_out;
+  float* dtanh_out;
   float* delta_out;
-  float* gm_out;
   // colour network (k_color_adjoint): per sample dL/d(colour), (r, g, b, 0)
   const float4* cseed;
 };
@@ -248,6 +254,8 @@ int mlp_row_groups(int waves, int width);
 int adjoint_waves();                       // recompute-and-VJP kernel
 int vjp_saved_waves(int precision);        // VJP from saved masks
 void launch_vjp_saved(int precision, const AdjArgs& a, int grid, hipStream_t s);
+// the same with the tiles, waves and column sums of launch_adjoint (float32 or split)
+void launch_vjp_again(int precision, const AdjArgs& a, int grid, hipStream_t s);
 // colour network: forward at hits (precision kPrecF32 or kPrecBF16) and
 // recompute + VJP with per-sample colour seeds (kPrecF32 or kPrecSplit)
 void launch_color(int precision, const ColorArgs& a, int grid, hipStream_t s);

@@ -615,6 +615,7 @@ struct EpCtx {
   float* gp;                // camera gradient: per-row point-gradient partials [row][kGpSlots][3] (or null)
   int gp_row0;              // global row index of the tile's first row
   bool gp_accum;            // add to the partials (the skip layer wrote them first)
+  const float* gpw;         // the rows' factors in the point gradient (LDS)
   float* delta;             // rows of this layer's delta, from the tile's first row (or null)
   int dstride;              // floats per delta row
 };
@@ -1062,7 +1063,7 @@ __device__ __forceinline__ void ep_vjp(const NetDev& net, const EpCtx& ec, f32x1
                   z = gz[i] + __shfl_xor(gz[i], 32);
       if (g == 0) {
         const int m = (mt0 + i) * 32 + r;
-        const float w = s.gm[m];
+        const float w = ec.gpw[m];
         float* dst = ec.gp + ((size_t)(ec.gp_row0 + m) * kGpSlots + nw) * 3;
         if (ec.gp_accum) {
           dst[0] += w * x;
@@ -1095,7 +1096,7 @@ __device__ __forceinline__ void ep_vjp(const NetDev& net, const EpCtx& ec, f32x1
           *(float4*)(row + feat(nt0, j, q, g)) = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1],
                                                              acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
     }
-  } else if (ec.which >= 0) {
+  } else if (ec.which >= 0 && (!GP || ec.partial)) {
     // column sums over the tile's rows, each row scaled by its seed gm[m]
 #pragma unroll
     for (int j = 0; j < NTW; ++j) {
@@ -1875,10 +1876,10 @@ __global__ __launch_bounds__(kFwdWaves<P> * 64) __attribute__((amdgpu_waves_per_
 
 // VJP through the hidden layers l = nl-2 .. 1 for the rows of a tile whose
 // output-layer seed is in LDS (unit-delta chain; every row is weighted by its
-// factor s.gm where the column sums are taken).
+// factor s.gm where the column sums are taken, and by gpw in its point gradient).
 template <int P, int NW, bool CAP, bool GP = true>
 __device__ __forceinline__ void vjp_layers(const AdjArgs& a, const Sm<P>& s, const MaskRef& mk, float* part,
-                                           size_t blk0, int rstride, int tile) {
+                                           const float* gpw, size_t blk0, int rstride, int tile) {
   const NetDev& net = a.net;
   for (int l = net.nl - 2; l >= 1; --l) {
     EpCtx ec{};
@@ -1887,13 +1888,14 @@ __device__ __forceinline__ void vjp_layers(const AdjArgs& a, const Sm<P>& s, con
     ec.mk = mk;
     ec.ntmax = net.kmax / 32;
     ec.partial = part;
+    ec.gpw = gpw;
     ec.kmax = net.kmax;
     ec.which = (l - 1 == 0) ? 0 : ((l - 1 == net.skip) ? 1 : -1);
     ec.write_act = (l - 1 != 0);
     ec.gp = a.gp_part;
     ec.gp_row0 = tile * Cfg<P>::M;
     ec.gp_accum = (l - 1 == 0) && net.skip >= 1;   // the skip layer comes first in this loop
-    if (GP && a.delta_out) {
+    if (GP && !part && a.delta_out) {
       // row layout: layer 0's features, then the skip layer's
       ec.dstride = net.wpad[0] + (net.skip >= 1 ? net.wpad[net.skip] : 0);
       ec.delta = a.delta_out + (size_t)tile * Cfg<P>::M * ec.dstride + (ec.which == 1 ? net.wpad[0] : 0);
@@ -1920,7 +1922,9 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
   const int tid = threadIdx.x;
   const int count = *a.n_samples;
   const int ntmax = net.kmax / 32;
-  const MaskRef mk{a.mask_ws + (size_t)blockIdx.x * (size_t)(net.nl) * M * ntmax, ntmax, M * ntmax, false};
+  const bool multi = a.chunk && a.chunk->w;       // unrolled march, several steps: unit seeds, no column sums
+  const MaskRef mk = multi && !a.delta_out ? MaskRef{a.mask_out, (net.nl - 1) * ntmax, ntmax, true}
+                           : MaskRef{a.mask_ws + (size_t)blockIdx.x * (size_t)(net.nl) * M * ntmax, ntmax, M * ntmax, false};
   const bool theta = a.hbuf != nullptr;
   const int t_end = theta ? min(a.tile_end, (count + M - 1) / M) : (count + M - 1) / M;
   const int rstride = a.cap_rows;             // capture chunk rows (feature stride)
@@ -1934,6 +1938,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
       const float4 smp = a.samples[idx];
       s.pts[tid] = make_float4(smp.x, smp.y, smp.z, 0.f);
       s.fval[tid] = smp.w;
+      s.rid[tid] = idx;
       lt = a.sample_lat[idx];
     }
     set_latents<P, M>(s, lt, tid < M);
@@ -1944,10 +1949,11 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
     if (tid < M) {
       float m = net.blast;
       for (int w = 0; w < wn; ++w) m += s.part[w * M + tid];
-      const float th = tanhf(m);
-      s.gm[tid] = s.fval[tid] * 0.05f * (1.f - th * th);
+      const float th = tanhf(m), dt = 1.f - th * th;
+      s.gm[tid] = s.fval[tid] * 0.05f * dt;
       if (theta) cap_put<P>(a.gmbuf, row0 + tid, s.gm[tid]);
-      else if (a.gm_out) a.gm_out[(size_t)tile * M + tid] = s.gm[tid];
+      else if (multi) a.dtanh_out[tile * M + tid] = dt;
+      else if (a.chunk) s.fval[tid] = 0.05f * dt;              // the factor of a unit seed
     }
     __syncthreads();
     if (theta) {
@@ -1964,9 +1970,10 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
         }
       }
     }
-    float* part = a.partial + (size_t)tile * 4 * net.kmax;
-    if (theta) vjp_layers<P, kAdjWaves, true>(a, s, mk, part, blk0, rstride, tile);
-    else vjp_layers<P, kAdjWaves, false>(a, s, mk, part, 0, 0, tile);
+    float* part = multi ? nullptr : a.partial + (size_t)tile * 4 * net.kmax;
+    const float* gpw = a.chunk && !multi ? s.fval : s.gm;
+    if (theta) vjp_layers<P, kAdjWaves, true>(a, s, mk, part, gpw, blk0, rstride, tile);
+    else vjp_layers<P, kAdjWaves, false>(a, s, mk, part, gpw, 0, 0, tile);
   }
 }
 
@@ -1976,13 +1983,13 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // output-layer seed w_last [h > 0] is rebuilt from the saved bits of the last
 // hidden layer, and the forward's 1 - tanh(m)^2 gives the row factor.
 // ---------------------------------------------------------------------------
-template <int P>
-__global__ __launch_bounds__(kVjpWaves<P> * 64) __attribute__((amdgpu_waves_per_eu(kVjpWaves<P> / 4, kVjpWaves<P> / 4))) void k_vjp_saved(AdjArgs a) {
+template <int P, int NW = kVjpWaves<P>>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_vjp_saved(AdjArgs a) {
   constexpr int M = Cfg<P>::M;
   Sm<P> s(dyn_smem, a.net.kmax);
   const NetDev& net = a.net;
   const int tid = threadIdx.x;
-  const int t0 = *a.n_begin / M, t1 = *a.n_samples / M;
+  const int t0 = a.n_begin ? *a.n_begin / M : 0, t1 = *a.n_samples / M;
   const int ntmax = net.kmax / 32;
   const MaskRef mk{const_cast<unsigned*>(a.smask), (net.nl - 1) * ntmax, ntmax, true};
   const int ll = net.nl - 2, q4 = net.wpad[ll] / 4;
@@ -1990,14 +1997,14 @@ __global__ __launch_bounds__(kVjpWaves<P> * 64) __attribute__((amdgpu_waves_per_
     if (tid < M) {
       const int idx = tile * M + tid;
       const float4 smp = a.samples[idx];
-      const int si = a.sample_idx[idx];
+      const int si = a.sample_idx ? a.sample_idx[idx] : idx;
       s.pts[tid] = make_float4(smp.x, smp.y, smp.z, 0.f);
       s.lat[tid] = a.sample_lat[idx];
       s.rid[tid] = si;
       s.gm[tid] = smp.w * 0.05f * a.sdtanh[si];
     }
     __syncthreads();
-    for (int i = tid; i < M * q4; i += kVjpWaves<P> * 64) {
+    for (int i = tid; i < M * q4; i += NW * 64) {
       const int m = i / q4, n = 4 * (i - m * q4);
       const unsigned word = a.smask[mask_at(mk, s.rid[m], ll, n >> 5)] >> (n & 31);
       const float4 w4 = ld4(net.wlast + n);
@@ -2006,8 +2013,8 @@ __global__ __launch_bounds__(kVjpWaves<P> * 64) __attribute__((amdgpu_waves_per_
       store4<P>(s, m, n, (n >> 2) & 1, v, true);
     }
     __syncthreads();
-    // no point gradients here (the camera and unrolled passes use k_adjoint)
-    vjp_layers<P, kVjpWaves<P>, false, false>(a, s, mk, a.partial + (size_t)tile * 4 * net.kmax, 0, 0, tile);
+    // no point gradients here (k_adjoint makes them)
+    vjp_layers<P, NW, false, false>(a, s, mk, a.partial + (size_t)tile * 4 * net.kmax, nullptr, 0, 0, tile);
   }
 }
 
@@ -2114,7 +2121,7 @@ __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(
       store4<P>(s, m, n, (n >> 2) & 1, v, true);
     }
     __syncthreads();
-    vjp_layers<P, kBwdWaves, false, false>(a, s, mk, a.partial + (size_t)tile * 4 * net.kmax, 0, 0, tile);
+    vjp_layers<P, kBwdWaves, false, false>(a, s, mk, a.partial + (size_t)tile * 4 * net.kmax, nullptr, 0, 0, tile);
   }
 }
 
@@ -2486,6 +2493,9 @@ static hipError_t setup_p(int bytes) {
   }
   e = hipFuncSetAttribute((const void*)k_vjp_saved<P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess || P == kPrecBF16) return e;          // the recompute has no bf16 kernel
+  e = hipFuncSetAttribute((const void*)k_vjp_saved<P == kPrecBF16 ? kPrecSplit : P, kAdjWaves>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
   return hipFuncSetAttribute((const void*)k_adjoint<P == kPrecBF16 ? kPrecSplit : P>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
@@ -2559,6 +2569,12 @@ void launch_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t st) {
 static_assert(kAdjWaves * 64 == 512, "the recompute-and-VJP dispatch assumes 8 waves");
 int mlp_row_groups(int waves, int width) { return (waves == 8 && width <= 128) ? 2 : 1; }
 int adjoint_waves() { return kAdjWaves; }
+void launch_vjp_again(int precision, const AdjArgs& a, int grid, hipStream_t st) {
+  const size_t sm = mlp_smem_bytes(precision, a.net);
+  const dim3 blk(kAdjWaves * 64);
+  if (precision == 2) hipLaunchKernelGGL((k_vjp_saved<2, kAdjWaves>), dim3(grid), blk, sm, st, a);
+  else if (precision == 0) hipLaunchKernelGGL((k_vjp_saved<0, kAdjWaves>), dim3(grid), blk, sm, st, a);
+}
 int vjp_saved_waves(int precision) { return precision == 1 ? kVjpWaves<1> : kVjpWaves<0>; }
 void launch_vjp_saved(int precision, const AdjArgs& a, int grid, hipStream_t st) {
   const size_t sm = mlp_smem_bytes(precision, a.net);

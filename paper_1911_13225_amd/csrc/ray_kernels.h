@@ -42,40 +42,65 @@ struct SeedIn {
   const float* imp_gv;
 };
 
-// One step of the gradient through the unrolled march: the rays of level lvl
-// that took global step `step`, their t at that step (t_hist, indexed by ray
-// slot) and the current adjoints of t (lam, by ray slot).
-struct UlIn {
-  int step, lvl;
+// The gradient through the unrolled march, one coarse-to-fine level of it: the
+// rays of level lvl of n_img images (in latent order, blk workgroups of 256 rays
+// per image), at their S steps first, first + 1, ...  Steps are indexed from
+// first below; "slots" are the distinct latents of the images.
+struct UlLevel {
+  int lvl, first, S, n_img, blk, n_slot;
   const float* g_depth;
   const float* g_sil;
-  const float* t_hist;
-  const float* lam;
-};
-
-// Several steps of that gradient at once (see k_ulg_lambda): the rays of level
-// lvl at their steps in [s0, s1], t_hist [step][t_stride].
-struct UlGroup {
-  int s0, s1, lvl;
-  const float* g_depth;
-  const float* g_sil;
-  const float* t_hist;
+  const float* t_hist;             // t of every ray slot at every global step [step][t_stride]
   size_t t_stride;
-  float* lam;
+  float* lam;                      // adjoint of every ray slot's current t
+  const int* img_slot;             // [n_img] slot of the image's latent
+  const int* slot_lat;             // [n_slot]
+  uint8_t* top;                    // [n_img][rays]: steps at whose queries the ray may have a seed (0 .. top - 1)
+  int* off;                        // [S][n_img blk]: rank of the workgroup's first ray in its segment
+  int* seg_rays;                   // [S][n_slot]: rays of a segment (the rays of one latent at one step)
+  int* seg_base;                   // [S][n_slot]: its first tile, from the step's first
+  int* step_tiles;                 // [S]
+  int* step_base;                  // [S]: the step's first tile, from its chunk's first
+  int4* chunk;                     // [rounds] (last step, first step, tiles, more than one step); tiles 0: none
 };
-// Rows of one group: unit-seed samples (launch_ulg_samples), then, with the
-// adjoint's point gradients, every sample's seed and the rays' adjoints
-// (launch_ulg_lambda), then the column sums of the saved delta rows
-// (launch_ul_colsum, partials as the adjoint writes them: one row group).
-void launch_ulg_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent, int n_img,
-                        int nr, int n_lat, int tile, const UlGroup& in, int* bsum, int* boff, int* seg_base,
-                        int* seg_total, int* seg_padded, int* n_samples, float4* samples, int* sample_lat,
-                        hipStream_t s);
-void launch_ulg_lambda(const RayPool& pl, const ImgDesc* imgs, const int* img_order, int n_img, int nr,
-                       const UlGroup& in, const int* boff, const float4* samples, const float* gp_part, float* gm,
-                       hipStream_t s);
-void launch_ul_colsum(const float* delta, const float* gm, const int* n_samples, int max_samples, int w0, int ws,
-                      int kmax, float* partial, hipStream_t s);
+// img_slot and slot_lat of the images in latent order
+void launch_ul_slots(const int* img_order, const int* img_latent, int n_img, int* img_slot, int* slot_lat,
+                     hipStream_t s);
+// Tiles: a step of `big` or more is a chunk of its own, others share chunks of
+// at most `cap` (big <= (cap + 1) / 2).
+struct UlChunks {
+  int big, cap;
+};
+// Bound on the chunks of a level of S steps of at most t1 tiles each.
+int ul_rounds(int S, long long t1, const UlChunks& k);
+// The adjoints that reach the level through its split (lvl > 0), the level's
+// samples (which ray has one at which step) and the chunks.
+void launch_ul_plan(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const UlLevel& lv, int tile,
+                    const UlChunks& k, int rounds, hipStream_t s);
+// The samples of chunk `next` (or null), with their seeds if it is a single step
+// and unit seeds else, its length in n_samples[0] and, if it has several steps,
+// in n_samples[1]; and the column sums of chunk `done` (or null) join sums
+// [slot][kUlChains][S0, Sskip][kmax].
+constexpr int kUlChains = 4;
+struct UlSums {
+  const float* partial;
+  int kmax, w0, mg0, ws, mgs;
+  double* sums;
+};
+void launch_ul_step(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const UlLevel& lv, const int4* next,
+                    const int4* done, int tile, float4* samples, int* sample_lat, int* n_samples, const UlSums& sum,
+                    hipStream_t s);
+// With the adjoint's point gradients (of unit seeds): every sample's seed, and
+// the rays' adjoints before the chunk's steps.
+void launch_ul_lambda(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const UlLevel& lv,
+                      const int4* chunk, int tile, float4* samples, const float* gp_part, hipStream_t s);
+// Column sums of a chunk of several steps from the rows of delta that the adjoint
+// kept, bit for bit those of its own epilogue.
+void launch_ul_colsum(const int4* chunk, int max_tiles, const float* delta, const float4* samples, const float* dtanh,
+                      float* partial, int kmax, int w0, int mg0, int ws, int mgs, hipStream_t s);
+// The sums as one tile per latent, for launch_gz_reduce.
+void launch_ul_total(const int* slot_lat, int n_slot, int n_lat, int tile, const double* sums, int kmax, float* partial,
+                     int* seg_base, int* seg_padded, hipStream_t s);
 
 // Second sample list of the split layout (normal-stencil samples).
 struct SplitList {
@@ -108,15 +133,7 @@ void launch_cam_reduce(const RayPool& pl, const ImgDesc* imgs, const int* img_vi
 void launch_hit_gv(const RayPool& pl, const ImgDesc* imgs, const float4* samples, const int4* sample_cam,
                    const float* gp_part, const int* n_samples, int max_samples, float* gv, hipStream_t s);
 void launch_ul_init(const RayPool& pl, const ImgDesc* imgs, int n_img, int spi, const float* g_depth, float* lam,
-                    hipStream_t s);
-void launch_ul_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent,
-                       int n_img, int nr, int n_lat, int tile, const UlIn& in, int* bsum, int* boff, int* seg_base,
-                       int* seg_total, int* seg_padded, int* n_samples, float4* samples, int* sample_lat,
-                       int4* sample_cam, hipStream_t s);
-void launch_ul_lambda(const RayPool& pl, const float4* samples, const int4* sample_cam, const float* gp_part,
-                      const int* n_samples, int max_samples, float* lam, hipStream_t s);
-void launch_ul_split(const RayPool& pl, const ImgDesc* imgs, const int* img_order, int n_img, int max_parents,
-                     int plvl, float* lam, hipStream_t s);
+                    double* sums, long long n_sums, hipStream_t s);
 void launch_color_hits(const RayPool& pl, const ImgDesc* imgs, int n_img, int hw, int* list, int* counter,
                        hipStream_t s);
 void launch_color_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent,

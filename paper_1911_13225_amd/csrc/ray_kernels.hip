@@ -907,9 +907,6 @@ __global__ void k_fill_u64(unsigned long long* p, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// launchers
-// ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // Exact gradient through the unrolled march (Eq. 2 with both terms), in
 // reverse over the marching steps.  lam[r] is the adjoint of ray r's current
 // t: dL/dt after the step being processed.  A ray's query at step n gets the
@@ -919,245 +916,90 @@ __global__ void k_fill_u64(unsigned long long* p, int n) {
 //     + dL/dS sign f            at a level-0 ray's minimum-|f| step,
 // the decoder's VJP at that point adds a df/dz to dL/dz, and lam[r] gains
 // a grad_p f . v (the same query's dependence on t through p = c + t v).
+//
+// Only the scalar adjoint of t runs from step to step; the decoder's
+// derivatives at a query do not depend on it.  A launch per step would leave
+// the chip to a few rays for most of the steps, so steps of few rays are taken
+// in chunks: one launch recomputes and back-propagates all their queries with
+// unit seeds and keeps the point gradients and, at layer 0 and the skip layer,
+// the rows of delta; a thread per ray then runs the recurrence over its steps
+// (k_ul_lambda), and the column sums are made with the resulting seeds, from the
+// rows (k_ul_colsum) or, where there is no memory for them, from the ReLU masks
+// by a second VJP.  A step
+// that fills the chip by itself is a chunk of its own: its seeds are known, and
+// the first launch makes the column sums as well.
+//   What is added up, and in which order, depends neither on the chunks nor on
+// the images beside: a latent's rays at one step are a segment of their own,
+// padded to whole tiles, every ray that can have a seed at the step is in it,
+// and the tiles' sums are added in order of step and tile.  So the chunks may
+// be as long as the memory at hand allows, and the gradient of an image is the
+// same bit for bit with any of them.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float ul_seed(const RayPool& pl, const ImgDesc& im, int r, int pix, const UlIn& in) {
+struct UlRay {
+  float alpha, dterm, sterm;       // the depth term at step `last`, the silhouette term at step `near`
+  int last, near;
+  bool stays;                      // the last step moved no t (hit, or the step limit)
+};
+__device__ __forceinline__ UlRay ul_ray(const RayPool& pl, const ImgDesc& im, int r, int pix, const UlLevel& lv) {
   const uint8_t st = pl.st[r];
-  if (st == ST_MISS || st == ST_ERROR) return 0.f;
-  const int last = (int)pl.n[r] - 1;
-  if (in.step > last) return 0.f;
-  const bool term = in.step == last;
-  const bool moved = !(term && (st == ST_HIT || st == ST_UNCONVERGED));
-  float a = moved ? im.alpha * in.lam[r] : 0.f;
-  if (in.lvl == 0) {
+  UlRay y{im.alpha, 0.f, 0.f, (int)pl.n[r] - 1, -1, st == ST_HIT || st == ST_UNCONVERGED};
+  if (lv.lvl == 0) {
     const size_t q = (size_t)im.out_base + pix;
-    if (term && st == ST_HIT && in.g_depth) {
+    if (st == ST_HIT && lv.g_depth) {
       const int V = pix / im.W, U = pix - V * im.W;
       float3 dd;
       float xt, yt;
       level_ray(im, 0, U, V, dd, xt, yt);
-      a += in.g_depth[q] / sqrtf(xt * xt + yt * yt + 1.f);
+      y.dterm = lv.g_depth[q] / sqrtf(xt * xt + yt * yt + 1.f);
     }
-    if (in.g_sil && (int)pl.rec_n[r] == in.step && pl.rec_f[r] != INFINITY) {
-      const float f0 = pl.rec_f[r];
-      a += in.g_sil[q] * (f0 > 0.f ? 1.f : (f0 < 0.f ? -1.f : 0.f));
+    const float f0 = pl.rec_f[r];
+    if (lv.g_sil && f0 != INFINITY) {
+      y.sterm = lv.g_sil[q] * (f0 > 0.f ? 1.f : (f0 < 0.f ? -1.f : 0.f));
+      y.near = pl.rec_n[r];
     }
   }
+  return y;
+}
+__device__ __forceinline__ float ul_seed(const UlRay& y, int step, float lam) {
+  float a = step == y.last && y.stays ? 0.f : y.alpha * lam;
+  if (step == y.last) a += y.dterm;
+  if (step == y.near) a += y.sterm;
   return a;
 }
 
-// Per block of 256 rays of level in.lvl: the number of rays with a nonzero seed.
-__global__ __launch_bounds__(256) void k_ul_count(RayPool pl, const ImgDesc* imgs, const int* img_order, UlIn in,
-                                                  int* bsum) {
-  __shared__ int red[256];
-  const ImgDesc& im = imgs[img_order[blockIdx.y]];
-  const int nr = (im.H >> in.lvl) * (im.W >> in.lvl);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  int c = 0;
-  if (i < nr) c = ul_seed(pl, im, im.slot_base + im.lvl_off[in.lvl] + i, i, in) != 0.f ? 1 : 0;
-  red[threadIdx.x] = c;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+__global__ __launch_bounds__(1024) void k_ul_slots(const int* img_order, const int* img_latent, int n_img,
+                                                   int* img_slot, int* slot_lat) {
+  __shared__ int buf[1024];
+  const int tid = threadIdx.x;
+  int carry = -1;                           // slot of the last image so far
+  for (int i0 = 0; i0 < n_img; i0 += 1024) {
+    const int i = i0 + tid;
+    const int lat = i < n_img ? img_latent[img_order[i]] : -1;
+    const int first = i < n_img && (i == 0 || img_latent[img_order[i - 1]] != lat) ? 1 : 0;
+    buf[tid] = first;
     __syncthreads();
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
-}
-
-// Writes one sample per counted ray: its point of step in.step and its seed;
-// sample_cam = (image, ray slot).
-__global__ __launch_bounds__(256) void k_ul_write(RayPool pl, const ImgDesc* imgs, const int* img_order, UlIn in,
-                                                  const int* boff, float4* samples, int* sample_lat,
-                                                  int4* sample_cam) {
-  __shared__ int buf[256];
-  const int img = img_order[blockIdx.y];
-  const ImgDesc& im = imgs[img];
-  const int nr = (im.H >> in.lvl) * (im.W >> in.lvl);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int r = im.slot_base + im.lvl_off[in.lvl] + i;
-  const float a = i < nr ? ul_seed(pl, im, r, i, in) : 0.f;
-  const int o = boff[blockIdx.y * gridDim.x + blockIdx.x] + block_excl_scan(a != 0.f ? 1 : 0, buf);
-  if (a == 0.f) return;
-  const float4 d = pl.d[r];
-  const float t = in.t_hist[r];
-  samples[o] = make_float4(fmaf(t, d.x, im.c[0]), fmaf(t, d.y, im.c[1]), fmaf(t, d.z, im.c[2]), a);
-  sample_lat[o] = im.latent;
-  sample_cam[o] = make_int4(img, r, 0, 0);
-}
-
-// lam[r] += a grad_p f . v for every sample of the step (grad_p f = the
-// residual term's p / (2 |p|) plus the adjoint's per-wave partials).
-__global__ void k_ul_lambda(RayPool pl, const float4* samples, const int4* sample_cam, const float* gp_part,
-                            const int* n_samples, float* lam) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= *n_samples) return;
-  const int4 sc = sample_cam[i];
-  if (sc.x < 0) return;
-  const float4 smp = samples[i];
-  const float rn = sqrtf(smp.x * smp.x + smp.y * smp.y + smp.z * smp.z);
-  const float h = rn > 0.f ? 0.5f * smp.w / rn : 0.f;
-  float g[3] = {h * smp.x, h * smp.y, h * smp.z};
-  const float* pp = gp_part + (size_t)i * 3 * kGpSlots;
-  for (int w = 0; w < kGpSlots; ++w) {
-    g[0] += pp[3 * w];
-    g[1] += pp[3 * w + 1];
-    g[2] += pp[3 * w + 2];
-  }
-  const float4 d = pl.d[sc.y];
-  lam[sc.y] += g[0] * d.x + g[1] * d.y + g[2] * d.z;
-}
-
-// ---------------------------------------------------------------------------
-// The same gradient for a group of steps at once.  Only the scalar adjoint of
-// t runs from step to step; the decoder's derivatives at a query do not depend
-// on it.  So every query of the group is recomputed and back-propagated with a
-// unit seed in one launch, which keeps its row of delta (layer 0 and the skip
-// layer) and its point gradient; a thread per ray then runs the recurrence
-// over its steps, and the column sums weighted with the resulting seeds give
-// dL/dz.  A launch per step left the chip to a few rays for most of the steps
-// (152 us of recompute and VJP and 55 us around it, 50 times).  Gradient of two
-// images of 96^2 (bf16, DeepSDF) 10.3 -> 1.1 ms, float32 38.8 -> 4.1 ms, of
-// four of 256^2 (two steps a group) 12.7 -> 8.9 ms.
-// ---------------------------------------------------------------------------
-// Steps of the group at which ray r can have a nonzero seed: [lo, hi], empty if
-// hi < lo.  lam is the ray's adjoint above the group.
-__device__ __forceinline__ int2 ulg_range(const RayPool& pl, const ImgDesc& im, int r, int pix, const UlGroup& in) {
-  const uint8_t st = pl.st[r];
-  if (st == ST_MISS || st == ST_ERROR) return make_int2(0, -1);
-  int hi = min((int)pl.n[r] - 1, in.s1);
-  if (hi < in.s0) return make_int2(0, -1);
-  if (in.lam[r] == 0.f) {
-    // nothing reaches the ray from above: its first seed is at its
-    // minimum-|f| step (a hit's depth term is in lam from the start)
-    if (in.lvl != 0 || !in.g_sil || pl.rec_f[r] == INFINITY || in.g_sil[(size_t)im.out_base + pix] == 0.f)
-      return make_int2(0, -1);
-    hi = min(hi, (int)pl.rec_n[r]);
-    if ((int)pl.rec_n[r] > in.s1 || hi < in.s0) return make_int2(0, -1);
-  }
-  return make_int2(in.s0, hi);
-}
-
-__global__ __launch_bounds__(256) void k_ulg_count(RayPool pl, const ImgDesc* imgs, const int* img_order, UlGroup in,
-                                                   int* bsum) {
-  __shared__ int red[256];
-  const ImgDesc& im = imgs[img_order[blockIdx.y]];
-  const int nr = (im.H >> in.lvl) * (im.W >> in.lvl);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  int c = 0;
-  if (i < nr) {
-    const int2 s = ulg_range(pl, im, im.slot_base + im.lvl_off[in.lvl] + i, i, in);
-    c = max(s.y - s.x + 1, 0);
-  }
-  red[threadIdx.x] = c;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
-}
-
-// One unit-seed sample per ray and step of its range, a ray's samples together
-// and in descending steps.
-__global__ __launch_bounds__(256) void k_ulg_write(RayPool pl, const ImgDesc* imgs, const int* img_order, UlGroup in,
-                                                   const int* boff, float4* samples, int* sample_lat) {
-  __shared__ int buf[256];
-  const ImgDesc& im = imgs[img_order[blockIdx.y]];
-  const int nr = (im.H >> in.lvl) * (im.W >> in.lvl);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int r = im.slot_base + im.lvl_off[in.lvl] + i;
-  const int2 s = i < nr ? ulg_range(pl, im, r, i, in) : make_int2(0, -1);
-  const int o = boff[blockIdx.y * gridDim.x + blockIdx.x] + block_excl_scan(max(s.y - s.x + 1, 0), buf);
-  if (s.y < s.x) return;
-  const float4 d = pl.d[r];
-  for (int n = s.y; n >= s.x; --n) {
-    const float t = in.t_hist[(size_t)n * in.t_stride + r];
-    samples[o + s.y - n] = make_float4(fmaf(t, d.x, im.c[0]), fmaf(t, d.y, im.c[1]), fmaf(t, d.z, im.c[2]), 1.f);
-    sample_lat[o + s.y - n] = im.latent;
-  }
-}
-
-// The recurrence of k_ul_lambda over a ray's steps of the group, latest first:
-// the seed a of each query (as ul_seed), lam += a grad_p f . v, and the
-// sample's row factor gm (0.05 (1 - tanh^2 m) from the unit-seed pass) times a.
-__global__ __launch_bounds__(256) void k_ulg_lambda(RayPool pl, const ImgDesc* imgs, const int* img_order, UlGroup in,
-                                                    const int* boff, const float4* samples, const float* gp_part,
-                                                    float* gm) {
-  __shared__ int buf[256];
-  const ImgDesc& im = imgs[img_order[blockIdx.y]];
-  const int nr = (im.H >> in.lvl) * (im.W >> in.lvl);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int r = im.slot_base + im.lvl_off[in.lvl] + i;
-  const int2 s = i < nr ? ulg_range(pl, im, r, i, in) : make_int2(0, -1);
-  int o = boff[blockIdx.y * gridDim.x + blockIdx.x] + block_excl_scan(max(s.y - s.x + 1, 0), buf);
-  if (s.y < s.x) return;
-  const float4 d = pl.d[r];
-  const UlIn at{0, in.lvl, in.g_depth, in.g_sil, nullptr, in.lam};
-  for (int n = s.y; n >= s.x; --n, ++o) {
-    UlIn u = at;
-    u.step = n;
-    const float a = ul_seed(pl, im, r, i, u);
-    const float4 smp = samples[o];
-    const float rn = sqrtf(smp.x * smp.x + smp.y * smp.y + smp.z * smp.z);
-    const float h = rn > 0.f ? 0.5f / rn : 0.f;
-    float g[3] = {h * smp.x, h * smp.y, h * smp.z};
-    const float* pp = gp_part + (size_t)o * 3 * kGpSlots;
-    for (int w = 0; w < kGpSlots; ++w) {
-      g[0] += pp[3 * w];
-      g[1] += pp[3 * w + 1];
-      g[2] += pp[3 * w + 2];
+    for (int o = 1; o < 1024; o <<= 1) {
+      const int x = tid >= o ? buf[tid - o] : 0;
+      __syncthreads();
+      buf[tid] += x;
+      __syncthreads();
     }
-    gm[o] *= a;
-    in.lam[r] += a * (g[0] * d.x + g[1] * d.y + g[2] * d.z);
-  }
-}
-
-// Column sums of each tile of 64 delta rows weighted with gm, in the layout of
-// the adjoint's partials (row group 0 of layer 0 and of the skip layer).  A
-// thread owns four columns; the rows are read once, 16 bytes per lane, 8 rows in flight.
-__global__ __launch_bounds__(256) void k_ul_colsum(const float* __restrict__ delta, const float* __restrict__ gm,
-                                                   const int* __restrict__ n_samples, int w0, int ws, int kmax,
-                                                   float* __restrict__ partial) {
-  __shared__ float wgt[64];
-  const int tiles = *n_samples / 64, dw = w0 + ws, c = 4 * threadIdx.x;
-  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    if (threadIdx.x < 64) wgt[threadIdx.x] = gm[(size_t)tile * 64 + threadIdx.x];
-    __syncthreads();
-    if (c < dw) {
-      float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-      const float* p = delta + (size_t)tile * 64 * dw + c;
-      for (int m = 0; m < 64; m += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(p + (size_t)(m + u) * dw);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const float w = wgt[m + u];
-          acc.x = fmaf(w, v[u].x, acc.x);
-          acc.y = fmaf(w, v[u].y, acc.y);
-          acc.z = fmaf(w, v[u].z, acc.z);
-          acc.w = fmaf(w, v[u].w, acc.w);
-        }
-      }
-      float* out = partial + (size_t)tile * 4 * kmax + (c < w0 ? c : 2 * kmax + c - w0);
-      *(float4*)out = acc;
+    if (i < n_img) {
+      img_slot[i] = carry + buf[tid];
+      if (first) slot_lat[carry + buf[tid]] = lat;
     }
+    carry += buf[1023];
     __syncthreads();
   }
 }
 
-// Coarse-to-fine split in reverse: every ray of level plvl collects the
-// adjoints of its four children (fixed order) whose start was its t, i.e. it
-// did not miss the sphere and the clamp into the child's interval (computed
-// exactly as the forward's split) did not bind.
-__global__ __launch_bounds__(256) void k_ul_split(RayPool pl, const ImgDesc* imgs, const int* img_order, int plvl,
-                                                  float* lam) {
-  const ImgDesc& im = imgs[img_order[blockIdx.y]];
-  const int Wp = im.W >> plvl, Hp = im.H >> plvl, Wc = im.W >> (plvl - 1);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= Wp * Hp) return;
-  const int pr = im.slot_base + im.lvl_off[plvl] + i;
-  if (pl.st[pr] == ST_MISS) return;
-  const float tp = pl.d[pr].w;
+// Coarse-to-fine split in reverse: the adjoints of ray i's (level plvl) four
+// children (fixed order) whose start was its t, i.e. it did not miss the sphere
+// and the clamp into the child's interval (computed exactly as the forward's
+// split) did not bind.
+__device__ __forceinline__ float ul_split(const RayPool& pl, const ImgDesc& im, int plvl, int i, const float* lam) {
+  const int Wp = im.W >> plvl, Wc = im.W >> (plvl - 1);
+  const float tp = pl.d[im.slot_base + im.lvl_off[plvl] + i].w;
   const int Vp = i / Wp, Up = i - Vp * Wp;
   float acc = 0.f;
   for (int dy = 0; dy < 2; ++dy)
@@ -1169,15 +1011,399 @@ __global__ __launch_bounds__(256) void k_ul_split(RayPool pl, const ImgDesc* img
       const bool inside = sphere_interval(im, d, t_lo, t_hi);
       if (inside && tp > t_lo && tp < t_hi) acc += lam[im.slot_base + im.lvl_off[plvl - 1] + V * Wc + U];
     }
-  lam[pr] += acc;
+  return acc;
+}
+
+// The adjoints that reach the level through its split, the steps at which each
+// ray can have a seed (top), and per workgroup of 256 rays and step the number
+// of them.  A ray with an adjoint has one at all of its
+// steps; nothing reaches the others from above, so a level-0 ray's first seed
+// is at its minimum-|f| step (a hit's depth term is in lam from the start), and
+// a coarser ray has none.
+__global__ __launch_bounds__(256) void k_ul_top(RayPool pl, const ImgDesc* imgs, const int* img_order, UlLevel lv) {
+  __shared__ int cnt[256];
+  const int tid = threadIdx.x, pos = blockIdx.y;
+  const ImgDesc& im = imgs[img_order[pos]];
+  const int nr = (im.H >> lv.lvl) * (im.W >> lv.lvl);
+  const int i = blockIdx.x * 256 + tid;
+  int top = 0;
+  if (i < nr) {
+    const int r = im.slot_base + im.lvl_off[lv.lvl] + i;
+    const uint8_t st = pl.st[r];
+    float lam = lv.lam[r];
+    if (lv.lvl > 0 && st != ST_MISS) lv.lam[r] = lam += ul_split(pl, im, lv.lvl, i, lv.lam);
+    if (st != ST_MISS && st != ST_ERROR) {
+      int hi = (int)pl.n[r] - 1;
+      if (lam == 0.f)
+        hi = lv.lvl == 0 && lv.g_sil && pl.rec_f[r] != INFINITY && lv.g_sil[(size_t)im.out_base + i] != 0.f
+                 ? min(hi, (int)pl.rec_n[r]) : -1;
+      top = min(max(hi - lv.first + 1, 0), lv.S);
+    }
+    lv.top[(size_t)pos * nr + i] = (uint8_t)top;
+  }
+  cnt[tid] = 0;
+  __syncthreads();
+  if (top) atomicAdd(&cnt[top - 1], 1);
+  __syncthreads();
+  for (int o = 1; o < 256; o <<= 1) {       // rays with a sample at step tid: those of top > tid
+    const int x = tid + o < 256 ? cnt[tid + o] : 0;
+    __syncthreads();
+    cnt[tid] += x;
+    __syncthreads();
+  }
+  if (tid < lv.S) lv.off[(size_t)tid * lv.n_img * lv.blk + (size_t)pos * lv.blk + blockIdx.x] = cnt[tid];
+}
+
+// Exclusive prefix of v over 1024 threads; *total receives the sum.
+__device__ __forceinline__ int scan1024(int v, int* buf, int* total) {
+  const int tid = threadIdx.x;
+  __syncthreads();                          // (the last scan's buf has been read)
+  buf[tid] = v;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int x = tid >= o ? buf[tid - o] : 0;
+    __syncthreads();
+    buf[tid] += x;
+    __syncthreads();
+  }
+  *total = buf[1023];
+  return buf[tid] - v;
+}
+
+// Per step (blockIdx.x): the counts of k_ul_top become ranks within the segment
+// of their latent, and the segments get their tiles in slot order.
+__global__ __launch_bounds__(1024) void k_ul_scan(UlLevel lv, int tile) {
+  __shared__ int buf[1024];
+  const int tid = threadIdx.x, s = blockIdx.x;
+  int* off = lv.off + (size_t)s * lv.n_img * lv.blk;
+  int* rays = lv.seg_rays + (size_t)s * lv.n_slot;
+  for (int i0 = 0; i0 < lv.n_img;) {
+    const int slot = lv.img_slot[i0];
+    int i1 = i0 + 1;
+    while (i1 < lv.n_img && lv.img_slot[i1] == slot) ++i1;
+    const long long b0 = (long long)i0 * lv.blk, nb = (long long)(i1 - i0) * lv.blk;
+    int carry = 0;
+    for (long long c0 = 0; c0 < nb; c0 += 1024) {
+      const bool in = c0 + tid < nb;
+      int tot;
+      const int x = scan1024(in ? off[b0 + c0 + tid] : 0, buf, &tot);
+      if (in) off[b0 + c0 + tid] = carry + x;
+      carry += tot;
+    }
+    if (tid == 0) rays[slot] = carry;
+    i0 = i1;
+  }
+  __syncthreads();
+  int carry = 0;
+  for (int l0 = 0; l0 < lv.n_slot; l0 += 1024) {
+    const bool in = l0 + tid < lv.n_slot;
+    int tot;
+    const int x = scan1024(in ? (rays[l0 + tid] + tile - 1) / tile : 0, buf, &tot);
+    if (in) lv.seg_base[(size_t)s * lv.n_slot + l0 + tid] = carry + x;
+    carry += tot;
+  }
+  if (tid == 0) lv.step_tiles[s] = carry;
+}
+
+// Whole steps to chunks, the last step first (one workgroup).
+__global__ __launch_bounds__(256) void k_ul_chunks(UlLevel lv, UlChunks k, int rounds) {
+  __shared__ int T[256];
+  const int tid = threadIdx.x;
+  if (tid < lv.S) T[tid] = lv.step_tiles[tid];
+  for (int c = tid; c < rounds; c += 256) lv.chunk[c] = make_int4(0, 0, 0, 0);
+  __syncthreads();
+  if (tid) return;
+  int c = 0;
+  for (int s = lv.S - 1; s >= 0;) {
+    const int hi = s;
+    int sum = T[s];
+    lv.step_base[s--] = 0;
+    if (sum < k.big)
+      for (; s >= 0 && T[s] < k.big && sum + T[s] <= k.cap; --s) {
+        lv.step_base[s] = sum;
+        sum += T[s];
+      }
+    if (sum > 0 && c < rounds) lv.chunk[c++] = make_int4(hi, s + 1, sum, hi > s + 1);   // (rounds suffice: ul_rounds)
+  }
+}
+int ul_rounds(int S, long long t1, const UlChunks& k) {
+  if (t1 >= k.big) return S;
+  if (S * t1 <= k.cap) return 1;
+  // no step is big; a chunk ends where the next step would not fit (or is the last)
+  return (int)std::min<long long>(S, S * t1 / (k.cap - t1 + 1) + 1);
+}
+
+// Where the samples of a workgroup's 256 rays lie in a chunk: per step the first
+// sample of each wave.  Prepared for all steps at once (one barrier; a barrier
+// per step made each wait for the loads of the one before).
+struct UlSlots {
+  int at[256][4];
+};
+__device__ __forceinline__ void ul_slots(const UlLevel& lv, const int4& c, int pos, int blk, int slot, int top, int tile,
+                                         UlSlots& u) {
+  const int tid = threadIdx.x, w = tid >> 6;
+  for (int s = c.y; s <= c.x; ++s) {
+    const int n = __popcll(__ballot(top > s));
+    if ((tid & 63) == 0) u.at[s][w] = n;
+  }
+  __syncthreads();
+  const int s = c.y + tid;
+  if (s <= c.x) {
+    int o = (lv.step_base[s] + lv.seg_base[(size_t)s * lv.n_slot + slot]) * tile +
+            lv.off[(size_t)s * lv.n_img * lv.blk + (size_t)pos * lv.blk + blk];
+    for (int k = 0; k < 4; ++k) {
+      const int n = u.at[s][k];
+      u.at[s][k] = o;
+      o += n;
+    }
+  }
+  __syncthreads();
+}
+// This thread's sample at step s (if top > s).
+__device__ __forceinline__ int ul_at(const UlSlots& u, int s, int top) {
+  const unsigned long long bal = __ballot(top > s);
+  return u.at[s][threadIdx.x >> 6] + __popcll(bal & ((1ull << (threadIdx.x & 63)) - 1ull));
+}
+
+// One sample per ray and step of the chunk; zero seeds in the segments' padding.
+__device__ __forceinline__ void ul_write(const RayPool& pl, const ImgDesc* imgs, const int* img_order,
+                                         const UlLevel& lv, const int4& c, int blk, int pos, int tile, float4* samples,
+                                         int* sample_lat, UlSlots& u) {
+  const ImgDesc& im = imgs[img_order[pos]];
+  const int nr = (im.H >> lv.lvl) * (im.W >> lv.lvl);
+  const int tid = threadIdx.x, i = blk * 256 + tid;
+  const int r = im.slot_base + im.lvl_off[lv.lvl] + i;
+  const int top = i < nr ? lv.top[(size_t)pos * nr + i] : 0;
+  const int slot = lv.img_slot[pos];
+  const float lam = top ? lv.lam[r] : 0.f;
+  const float4 d = top ? pl.d[r] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const UlRay y = top && !c.w ? ul_ray(pl, im, r, i, lv) : UlRay{};
+  ul_slots(lv, c, pos, blk, slot, top, tile, u);
+  for (int s = c.x; s >= c.y; --s) {
+    const int o = ul_at(u, s, top);
+    if (top <= s) continue;
+    const float t = lv.t_hist[(size_t)(lv.first + s) * lv.t_stride + r];
+    samples[o] = make_float4(fmaf(t, d.x, im.c[0]), fmaf(t, d.y, im.c[1]), fmaf(t, d.z, im.c[2]),
+                             c.w ? 1.f : ul_seed(y, lv.first + s, lam));
+    sample_lat[o] = im.latent;
+  }
+  if (blk != 0 || (pos > 0 && lv.img_slot[pos - 1] == slot)) return;
+  for (int s = c.y + (tid >> 6); s <= c.x; s += 4) {       // the segment's first workgroup: a wave per step
+    const size_t seg = (size_t)s * lv.n_slot + slot;
+    const int n = lv.seg_rays[seg], o = (lv.step_base[s] + lv.seg_base[seg]) * tile;
+    for (int k = n + (tid & 63); k < (n + tile - 1) / tile * tile; k += 64) {
+      samples[o + k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      sample_lat[o + k] = im.latent;
+    }
+  }
+}
+
+// The tiles of a slot's segments, latest step first, added to its sums in
+// kUlChains interleaved chains (one wave each, a lane per column), in 64 bits:
+// a chain of additions over all tiles of all steps.
+__device__ __forceinline__ void ul_sum(const UlLevel& lv, const int4& c, int slot, int colblk, int tile,
+                                       const UlSums& a, int (&tb)[256], int (&nt)[256]) {
+  const int q = threadIdx.x >> 6, col = colblk * 64 + (threadIdx.x & 63);
+  const int s0 = c.y + threadIdx.x;
+  if (s0 <= c.x) {
+    const size_t seg = (size_t)s0 * lv.n_slot + slot;
+    tb[s0] = lv.step_base[s0] + lv.seg_base[seg];
+    nt[s0] = (lv.seg_rays[seg] + tile - 1) / tile;
+  }
+  __syncthreads();
+  const int which = col < a.w0 ? 0 : 1, n = which ? col - a.w0 : col, mg = which ? a.mgs : a.mg0;
+  const float* p = a.partial + (size_t)(2 * which) * a.kmax + n;
+  double* out = a.sums + ((size_t)(slot * kUlChains + q) * 2 + which) * a.kmax + n;
+  double acc = *out;
+  constexpr int D = 16;                      // tiles in flight
+  int s = c.x + 1, t = 0, end = 0, base = 0;
+  auto settle = [&]() {                      // to the chain's next tile, in the next segment that has one
+    while (t >= end && s > c.y) {
+      --s;
+      t = q;
+      end = __builtin_amdgcn_readfirstlane(nt[s]);
+      base = __builtin_amdgcn_readfirstlane(tb[s]);
+    }
+  };
+  settle();
+  while (t < end) {
+    float v[D][2];
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      v[u][0] = v[u][1] = 0.f;
+      if (t >= end) continue;
+      const float* x = p + (size_t)(base + t) * 4 * a.kmax;
+      v[u][0] = x[0];
+      if (mg > 1) v[u][1] = x[a.kmax];
+      t += kUlChains;
+      settle();
+    }
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      acc += v[u][0];
+      acc += v[u][1];
+    }
+  }
+  *out = acc;
+}
+
+// Both in one launch, by workgroup: the samples of chunk `next` and the sums of
+// chunk `done` (either may be null).
+__global__ __launch_bounds__(256) void k_ul_step(RayPool pl, const ImgDesc* imgs, const int* img_order, UlLevel lv,
+                                                 const int4* next, const int4* done, int tile, float4* samples,
+                                                 int* sample_lat, int* n_samples, UlSums sum) {
+  __shared__ union {
+    UlSlots slots;
+    int seg[2][256];
+  } sh;
+  const int wb = next ? lv.n_img * lv.blk : 0, b = blockIdx.x;
+  if (b < wb) {
+    const int4 c = *next;
+    if (b == 0 && threadIdx.x == 0) {
+      n_samples[0] = c.z * tile;
+      n_samples[1] = c.w ? c.z * tile : 0;
+    }
+    if (c.z) ul_write(pl, imgs, img_order, lv, c, b % lv.blk, b / lv.blk, tile, samples, sample_lat, sh.slots);
+  } else {
+    const int4 c = *done;
+    const int cols = (sum.w0 + sum.ws) / 64;
+    if (c.z) ul_sum(lv, c, (b - wb) / cols, (b - wb) % cols, tile, sum, sh.seg[0], sh.seg[1]);
+  }
+}
+
+// The recurrence over the chunk's steps of each ray, latest first: the seed of
+// its query (written to the sample), then lam += a grad_p f . v, with grad_p f
+// the residual term's p / (2 |p|) plus the adjoint's per-wave partials.  Only
+// lam and the seed run from step to step; the loads of four steps are in flight.
+__global__ __launch_bounds__(256) void k_ul_lambda(RayPool pl, const ImgDesc* imgs, const int* img_order, UlLevel lv,
+                                                   const int4* chunk, int tile, float4* samples,
+                                                   const float* gp_part) {
+  __shared__ UlSlots u;
+  const int4 c = *chunk;
+  if (c.z == 0) return;
+  const int pos = blockIdx.y;
+  const ImgDesc& im = imgs[img_order[pos]];
+  const int nr = (im.H >> lv.lvl) * (im.W >> lv.lvl);
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int r = im.slot_base + im.lvl_off[lv.lvl] + i;
+  const int top = i < nr ? lv.top[(size_t)pos * nr + i] : 0;
+  float lam = top ? lv.lam[r] : 0.f;
+  const float4 d = top ? pl.d[r] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const UlRay y = top ? ul_ray(pl, im, r, i, lv) : UlRay{};
+  ul_slots(lv, c, pos, blockIdx.x, lv.img_slot[pos], top, tile, u);
+  constexpr int G = 4, V = 3 * kGpSlots / 4;
+  for (int s1 = c.x; s1 >= c.y; s1 -= G) {
+    int o[G];
+    float4 smp[G], gp[G][V];
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int s = max(s1 - k, c.y);        // (past the chunk: its first step again, not used)
+      o[k] = ul_at(u, s, top);
+      if (top <= s) continue;
+      smp[k] = samples[o[k]];
+#pragma unroll
+      for (int v = 0; v < V; ++v) gp[k][v] = ((const float4*)(gp_part + (size_t)o[k] * 3 * kGpSlots))[v];
+    }
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int s = s1 - k;
+      if (s < c.y || top <= s) continue;
+      const float4 p = smp[k];
+      const float rn = sqrtf(p.x * p.x + p.y * p.y + p.z * p.z);
+      const float h = rn > 0.f ? 0.5f / rn : 0.f;
+      float g[3] = {h * p.x, h * p.y, h * p.z};
+#pragma unroll
+      for (int w = 0; w < 3 * kGpSlots; ++w) {
+        const float4 x = gp[k][w / 4];
+        g[w % 3] += w % 4 == 0 ? x.x : (w % 4 == 1 ? x.y : (w % 4 == 2 ? x.z : x.w));
+      }
+      const float a = ul_seed(y, lv.first + s, lam);
+      samples[o[k]].w = a;
+      lam += a * (g[0] * d.x + g[1] * d.y + g[2] * d.z);
+    }
+  }
+  if (top > c.y) lv.lam[r] = lam;
+}
+
+// Column sums of each tile of 64 delta rows weighted with the seeds' factors, in
+// the order of the adjoint's epilogue (ep_vjp): a lane holds rows r and, where a
+// wave covers the whole tile (one row group), r + 32, added in that order; then
+// the lanes in pairs 16, 8, 4, 2 and 1 apart.  A thread owns four columns; the
+// rows are read once, 16 bytes per lane.
+template <int BIT, bool TWO>
+__device__ __forceinline__ float4 ul_tree(const float* p, int dw, const float* wgt, int r) {
+  if constexpr (BIT == 32) {
+    const float4 x = *(const float4*)(p + (size_t)r * dw);
+    float4 a = make_float4(fmaf(wgt[r], x.x, 0.f), fmaf(wgt[r], x.y, 0.f), fmaf(wgt[r], x.z, 0.f),
+                           fmaf(wgt[r], x.w, 0.f));
+    if constexpr (TWO) {
+      const float4 y = *(const float4*)(p + (size_t)(r + 32) * dw);
+      const float w = wgt[r + 32];
+      a = make_float4(fmaf(w, y.x, a.x), fmaf(w, y.y, a.y), fmaf(w, y.z, a.z), fmaf(w, y.w, a.w));
+    }
+    return a;
+  } else {
+    const float4 a = ul_tree<2 * BIT, TWO>(p, dw, wgt, r), b = ul_tree<2 * BIT, TWO>(p, dw, wgt, r + BIT);
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+  }
+}
+__global__ __launch_bounds__(256) void k_ul_colsum(const int4* chunk, const float* __restrict__ delta,
+                                                   const float4* __restrict__ samples,
+                                                   const float* __restrict__ dtanh, float* __restrict__ partial,
+                                                   int kmax, int w0, int mg0, int ws, int mgs) {
+  __shared__ float wgt[64];
+  const int4 c = *chunk;
+  if (!c.w) return;
+  const int dw = w0 + ws, col = 4 * threadIdx.x, which = col < w0 ? 0 : 1, n = which ? col - w0 : col;
+  for (int tile = blockIdx.x; tile < c.z; tile += gridDim.x) {
+    const size_t row = (size_t)tile * 64;
+    if (threadIdx.x < 64) wgt[threadIdx.x] = samples[row + threadIdx.x].w * 0.05f * dtanh[row + threadIdx.x];
+    __syncthreads();
+    if (col < dw) {
+      const float* p = delta + row * dw + col;
+      float* out = partial + (size_t)tile * 4 * kmax + 2 * which * kmax + n;
+      if ((which ? mgs : mg0) == 1) {
+        *(float4*)out = ul_tree<1, true>(p, dw, wgt, 0);
+      } else {
+        *(float4*)out = ul_tree<1, false>(p, dw, wgt, 0);
+        *(float4*)(out + kmax) = ul_tree<1, false>(p + (size_t)32 * dw, dw, wgt + 32, 0);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void k_ul_total(const int* slot_lat, int n_slot, int n_lat, int tile,
+                                                  const double* sums, int kmax, float* partial, int* seg_base,
+                                                  int* seg_padded) {
+  for (int l = blockIdx.x * 256 + threadIdx.x; l < n_lat; l += gridDim.x * 256) {
+    int lo = 0, hi = n_slot - 1;             // slot_lat ascends
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (slot_lat[mid] < l) lo = mid + 1; else hi = mid;
+    }
+    const bool used = slot_lat[lo] == l;
+    seg_base[l] = used ? lo * tile : 0;
+    seg_padded[l] = used ? tile : 0;
+  }
+  for (int slot = blockIdx.x; slot < n_slot; slot += gridDim.x)
+    for (int k = threadIdx.x; k < 2 * kmax; k += 256) {
+      double a = 0.0;
+      for (int q = 0; q < kUlChains; ++q) a += sums[(size_t)(slot * kUlChains + q) * 2 * kmax + k];
+      partial[(size_t)slot * 4 * kmax + (k < kmax ? k : kmax + k)] = (float)a;
+    }
 }
 
 // Initial adjoints: dL/dd / |(xt, yt, 1)| for level-0 hits (d = t + f, so the
-// last t carries the depth gradient directly), 0 for every other ray slot.
+// last t carries the depth gradient directly), 0 for every other ray slot; and
+// zero sums.
 __global__ __launch_bounds__(256) void k_ul_init(RayPool pl, const ImgDesc* imgs, const float* g_depth, int spi,
-                                                 float* lam) {
+                                                 float* lam, double* sums, long long n_sums) {
   const ImgDesc& im = imgs[blockIdx.y];
   const int i = blockIdx.x * 256 + threadIdx.x;
+  for (long long k = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; k < n_sums;
+       k += (long long)gridDim.x * gridDim.y * 256)
+    sums[k] = 0.0;
   if (i >= spi) return;
   const int r = im.slot_base + i;
   float v = 0.f;
@@ -1242,6 +1468,9 @@ __global__ __launch_bounds__(256) void k_color_write(RayPool pl, const ImgDesc* 
   sample_lat[o] = im.latent;
 }
 
+// ---------------------------------------------------------------------------
+// launchers
+// ---------------------------------------------------------------------------
 static inline unsigned nblk(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
 void launch_init_level(const RayPool& pl, const ImgDesc* imgs, int n_img, int max_rays, int* list, int* counter,
@@ -1378,54 +1607,40 @@ void launch_adam(float* z, float* m, float* v, const float* g, int L, float lr, 
 }
 
 void launch_ul_init(const RayPool& pl, const ImgDesc* imgs, int n_img, int spi, const float* g_depth, float* lam,
+                    double* sums, long long n_sums, hipStream_t s) {
+  hipLaunchKernelGGL(k_ul_init, dim3(nblk(spi, 256), n_img), dim3(256), 0, s, pl, imgs, g_depth, spi, lam, sums, n_sums);
+}
+void launch_ul_slots(const int* img_order, const int* img_latent, int n_img, int* img_slot, int* slot_lat,
+                     hipStream_t s) {
+  hipLaunchKernelGGL(k_ul_slots, dim3(1), dim3(1024), 0, s, img_order, img_latent, n_img, img_slot, slot_lat);
+}
+void launch_ul_plan(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const UlLevel& lv, int tile,
+                    const UlChunks& k, int rounds, hipStream_t s) {
+  hipLaunchKernelGGL(k_ul_top, dim3(lv.blk, lv.n_img), dim3(256), 0, s, pl, imgs, img_order, lv);
+  hipLaunchKernelGGL(k_ul_scan, dim3(lv.S), dim3(1024), 0, s, lv, tile);
+  hipLaunchKernelGGL(k_ul_chunks, dim3(1), dim3(256), 0, s, lv, k, rounds);
+}
+void launch_ul_step(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const UlLevel& lv, const int4* next,
+                    const int4* done, int tile, float4* samples, int* sample_lat, int* n_samples, const UlSums& sum,
                     hipStream_t s) {
-  hipLaunchKernelGGL(k_ul_init, dim3(nblk(spi, 256), n_img), dim3(256), 0, s, pl, imgs, g_depth, spi, lam);
+  const unsigned grid = (next ? (unsigned)lv.n_img * lv.blk : 0) + (done ? (unsigned)lv.n_slot * ((sum.w0 + sum.ws) / 64) : 0);
+  hipLaunchKernelGGL(k_ul_step, dim3(grid), dim3(256), 0, s, pl, imgs, img_order, lv, next, done, tile, samples,
+                     sample_lat, n_samples, sum);
 }
-void launch_ul_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent,
-                       int n_img, int nr, int n_lat, int tile, const UlIn& in, int* bsum, int* boff, int* seg_base,
-                       int* seg_total, int* seg_padded, int* n_samples, float4* samples, int* sample_lat,
-                       int4* sample_cam, hipStream_t s) {
-  const int bpl = (int)nblk(nr, 256);
-  hipLaunchKernelGGL(k_ul_count, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, bsum);
-  hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, bsum, n_img, bpl, img_order, img_latent, 0, tile,
-                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples,
-                     PadOut{samples, sample_lat, nullptr, sample_cam, nullptr});
-  hipLaunchKernelGGL(k_ul_write, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, boff, samples,
-                     sample_lat, sample_cam);
+void launch_ul_lambda(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const UlLevel& lv,
+                      const int4* chunk, int tile, float4* samples, const float* gp_part, hipStream_t s) {
+  hipLaunchKernelGGL(k_ul_lambda, dim3(lv.blk, lv.n_img), dim3(256), 0, s, pl, imgs, img_order, lv, chunk, tile,
+                     samples, gp_part);
 }
-void launch_ul_lambda(const RayPool& pl, const float4* samples, const int4* sample_cam, const float* gp_part,
-                      const int* n_samples, int max_samples, float* lam, hipStream_t s) {
-  if (max_samples <= 0) return;
-  hipLaunchKernelGGL(k_ul_lambda, dim3(nblk(max_samples, 256)), dim3(256), 0, s, pl, samples, sample_cam, gp_part,
-                     n_samples, lam);
+void launch_ul_colsum(const int4* chunk, int max_tiles, const float* delta, const float4* samples, const float* dtanh,
+                      float* partial, int kmax, int w0, int mg0, int ws, int mgs, hipStream_t s) {
+  hipLaunchKernelGGL(k_ul_colsum, dim3(std::max(1, std::min(max_tiles, 2048))), dim3(256), 0, s, chunk, delta, samples,
+                     dtanh, partial, kmax, w0, mg0, ws, mgs);
 }
-void launch_ulg_samples(const RayPool& pl, const ImgDesc* imgs, const int* img_order, const int* img_latent, int n_img,
-                        int nr, int n_lat, int tile, const UlGroup& in, int* bsum, int* boff, int* seg_base,
-                        int* seg_total, int* seg_padded, int* n_samples, float4* samples, int* sample_lat,
-                        hipStream_t s) {
-  const int bpl = (int)nblk(nr, 256);
-  hipLaunchKernelGGL(k_ulg_count, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, bsum);
-  hipLaunchKernelGGL(k_samples_scan, dim3(1), dim3(1024), 0, s, bsum, n_img, bpl, img_order, img_latent, 0, tile,
-                     n_lat, boff, seg_base, seg_total, seg_padded, nullptr, n_samples,
-                     PadOut{samples, sample_lat, nullptr, nullptr, nullptr});
-  hipLaunchKernelGGL(k_ulg_write, dim3(bpl, n_img), dim3(256), 0, s, pl, imgs, img_order, in, boff, samples,
-                     sample_lat);
-}
-void launch_ulg_lambda(const RayPool& pl, const ImgDesc* imgs, const int* img_order, int n_img, int nr,
-                       const UlGroup& in, const int* boff, const float4* samples, const float* gp_part, float* gm,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(k_ulg_lambda, dim3(nblk(nr, 256), n_img), dim3(256), 0, s, pl, imgs, img_order, in, boff,
-                     samples, gp_part, gm);
-}
-void launch_ul_colsum(const float* delta, const float* gm, const int* n_samples, int max_samples, int w0, int ws,
-                      int kmax, float* partial, hipStream_t s) {
-  const int grid = std::max(1, std::min(max_samples / 64, 1024));
-  hipLaunchKernelGGL(k_ul_colsum, dim3(grid), dim3(256), 0, s, delta, gm, n_samples, w0, ws, kmax, partial);
-}
-void launch_ul_split(const RayPool& pl, const ImgDesc* imgs, const int* img_order, int n_img, int max_parents,
-                     int plvl, float* lam, hipStream_t s) {
-  hipLaunchKernelGGL(k_ul_split, dim3(nblk(max_parents, 256), n_img), dim3(256), 0, s, pl, imgs, img_order, plvl,
-                     lam);
+void launch_ul_total(const int* slot_lat, int n_slot, int n_lat, int tile, const double* sums, int kmax, float* partial,
+                     int* seg_base, int* seg_padded, hipStream_t s) {
+  hipLaunchKernelGGL(k_ul_total, dim3(std::min(std::max(n_slot, (int)nblk(n_lat, 256)), 1024)), dim3(256), 0, s,
+                     slot_lat, n_slot, n_lat, tile, sums, kmax, partial, seg_base, seg_padded);
 }
 void launch_color_hits(const RayPool& pl, const ImgDesc* imgs, int n_img, int hw, int* list, int* counter,
                        hipStream_t s) {
