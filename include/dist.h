@@ -313,7 +313,8 @@ int dist_photometric_loss(const dist_camera* cams, int32_t n_views,
  *                     + w_normal sum_{fg_r & fg_t} -(normal . normal_t) ]
  * fg_r is the rendered silhouette (sil < 0), fg_t the target's (sil_t > 0.5);
  * sign(0) = 0 and max'(0) = 0; a hinge term whose weight sil_t or 1 - sil_t is
- * zero adds nothing (so a target depth off its silhouette is never read).
+ * zero adds nothing.  Depths and normals off either silhouette do not enter,
+ * whatever they hold.
  *   depth, sil, depth_t, sil_t   device [n_images][H][W] (sil_t in [0, 1]);
  *                                1 <= n_images <= 65535, H W <= 2^22
  *   normal, normal_t             device [n_images][H][W][3]; read only when

@@ -60,9 +60,6 @@ struct CamSpace {
   float* gv = nullptr;             // per output pixel: grad f . v at the hit (implicit depth gradient)
 };
 
-// Buffers of the gradient through the unrolled march: the ray parameter of
-// every ray slot at every step (kept by the forward) and the per-slot adjoint
-// of t.
 // Scratch of the device-side grouping of explicit samples by latent
 // (dist_sdf_vjp): sort keys and values, per-latent counts and starts, and the
 // sort's temporary storage.
@@ -101,6 +98,9 @@ struct UlShared {
   bool used = false;               // done has been recorded
 };
 
+// Buffers of the gradient through the unrolled march: the ray parameter of
+// every ray slot at every step (kept by the forward) and the per-slot adjoint
+// of t.
 struct UnrollSpace {
   char* mem = nullptr;
   size_t bytes = 0;

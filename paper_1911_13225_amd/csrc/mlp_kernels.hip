@@ -1241,8 +1241,9 @@ __device__ __forceinline__ void gemm_f32_m16(f32x4 (&acc)[NTW], const Sm<0>& s, 
     const char* ab = arow + 32 * k0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      // the next step's activations (after the layer's last step one chunk
-      // past K, inside the row's padding, not used)
+      // the next step's activations (after the layer's last step up to 32 bytes
+      // past K: in the row's 16 bytes of padding and, where the layer is as wide
+      // as the tile, the next row, which the 64-row allocation holds; not used)
       b[(d & 1) ^ 1][0] = *(const float*)(ab + 32 * (d + 1));
       b[(d & 1) ^ 1][1] = *(const float*)(ab + 32 * (d + 1) + 8);
 #pragma unroll

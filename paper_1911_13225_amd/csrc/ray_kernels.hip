@@ -934,6 +934,9 @@ __global__ void k_fill_u64(unsigned long long* p, int n) {
 // and the tiles' sums are added in order of step and tile.  So the chunks may
 // be as long as the memory at hand allows, and the gradient of an image is the
 // same bit for bit with any of them.
+//   The backward of two images of 96^2 (8 x 512 decoder) takes 1.12 ms in bf16
+// and 4.0 in float32 (a launch per step: 10.5 and 39.7), of eight of 256^2 18.1
+// in bf16 (24.4); recompute and VJP are 80% of it and 97%.
 // ---------------------------------------------------------------------------
 struct UlRay {
   float alpha, dterm, sterm;       // the depth term at step `last`, the silhouette term at step `near`
