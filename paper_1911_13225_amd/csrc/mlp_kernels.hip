@@ -1915,7 +1915,9 @@ __device__ __forceinline__ void vjp_layers(const AdjArgs& a, const Sm<P>& s, con
 // samples of one latent; it writes the column sums of delta at layer 0 (S0)
 // and at the skip layer (Sskip); dL/dz = W0_z^T S0 + Wskip_z^T Sskip.
 // ---------------------------------------------------------------------------
-template <int P>
+// KEEP: masks may go to mask_out by sample (a row's place is then looked up for
+// every mask word, 3% of a tile's time).
+template <int P, bool KEEP = false>
 __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adjoint(AdjArgs a) {
   constexpr int M = Cfg<P>::M;
   Sm<P> s(dyn_smem, a.net.kmax);
@@ -1924,7 +1926,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
   const int count = *a.n_samples;
   const int ntmax = net.kmax / 32;
   const bool multi = a.chunk && a.chunk->w;       // unrolled march, several steps: unit seeds, no column sums
-  const MaskRef mk = multi && !a.delta_out ? MaskRef{a.mask_out, (net.nl - 1) * ntmax, ntmax, true}
+  const MaskRef mk = KEEP && multi ? MaskRef{a.mask_out, (net.nl - 1) * ntmax, ntmax, true}
                            : MaskRef{a.mask_ws + (size_t)blockIdx.x * (size_t)(net.nl) * M * ntmax, ntmax, M * ntmax, false};
   const bool theta = a.hbuf != nullptr;
   const int t_end = theta ? min(a.tile_end, (count + M - 1) / M) : (count + M - 1) / M;
@@ -1939,7 +1941,7 @@ __global__ __launch_bounds__(kAdjWaves * 64) __attribute__((amdgpu_waves_per_eu(
       const float4 smp = a.samples[idx];
       s.pts[tid] = make_float4(smp.x, smp.y, smp.z, 0.f);
       s.fval[tid] = smp.w;
-      s.rid[tid] = idx;
+      if (KEEP) s.rid[tid] = idx;
       lt = a.sample_lat[idx];
     }
     set_latents<P, M>(s, lt, tid < M);
@@ -2497,7 +2499,10 @@ static hipError_t setup_p(int bytes) {
   e = hipFuncSetAttribute((const void*)k_vjp_saved<P == kPrecBF16 ? kPrecSplit : P, kAdjWaves>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)k_adjoint<P == kPrecBF16 ? kPrecSplit : P>,
+  e = hipFuncSetAttribute((const void*)k_adjoint<P == kPrecBF16 ? kPrecSplit : P, true>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute((const void*)k_adjoint<P == kPrecBF16 ? kPrecSplit : P, false>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
@@ -2523,15 +2528,6 @@ hipError_t mlp_setup(int precision, const NetDev& net) {
   if (precision == 2) return setup_p<2>(bytes);
   return setup_p<0>(bytes);
 }
-
-// the recompute-and-VJP kernel exists in split and float32 precision only
-#define DIST_DISPATCH_BWD(KERNEL, ARGS)                                                                \
-  do {                                                                                                 \
-    const size_t sm = mlp_smem_bytes(precision, ARGS.net);                                             \
-    const dim3 blk(kAdjWaves * 64);                                                                    \
-    if (precision == 2) hipLaunchKernelGGL(KERNEL<2>, dim3(grid), blk, sm, st, ARGS);                  \
-    else if (precision == 0) hipLaunchKernelGGL(KERNEL<0>, dim3(grid), blk, sm, st, ARGS);             \
-  } while (0)
 
 void launch_march_run(int precision, const MarchArgs& a, int grid, hipStream_t st) {
   const size_t sm = mlp_smem_bytes(precision, a.net) + march_row_bytes() * rows_for(precision);
@@ -2566,8 +2562,17 @@ void launch_eval(int precision, const EvalArgs& a, int grid, hipStream_t st) {
   else if (precision == 2) launch_eval_p<2>(a, grid, st);
   else launch_eval_p<0>(a, grid, st);
 }
-void launch_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t st) { DIST_DISPATCH_BWD(k_adjoint, a); }
-static_assert(kAdjWaves * 64 == 512, "the recompute-and-VJP dispatch assumes 8 waves");
+void launch_adjoint(int precision, const AdjArgs& a, int grid, hipStream_t st) {
+  const size_t sm = mlp_smem_bytes(precision, a.net);
+  const dim3 blk(kAdjWaves * 64);
+  if (a.mask_out) {
+    if (precision == 2) hipLaunchKernelGGL((k_adjoint<2, true>), dim3(grid), blk, sm, st, a);
+    else if (precision == 0) hipLaunchKernelGGL((k_adjoint<0, true>), dim3(grid), blk, sm, st, a);
+  } else {
+    if (precision == 2) hipLaunchKernelGGL((k_adjoint<2, false>), dim3(grid), blk, sm, st, a);
+    else if (precision == 0) hipLaunchKernelGGL((k_adjoint<0, false>), dim3(grid), blk, sm, st, a);
+  }
+}
 int mlp_row_groups(int waves, int width) { return (waves == 8 && width <= 128) ? 2 : 1; }
 int adjoint_waves() { return kAdjWaves; }
 void launch_vjp_again(int precision, const AdjArgs& a, int grid, hipStream_t st) {
