@@ -236,7 +236,7 @@ int dist_render_bwd_camera(dist_ctx* ctx, const dist_saved* saved,
  * step (the recompute of App. B.2) and back-propagated, costing about two
  * decoder passes per march query; only the scalar adjoint of t runs in reverse
  * over the marching steps, so several steps share a launch.  The memory for
- * that (up to 512 MB or one step, if that is more) is one block per context,
+ * that (about 512 MB, or one step if that is more) is one block per context,
  * taken if there is room for it and given back when another allocation of the
  * context finds none; without it, and under graph capture, fewer steps share a
  * launch and the result is the same.

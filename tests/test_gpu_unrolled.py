@@ -154,3 +154,33 @@ def test_unrolled_gradient_in_a_graph(prec):
         torch.cuda.synchronize()
     out["saved"].free()
     ctx.close()
+
+
+def test_unrolled_gradients_on_two_streams():
+    """Calls on two streams share the context's block of memory and wait for
+    each other's use of it."""
+    from paper_1911_13225_amd import api
+    spec = di.C1_SPEC
+    prm = di.TraceParams(max_steps=50, c2f_levels=2, precision=1, want_normals=0, keep_history=1)
+    z = torch.tensor(di.make_latents(1, spec.latent_dim, sigma=0.05), device="cuda")
+    ctx = context(spec)
+    handles = []
+    for side, seed in ((64, 2000), (96, 3000)):
+        out = api.dist_render_fwd(ctx, di.random_sphere_cameras(2, side, side, base_seed=seed), z, prm, save=True)
+        handles.append((out["saved"], torch.isfinite(out["depth"]).float()))
+    call = lambda i: api.dist_render_bwd_unrolled(ctx, handles[i][0], handles[i][1], torch.ones_like(handles[i][1]),
+                                                  n_latents=1)
+    ref = [call(0), call(1)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = []
+    for _ in range(6):
+        for i in (0, 1):
+            with torch.cuda.stream(streams[i]):
+                got.append((i, call(i)))
+    torch.cuda.synchronize()
+    for i, g in got:
+        assert torch.equal(g, ref[i])
+    for s, _ in handles:
+        s.free()
+    ctx.close()
